@@ -379,7 +379,7 @@ int edm_knn(edm_ctx *ctx, const float *x, int64_t L, int32_t E, int32_t tau, int
   if (edm::n_query(L, E, tau, Tp) - 1 - 2 * static_cast<int64_t>(ctx->excl) < (k ? k : E + 1))
     return set_err(ctx, EDM_E_SHORT, "series too short for k neighbours outside the exclusion radius");
   if (ctx->form == EDM_FORM_CHOSEN && tau == 1 && (k == 0 || k == E + 1) && dist == nullptr &&
-      E >= edm::kGramEMin && L <= edm::kGramLMax && ctx->excl == 0) {
+      E >= edm::kGramEMin && L <= edm::kGramLMax && ctx->excl == 0 && !edm::knn_splits(L)) {
     // Chosen form: the table of one E through the matrix-core filter (the
     // filtered group scan in table mode; the group's other lists stay idle).
     const int64_t nq = L - (E - 1) - Tp;

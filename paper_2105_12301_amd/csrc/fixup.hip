@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
     int qi[K];
 #pragma unroll
     for (int r = 0; r < K; ++r) qi[r] = r < pos ? kp[r] : (r == pos ? m1 : kp[r - 1 < 0 ? 0 : r - 1]);
-    finish_list<E, 0, K, E>(a, row, pq, L, 0, a.need, vp, qi, x);
+    finish_list<E, E>(a, row, pq, L, 0, a.need, vp, qi, x);
   }
 }
 
@@ -139,47 +139,31 @@ __global__ __launch_bounds__(256) void k_scan_queries(KnnArgs a, int slot0) {
   const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
   const int p_first = (m1 - 1 < K) ? 0 : m1;
   for (int p = p_first + wave; p < m0; p += static_cast<int>(blockDim.x) / kWave) {
-    float qk[K];
-    int qi[K];
+    double l[K];
 #pragma unroll
-    for (int i = 0; i < K; ++i) {
-      qk[i] = __builtin_inff();
-      qi[i] = -1;
-    }
+    for (int i = 0; i < K; ++i) l[i] = entry_empty();
     for (int q = lane; q < m0; q += kWave) {
       const float kq = q == p ? __builtin_inff() : canon_key<E>(fx_xs, p, q);
-      if (kq < qk[K - 1]) slice_insert<0, K, K>(qk, qi, kq, q);
+      if (kq < entry_key(l[K - 1])) list_insert<0, K, K>(l, entry(kq, q));
     }
     int ri[K];
 #pragma unroll
     for (int r = 0; r < K; ++r) {
-      float bk = qk[0];
-      int bi = qi[0];
+      double best = l[0];
 #pragma unroll
-      for (int m = 1; m < kWave; m <<= 1) {
-        const float ok = __shfl_xor(bk, m);
-        const int oi = __shfl_xor(bi, m);
-        if (ok < bk || (ok == bk && static_cast<uint32_t>(oi) < static_cast<uint32_t>(bi))) {
-          bk = ok;
-          bi = oi;
-        }
-      }
-      ri[r] = bi;
-      if (bi >= 0 && qi[0] == bi) {  // this lane held the winner: drop it
+      for (int m = 1; m < kWave; m <<= 1) best = entry_min(best, __shfl_xor(best, m));
+      ri[r] = entry_idx(best);
+      if (entry_idx(l[0]) == ri[r]) {  // this lane held the winner (or is empty): drop it
 #pragma unroll
-        for (int i = 0; i < K - 1; ++i) {
-          qk[i] = qk[i + 1];
-          qi[i] = qi[i + 1];
-        }
-        qk[K - 1] = __builtin_inff();
-        qi[K - 1] = -1;
+        for (int i = 0; i < K - 1; ++i) l[i] = l[i + 1];
+        l[K - 1] = entry_empty();
       }
     }
     if (lane == 0) {
       float vp[E];
 #pragma unroll
       for (int j = 0; j < E; ++j) vp[j] = fx_xs[p + j];
-      finish_list<E, 0, K, E>(a, row, p, L, 0, a.need, vp, ri, fx_xs);
+      finish_list<E, E>(a, row, p, L, 0, a.need, vp, ri, fx_xs);
     }
   }
 }

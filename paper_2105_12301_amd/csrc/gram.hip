@@ -65,6 +65,7 @@
 
 #include "../../include/edm.h"
 #include "device_common.h"
+#include "group_scan.h"
 #include "kernels.h"
 #include "scan_common.h"
 
@@ -315,11 +316,6 @@ __device__ __forceinline__ uint32_t tile_of(uint32_t code) {
   return (code & 15u) | ((code >> 4) & 0xf0u) | ((code >> 8) & 0xf00u);
 }
 
-// (key, index) order with the index compared unsigned (index -1 sorts last).
-__device__ __forceinline__ bool lex_less(float ka, int ia, float kb, int ib) {
-  return ka < kb || (ka == kb && static_cast<uint32_t>(ia) < static_cast<uint32_t>(ib));
-}
-
 // Final step (Section 2.1 step 3) for dimension E of query p, E one of E0
 // and E1 = E0 + 1 (or E0 alone when E1 == E0): the same float64 arithmetic,
 // in the same order, as finish_list, with the lag and neighbour counts set
@@ -427,6 +423,8 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
   constexpr int C0 = Lay::kFirst;
   __shared__ Mom wmom[kGramWaves][NG];
   const uint32_t need = a.need_dev ? a.need_dev[row] : a.need;
+  constexpr uint32_t kOfGroup = ((1u << EHI) - 1u) & ~((1u << (ELO - 1)) - 1u);
+  if (a.mom == nullptr ? (need & kOfGroup) == 0u : ELO > a.E_max) return;  // no list of the group is wanted
   const float *__restrict__ x = a.X + static_cast<int64_t>(row) * a.ldx;
   const int L = static_cast<int>(a.L_dev ? a.L_dev[row] : a.L_uni);
   const int Tp = a.Tp;
@@ -489,7 +487,7 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
 
   // Lists of E that are not needed (or whose range ends before p) stay idle.
   auto list_active = [&](int E) {
-    return p < L - (E - 1) - Tp && (a.mom != nullptr || ((need >> (E - 1)) & 1u));
+    return p < L - (E - 1) - Tp && E <= a.E_max && (a.mom != nullptr || ((need >> (E - 1)) & 1u));
   };
   bool act_any = false;
   static_for<ELO, EHI>([&](auto EC) { act_any = act_any || list_active(decltype(EC)::value); });
@@ -724,17 +722,13 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
     });
   }
 
-  float qk[TOT];
-  int qi[TOT];
+  double l[TOT];
   static_for<ELO, EHI>([&](auto EC) {
     constexpr int E = decltype(EC)::value;
     constexpr int OFF = list_off<ELO>(E);
     const bool act = list_active(E);
 #pragma unroll
-    for (int i = 0; i < E + 1; ++i) {
-      qk[OFF + i] = act ? __builtin_inff() : -1.0f;
-      qi[OFF + i] = -1;
-    }
+    for (int i = 0; i < E + 1; ++i) l[OFF + i] = act ? entry_empty() : entry_idle();
   });
 
   // Pass 2: every E's threshold rides in the products, so the estimate of
@@ -750,13 +744,13 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
       constexpr int E = decltype(EC)::value;
       constexpr int g = E - ELO;
       constexpr int OFF = list_off<ELO>(E);
-      const float own = qk[OFF + E];
+      const float own = entry_key(l[OFF + E]);
       // K-th smallest key of the query's two half-lists together: the largest
       // elementwise minimum of one sorted list against the other reversed.
       float kth = ub[g];
       float u = -__builtin_inff();
 #pragma unroll
-      for (int i = 0; i <= E; ++i) u = fmaxf(u, fminf(qk[OFF + i], __shfl_xor(qk[OFF + E - i], 32)));
+      for (int i = 0; i <= E; ++i) u = fmaxf(u, fminf(entry_key(l[OFF + i]), __shfl_xor(entry_key(l[OFF + E - i]), 32)));
       kth = fminf(kth, u);
       const float T = own < 0.0f ? -kGramBig : fminf((kth - nq[g]) + kGramFloor, kGramBig);
       set_threshold<Lay>(bh[g][NCH - 1 - C0], bl[g][NCH - 1 - C0], T, h1);
@@ -794,14 +788,12 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
         exact_keys2(q0, has0 && q0 != p, key0, q1, has1 && q1 != p, key1);
         static_for<ELO, EHI>([&](auto EC) {
           constexpr int E = decltype(EC)::value;
-          // The empty asm hides the +inf of idle lanes from the optimiser,
-          // which would otherwise branch around the insertion.
-          float kin0 = key0[E - ELO], kin1 = key1[E - ELO];
-          asm volatile("" : "+v"(kin0), "+v"(kin1));
-          if (__builtin_amdgcn_ballot_w64(kin0 < qk[list_off<ELO>(E) + E]))
-            slice_insert<list_off<ELO>(E), E + 1, TOT>(qk, qi, kin0, q0);
-          if (__builtin_amdgcn_ballot_w64(kin1 < qk[list_off<ELO>(E) + E]))
-            slice_insert<list_off<ELO>(E), E + 1, TOT>(qk, qi, kin1, q1);
+          constexpr int OFF = list_off<ELO>(E);
+          const float kin0 = key0[E - ELO], kin1 = key1[E - ELO];
+          if (__builtin_amdgcn_ballot_w64(kin0 < entry_key(l[OFF + E])))
+            list_insert<OFF, E + 1, TOT>(l, entry(kin0, q0));
+          if (__builtin_amdgcn_ballot_w64(kin1 < entry_key(l[OFF + E])))
+            list_insert<OFF, E + 1, TOT>(l, entry(kin1, q1));
         });
       } else {
         const bool has = it < nsv;
@@ -810,10 +802,10 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
         exact_keys(q, has && q != p, key);
         static_for<ELO, EHI>([&](auto EC) {
           constexpr int E = decltype(EC)::value;
-          float kin = key[E - ELO];
-          asm volatile("" : "+v"(kin));
-          if (__builtin_amdgcn_ballot_w64(kin < qk[list_off<ELO>(E) + E]))
-            slice_insert<list_off<ELO>(E), E + 1, TOT>(qk, qi, kin, q);
+          constexpr int OFF = list_off<ELO>(E);
+          const float kin = key[E - ELO];
+          if (__builtin_amdgcn_ballot_w64(kin < entry_key(l[OFF + E])))
+            list_insert<OFF, E + 1, TOT>(l, entry(kin, q));
         });
       }
     }
@@ -867,58 +859,13 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
   flush();
 
   // Each query's two half-lists -> its full list (both lanes end equal).
-  // [own list ascending, maxima, partner list descending] is bitonic; its
-  // first half-cleaner stage (elementwise minimum) leaves the N smallest as a
-  // bitonic sequence, and the remaining stages sort it.  Blocks that start at
-  // or beyond K only order entries that are dropped, so they are skipped.
-  // Order: (key, index) lexicographic, the index unsigned (empty entries last).
   static_for<ELO, EHI>([&](auto EC) {
     constexpr int E = decltype(EC)::value;
-    constexpr int K = E + 1;
     constexpr int OFF = list_off<ELO>(E);
-    constexpr int N = K <= 8 ? 8 : (K <= 16 ? 16 : 32);
-    static_assert(N - K < K, "every position of the lower half holds an entry");
-    float ck[N];
-    int ci[N];
+    double other[E + 1];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int j = N - 1 - i;  // partner entry facing position i, if j < K
-      float pk = 0.0f;
-      int pi = 0;
-      if (j < K) {
-        pk = __shfl_xor(qk[OFF + j], 32);
-        pi = __shfl_xor(qi[OFF + j], 32);
-      }
-      if (i < K && j < K) {
-        const bool lt = lex_less(pk, pi, qk[OFF + i], qi[OFF + i]);
-        ck[i] = lt ? pk : qk[OFF + i];
-        ci[i] = lt ? pi : qi[OFF + i];
-      } else if (i < K) {
-        ck[i] = qk[OFF + i];
-        ci[i] = qi[OFF + i];
-      } else {
-        ck[i] = pk;
-        ci[i] = pi;
-      }
-    }
-#pragma unroll
-    for (int d = N / 2; d > 0; d >>= 1)
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-        if ((i & d) == 0 && (i & ~(2 * d - 1)) < K) {
-          const bool sw = lex_less(ck[i + d], ci[i + d], ck[i], ci[i]);
-          const float k0 = ck[i], k1 = ck[i + d];
-          const int i0 = ci[i], i1 = ci[i + d];
-          ck[i] = sw ? k1 : k0;
-          ci[i] = sw ? i1 : i0;
-          ck[i + d] = sw ? k0 : k1;
-          ci[i + d] = sw ? i0 : i1;
-        }
-#pragma unroll
-    for (int i = 0; i < K; ++i) {
-      qk[OFF + i] = ck[i];
-      qi[OFF + i] = ci[i];
-    }
+    for (int i = 0; i < E + 1; ++i) other[i] = __shfl_xor(l[OFF + i], 32);
+    list_merge<OFF, E + 1, TOT>(l, [&](int j) { return other[j]; });
   });
 
   // Epilogue: E alternates between the two lanes of a query.  The co-moments
@@ -934,8 +881,8 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
     int idx[K1];
 #pragma unroll
     for (int i = 0; i < K1; ++i) {
-      const int lo_i = i < E0 + 1 ? qi[list_off<ELO>(E0) + i] : -1;
-      idx[i] = up ? qi[list_off<ELO>(E1) + i] : lo_i;
+      const int lo_i = i < E0 + 1 ? entry_idx(l[list_off<ELO>(E0) + i]) : -1;
+      idx[i] = up ? entry_idx(l[list_off<ELO>(E1) + i]) : lo_i;
     }
     Mom mine = mom_zero();
     if (!h1 || up) mine = finish_round<E0, E1>(a, row, p, L, Tp, need, idx, up ? E1 : E0, XG ? x : xs);
@@ -952,7 +899,7 @@ __device__ __forceinline__ void gram_scan(const KnnArgs &a, const int row, const
     const int g = static_cast<int>(threadIdx.x);
     const int E = ELO + g;
     const int mE = L - (E - 1) - Tp;
-    if (mE - 1 >= E + 1 && blk0 < mE) {
+    if (E <= a.E_max && mE - 1 >= E + 1 && blk0 < mE) {
       Mom t = mom_merge(wmom[0][g], wmom[1][g]);
 #pragma unroll
       for (int w = 1; w < kGramWaves / 2; ++w) t = mom_merge(t, mom_merge(wmom[2 * w][g], wmom[2 * w + 1][g]));
@@ -973,6 +920,25 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(KnnArgs a, int slot0, int
   const int row = (s / nblk) * kGramXcds + x;
   if (row >= nslots) return;  // padding of the last die round (uniform)
   gram_scan<ELO, EHI, XG>(a, slot0 + row, s % nblk, gram_smem);
+}
+
+// Few workgroups: every group of the sweep in one launch (blockIdx.z), so that
+// they run side by side instead of one after the other on a mostly idle chip.
+// The exact E 1-4 scan splits each query's candidates over two waves.  The
+// longest groups start first.
+constexpr int kSmallZ = 7;
+__global__ __launch_bounds__(kGramThreads) void k_sweep_small(KnnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) float gram_smem[];
+  const int row = static_cast<int>(blockIdx.y), bx = static_cast<int>(blockIdx.x);
+  switch (blockIdx.z) {
+    case 0: gram_scan<14, 16, false>(a, row, bx, gram_smem); break;
+    case 1: gram_scan<19, 20, false>(a, row, bx, gram_smem); break;
+    case 2: gram_scan<5, 8, false>(a, row, bx, gram_smem); break;
+    case 3: gram_scan<17, 18, false>(a, row, bx, gram_smem); break;
+    case 4: group_scan<1, 4, 4, 2>(a, row, bx, gram_smem); break;
+    case 5: gram_scan<9, 11, false>(a, row, bx, gram_smem); break;
+    default: gram_scan<12, 13, false>(a, row, bx, gram_smem); break;
+  }
 }
 
 // Centring constant of each slot: the float32 mean (float64 sum).
@@ -1073,7 +1039,41 @@ size_t gram_shm(int64_t ld, bool xg) {
          sizeof(uint32_t) * kQueueCap * kGramThreads;
 }
 
+size_t small_lds(int64_t L_max) {
+  const size_t exact = static_cast<size_t>(scan_floats(L_max)) * sizeof(float) + group_extra_lds<1, 4, 4, 2>();
+  const size_t filter = gram_shm(gram_ld(L_max), false);
+  return exact > filter ? exact : filter;
+}
+
+// Blocks of 256 queries up to which a sweep takes the one-launch form: its 7
+// groups then make up to two rounds of workgroups on 256 compute units.
+constexpr int64_t kSmallBlocks = 64;
+
 }  // namespace
+
+bool gram_sweep_is_small(int nslots, int64_t L_max) {
+  return (L_max + kKnnThreads - 1) / kKnnThreads * nslots <= kSmallBlocks && !use_global_x(L_max) &&
+         small_lds(L_max) <= static_cast<size_t>(kScanLdsMax);
+}
+
+hipError_t launch_gram_small(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  if (nslots <= 0) return hipSuccess;
+  if (L_max > kGramLMax || a.gram_ld < L_max + kGramPad || a.tau != 1 || !gram_sweep_is_small(nslots, L_max))
+    return hipErrorInvalidValue;
+  KnnArgs b = a;
+  b.lds_x = scan_floats(L_max);
+  b.gram_lds = gram_ld(L_max);
+  const size_t shm = small_lds(L_max);
+  if (shm > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sweep_small),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
+    if (e != hipSuccess) return e;
+  }
+  TimedLaunch timed(EDM_KF_FILTER_SCAN, st);
+  const unsigned gx = static_cast<unsigned>((L_max + kKnnThreads - 1) / kKnnThreads);
+  hipLaunchKernelGGL(k_sweep_small, dim3(gx, static_cast<unsigned>(nslots), kSmallZ), dim3(kGramThreads), shm, st, b);
+  return hipGetLastError();
+}
 
 hipError_t launch_gram_prep(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
   if (nslots <= 0) return hipSuccess;

@@ -38,6 +38,7 @@ struct KnnArgs {
   int32_t E, tau, Tp, k;
   int32_t excl;              // exclusion radius: candidates with |q - p| <= excl are skipped
   int32_t p1_stride;         // filter pass 1 visits one candidate tile in p1_stride (0: by group and length)
+  int32_t lds_x;             // floats of the staged series in LDS (set by the launchers)
   int32_t *idx;              // [slot][nq][k] or nullptr
   float *dist;               // [slot][nq][k] or nullptr
   float *w;                  // [slot][nq][k] or nullptr
@@ -109,6 +110,10 @@ hipError_t launch_tables_persistent(const KnnArgs &a, int group, const TableItem
                                     int n_items, int *counter, int64_t L_max, int wg_per_cu,
                                     int n_cu, hipStream_t st);
 
+// Blocks of 256 queries that one table item of `group` covers in a launch whose
+// longest series has L_max samples (items then start at multiples of it).
+int tables_item_blocks(int group, int64_t L_max);
+
 // Matrix-core filter of the batched scans (gram.hip).  E values from
 // kGramEMin up run through it when KnnArgs::gram_nrm is set; kGramLMax bounds
 // the series length (LDS holds the BF16 halves of the series, and its float32
@@ -128,6 +133,10 @@ hipError_t launch_gram_prep(const KnnArgs &a, int nslots, int64_t L_max, hipStre
 // same outputs as launch_sweep_multi.
 hipError_t launch_gram_group(const KnnArgs &a, int lo, int hi, int nslots, int64_t L_max,
                              hipStream_t st);
+// The whole sweep (or every needed table) of E 1..20 in one launch, exact E
+// 1-4 included, for calls of few workgroups.
+bool gram_sweep_is_small(int nslots, int64_t L_max);
+hipError_t launch_gram_small(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st);
 // Work-list form for the plan: items (row, blk) of filtered group g
 // (kGramGroups[g]), table mode, one workgroup per item; same outputs as
 // launch_tables_persistent.  L_max bounds the rows of the items; a.gram_ld
@@ -144,6 +153,12 @@ hipError_t launch_tables_from_sweep(const KnnArgs &a, int E, int nslots, int64_t
 // Launch the kNN kernel for `nslots` libraries whose longest series has
 // `L_max` samples.  Returns a hipError_t.
 hipError_t launch_knn(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st);
+
+// Whether the exact scan of one library of L samples splits its candidates over
+// 16 waves (too few workgroups to fill the chip): it then beats the filter.
+bool knn_splits(int64_t L);
+// The part of launch_knn for lags above 1 and free neighbour counts.
+hipError_t launch_knn_lagged(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st);
 
 // Tables of one library (a.X, a.L_uni, tau, Tp, E, k = E+1, a.excl) whose
 // candidates are restricted to subsamples: set s holds the ascending member

@@ -1,0 +1,268 @@
+// All k-nearest-neighbour tables, fused with the time-delay embedding and the
+// simplex weights (kEDM paper: Section 2.1 steps 1-3, Algorithms 1 and 2).
+//
+// Design for gfx950
+// -----------------
+// * The paper materialises the L x L distance matrix (Algorithm 1) and then
+//   partially sorts each row (Algorithm 2).  Here nothing of size L^2 ever
+//   leaves the compute unit: each workgroup stages its library series once in
+//   LDS (<= 128 KiB of the 160 KiB per CU), each lane owns one query point,
+//   keeps its E coordinates and its sorted top-k (key, index) list in VGPRs,
+//   and streams every candidate through them.  The embedding is never stored
+//   (Section 3.3.1 fuses it for the same reason).
+// * Diagonal scan: at step s, lane l of a wave whose queries are p0..p0+63
+//   evaluates candidate q = s + l.  Consecutive queries have time-shifted
+//   neighbourhoods (v_{p+1} shares E-1 coordinates with v_p), so their top-k
+//   insertions fall on the same step and the wave diverges far less often
+//   than with every lane looking at the same candidate.  Every lane still
+//   visits its candidates in ascending q, so a strict "<" against the k-th key
+//   is the whole test (a later equal key has the larger index), and the self
+//   step q = p is the same step s = p0 for the whole wave (as is every step of an
+//   exclusion window |q - p| <= r: q - p = s - p0 for every lane).
+// * tau = 1: each lane keeps a sliding window of E + U - 1 samples in
+//   registers and loads one new LDS word per candidate, so the key costs
+//   exactly E subtractions, E multiplies and E adds of float32 VALU work.
+// * The ranking key is the float32 sum of Algorithm 1 in lag order with a
+//   rounding after every operation: this file is compiled with contraction off
+//   (and says so with a pragma), and fp32 denormals are kept (gfx950 default).
+// * Improving candidates are queued in LDS and inserted in batches
+//   (topk_list.h).  What bounds the scan is VALU issue: 3 E + ~20 instructions a
+//   step (10000 x 2000, E = 20: 54 ms against 31 ms for its 61 operations a
+//   pair at one a lane and clock; E = 1..20 together about 1100 -> 595 ms).
+// * Few workgroups (one series): the candidates of a query are split over 4 or
+//   16 waves whose lists are merged (one series of 1000, E = 3: 86 -> 15 us;
+//   10000 samples, E = 20: 560 us through the filter -> 277 us).
+// * Weights need only the k winners: their distances are recomputed in
+//   float64 from the staged samples, w_i = exp(-d_i / d_min) normalised
+//   (Section 2.1 step 3, "Normalize D_k" in Algorithm 2).
+// * Sweep mode fuses the self-prediction and its Pearson co-moments into the
+//   epilogue, so the E sweep writes no table at all.
+#pragma once
+
+#include "../../include/edm.h"
+#include "device_common.h"
+#include "kernels.h"
+#include "scan_common.h"
+#include "topk_list.h"
+
+#pragma clang fp contract(off)
+
+namespace edm {
+namespace {
+
+// Waves per SIMD the registers are kept to: four, or three where the list, the
+// window and the query's samples do not fit 128 registers (16-wave workgroups
+// have no choice).
+constexpr int knn_waves(int E, int threads) { return threads > 512 ? 4 : (E == 0 || E >= 15 ? 3 : 4); }
+
+// Q, S: layout of the workgroup (topk_list.h).
+template <int E_T, int K, bool T1, int Q, int S>
+__global__ __launch_bounds__(kWave * Q * S, knn_waves(E_T, kWave * Q * S)) void k_knn(KnnArgs a, int slot0) {
+  constexpr int EM = E_T ? E_T : EDM_E_MAX;
+  constexpr int kT = kWave * Q * S;
+  extern __shared__ __attribute__((aligned(16))) float knn_smem[];
+  __shared__ Mom wmom[Q];
+
+  const int slot = slot0 + static_cast<int>(blockIdx.y);
+  const int row = a.lib_ids ? a.lib_ids[slot] : slot;
+  const float *__restrict__ x = a.X + static_cast<int64_t>(row) * a.ldx;
+  const int L = static_cast<int>(a.L_dev ? a.L_dev[row] : a.L_uni);
+  const int E = E_T ? E_T : a.E;
+  const int tau = T1 ? 1 : a.tau;
+  const int off = (E - 1) * tau;
+  const int m = L - off - a.Tp;  // queries = candidates
+  const int excl = a.excl;       // exclusion radius: |q - p| <= excl is no candidate
+  if (m - 1 - 2 * excl < K) return;  // infeasible for this series (uniform)
+  const int blk0 = static_cast<int>(blockIdx.x) * (kWave * Q);
+  if (blk0 >= m) return;
+
+  const float *xs = stage_scan<kT>(x, L, knn_smem, a.status);
+
+  const int lane = threadIdx.x & (kWave - 1);
+  // wave-uniform: readfirstlane lets the compiler keep them (and the self step) scalar
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave);
+  const int qg = wave % Q, sp = wave / Q;
+  const int p0 = blk0 + qg * kWave;
+  const int p = p0 + lane;
+  const bool active = p < m;
+
+  float vp[EM];
+#pragma unroll
+  for (int j = 0; j < EM; ++j) vp[j] = (active && (E_T || j < E)) ? xs[p + j * tau] : 0.0f;
+
+  double l[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) l[i] = active ? entry_empty() : entry_idle();
+  double *const extra = reinterpret_cast<double *>(knn_smem + a.lds_x);
+  Pending pend(extra);
+  auto flush = [&]() { pend.drain([&](double e) { list_insert<0, K, K>(l, e); }); };
+
+  if (p0 < m) {  // wave-uniform: a wave with no query skips the scan
+    // steps s = -(kWave - 1) .. m - 1; split sp takes one contiguous share
+    const int share = (m + kWave - 1 + S - 1) / S;
+    const int s0 = -(kWave - 1) + sp * share;
+    const int s_end = s0 + share < m ? s0 + share : m;
+    auto offer = [&](int s, float acc, int q, bool valid) {
+      // T1: a lane's candidates come in ascending q; otherwise the residues
+      // are walked one by one and equal keys are ordered by the entry
+      const bool lt = T1 ? acc < entry_key(l[K - 1]) : entry(acc, q) < l[K - 1];
+      pend.push(entry(acc, q), valid && abs(s - p0) > excl && lt);
+    };
+    auto in_range = [&](int s, int q) { return s < s_end && static_cast<unsigned>(q) < static_cast<unsigned>(m); };
+    auto check = [&]() {
+      if (pend.full()) flush();
+    };
+    if constexpr (E_T > 0) {
+      const int s_full = m - (kWave - 1) < s_end ? m - (kWave - 1) : s_end;  // below: every lane's q < m
+      scan_steps<E_T, E_T, T1, kPendStep>(
+          vp, xs, lane, tau, s0, s_end, s_full,
+          [&](int s, int q, const float(&key)[1], auto edge) {
+            offer(s, key[0], q, !decltype(edge)::value || in_range(s, q));
+          },
+          check);
+    } else {
+#pragma unroll 1
+      for (int s = s0; s < s_end; ++s) {
+        const int q = s + lane;
+        const bool valid = in_range(s, q);
+        const int qc = valid ? q : 0;
+        float acc = 0.0f;
+#pragma unroll
+        for (int j = 0; j < EM; ++j) {
+          if (j < E) {
+            const float d = vp[j] - xs[qc + j * tau];
+            acc = acc + d * d;
+          }
+        }
+        offer(s, acc, q, valid);
+        check();
+      }
+    }
+    flush();
+  }
+  if constexpr (S > 1) {  // (the queues are drained: their LDS serves the merge)
+    merge_splits<Q, S, 0, K, K>(l, extra);
+  }
+  int qi[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) qi[i] = entry_idx(l[i]);
+
+  // Epilogue: float64 distances of the k winners, weights, outputs.  The
+  // loops over the winners stay rolled and rotate the register lists by one
+  // slot per trip, so only one neighbour's coordinates are live at a time.
+  Mom mine = mom_zero();
+  if (active && sp == 0) {
+    double D[K];  // distance, then weight, of neighbour qi[i]
+    float Df[K];  // distance rounded for output
+    double dmin = __builtin_inf();
+#pragma unroll 1
+    for (int r = 0; r < K; ++r) {
+      // A slot stays unfilled (-1) only if non-finite input made keys NaN;
+      // the status word reports that case, and index 0 keeps tables in range.
+      const int q = qi[0] < 0 ? 0 : qi[0];
+      double s2 = 0.0;
+#pragma unroll
+      for (int j = 0; j < EM; ++j) {
+        if (E_T || j < E) {
+          const double d = static_cast<double>(vp[j]) - static_cast<double>(xs[q + j * tau]);
+          s2 += d * d;
+        }
+      }
+      const double dq = sqrt(s2);
+      dmin = fmin(dmin, dq);
+#pragma unroll
+      for (int i = 0; i < K - 1; ++i) {
+        qi[i] = qi[i + 1];
+        D[i] = D[i + 1];
+        Df[i] = Df[i + 1];
+      }
+      qi[K - 1] = q;
+      D[K - 1] = dq;
+      Df[K - 1] = static_cast<float>(dq);
+    }
+    double wsum = 0.0;
+#pragma unroll 1
+    for (int r = 0; r < K; ++r) {
+      const double d = D[0];
+      const double wq = dmin > 0.0 ? exp(-d / dmin) : (d == 0.0 ? 1.0 : 0.0);
+      wsum += wq;
+#pragma unroll
+      for (int i = 0; i < K - 1; ++i) D[i] = D[i + 1];
+      D[K - 1] = wq;
+    }
+    const double inv = 1.0 / wsum;
+    const int64_t base = static_cast<int64_t>(slot) * a.tbl_stride + static_cast<int64_t>(p) * K;
+    if (a.idx) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) a.idx[base + i] = qi[i];
+    }
+    if (a.dist) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) a.dist[base + i] = Df[i];
+    }
+    if (a.w) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) a.w[base + i] = static_cast<float>(D[i] * inv);
+    }
+    if (a.mom) {
+      const int o_off = off + a.Tp;
+      double yh = 0.0;
+#pragma unroll
+      for (int i = 0; i < K; ++i) yh += (D[i] * inv) * static_cast<double>(xs[qi[i] + o_off]);
+      mine.n = 1.0;
+      mine.mo = static_cast<double>(xs[p + o_off]);
+      mine.mp = yh;
+    }
+  }
+  if constexpr (Q >= 4) {
+    if (a.mom) {  // uniform
+      if (sp == 0) {
+        const Mom wv = mom_wave_reduce(mine);
+        if (lane == 0) wmom[qg] = wv;
+      }
+      __syncthreads();
+      const int t4 = static_cast<int>(threadIdx.x) * 4;  // thread i merges the block of waves 4 i ..
+      if (t4 < Q && blk0 + t4 * kWave < m) {
+        Mom t = wmom[t4];
+#pragma unroll
+        for (int i = 1; i < kKnnThreads / kWave; ++i) t = mom_merge(t, wmom[t4 + i]);
+        a.mom[(static_cast<int64_t>(row) * a.E_max + (E - 1)) * a.mom_blocks + blockIdx.x * (Q / 4) + threadIdx.x] = t;
+      }
+    }
+  }
+}
+
+template <int E_T, int K, bool T1, int Q, int S>
+hipError_t launch_one(KnnArgs a, int nslots, int64_t L_max, hipStream_t st) {
+  const void *fn = reinterpret_cast<const void *>(&k_knn<E_T, K, T1, Q, S>);
+  const size_t shm = static_cast<size_t>(scan_lds<Q, S>(L_max, K, a.lds_x));
+  if (shm > 65536) {
+    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       static_cast<int>(shm));
+    if (e != hipSuccess) return e;
+  }
+  constexpr int kMaxY = 32768;
+  const unsigned gx = static_cast<unsigned>((L_max + kWave * Q - 1) / (kWave * Q));
+  for (int s0 = 0; s0 < nslots; s0 += kMaxY) {
+    const int ny = nslots - s0 < kMaxY ? nslots - s0 : kMaxY;
+    hipLaunchKernelGGL((k_knn<E_T, K, T1, Q, S>), dim3(gx, static_cast<unsigned>(ny)), dim3(kWave * Q * S), shm,
+                       st, a, s0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int E_T, int K, bool T1>
+hipError_t launch_layout(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  switch (scan_layout(nslots, L_max, K, a.mom != nullptr)) {
+    case ScanLayout::kTable16: return launch_one<E_T, K, T1, 1, 16>(a, nslots, L_max, st);
+    case ScanLayout::kSplit4: return launch_one<E_T, K, T1, 4, 4>(a, nslots, L_max, st);
+    case ScanLayout::kLong16: return launch_one<E_T, K, T1, 16, 1>(a, nslots, L_max, st);
+    case ScanLayout::kLong8: return launch_one<E_T, K, T1, 8, 1>(a, nslots, L_max, st);
+    default: return launch_one<E_T, K, T1, 4, 1>(a, nslots, L_max, st);
+  }
+}
+
+}  // namespace
+}  // namespace edm

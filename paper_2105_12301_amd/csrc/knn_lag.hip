@@ -1,0 +1,39 @@
+// All-kNN scans with a lag above 1, and with any number of neighbours
+// (knn_kernel.h): a translation unit of their own for the build's sake.
+#include <array>
+#include <utility>
+
+#include "knn_kernel.h"
+
+namespace edm {
+namespace {
+
+using LaunchFn = hipError_t (*)(const KnnArgs &, int, int64_t, hipStream_t);
+
+template <int K>
+hipError_t launch_generic(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  if (scan_layout(nslots, L_max, K, a.mom != nullptr) == ScanLayout::kTable16)
+    return launch_one<0, K, false, 1, 16>(a, nslots, L_max, st);
+  return launch_one<0, K, false, 4, 1>(a, nslots, L_max, st);
+}
+
+template <size_t... I>
+constexpr auto make_lagged(std::index_sequence<I...>) {
+  return std::array<LaunchFn, sizeof...(I)>{
+      &launch_layout<static_cast<int>(I) + 1, static_cast<int>(I) + 2, false>...};
+}
+template <size_t... I>
+constexpr auto make_generic(std::index_sequence<I...>) {
+  return std::array<LaunchFn, sizeof...(I)>{&launch_generic<static_cast<int>(I) + 1>...};
+}
+
+}  // namespace
+
+hipError_t launch_knn_lagged(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  static const auto lagged = make_lagged(std::make_index_sequence<EDM_E_MAX>{});
+  static const auto generic = make_generic(std::make_index_sequence<EDM_K_MAX>{});
+  const bool fast = a.k == a.E + 1 && a.E >= 1 && a.E <= EDM_E_MAX;
+  return fast ? lagged[a.E - 1](a, nslots, L_max, st) : generic[a.k - 1](a, nslots, L_max, st);
+}
+
+}  // namespace edm

@@ -404,6 +404,8 @@ __global__ __launch_bounds__(256) void k_target_means(const float *__restrict__ 
   const int64_t L = Ly_dev ? Ly_dev[t] : L_uni;
   const float *__restrict__ y = Y + t * ldy;
   double sum = 0.0;
+  // (unrolled: the loads of eight steps are in flight at once)
+#pragma unroll 8
   for (int64_t i = lane; i < L; i += kWave) sum += static_cast<double>(y[i]);
 #pragma unroll
   for (int msk = kWave / 2; msk > 0; msk >>= 1) sum += __shfl_xor(sum, msk);

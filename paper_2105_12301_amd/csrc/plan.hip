@@ -239,7 +239,8 @@ int edm_ccm_plan_create(edm_ctx *ctx, const int64_t *Lx, int64_t Nl, int64_t ldx
         if (!gm) continue;
         const int64_t m_lo = Lx[i] - (lo - 1) - Tp;
         const int64_t nb = (m_lo + edm::kKnnThreads - 1) / edm::kKnnThreads;
-        for (int64_t b = 0; b < nb; ++b)
+        const int step = c <= kNGroups ? edm::tables_item_blocks(c, B.L_max) : 1;
+        for (int64_t b = 0; b < nb; b += step)
           titems.push_back(edm::TableItem{i, static_cast<int16_t>(c), static_cast<int16_t>(b)});
       }
       B.t_count[c] = static_cast<int64_t>(titems.size()) - B.t_begin[c];

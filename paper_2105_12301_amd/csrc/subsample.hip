@@ -25,6 +25,7 @@
 #include "../../include/edm.h"
 #include "device_common.h"
 #include "kernels.h"
+#include "topk_list.h"
 
 #pragma clang fp contract(off)
 
@@ -32,28 +33,14 @@ namespace edm {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kChunk = 4096;  // member indices staged per LDS chunk
-
-template <int K>
-__device__ __forceinline__ void sub_insert(float (&qk)[K], int (&qi)[K], float key, int q) {
-#pragma unroll
-  for (int i = K - 1; i > 0; --i) {
-    const bool lt_prev = key < qk[i - 1];
-    const bool lt_cur = key < qk[i];
-    qi[i] = lt_prev ? qi[i - 1] : (lt_cur ? q : qi[i]);
-    qk[i] = __builtin_amdgcn_fmed3f(qk[i - 1], key, qk[i]);
-  }
-  const bool lt0 = key < qk[0];
-  qi[0] = lt0 ? q : qi[0];
-  qk[0] = lt0 ? key : qk[0];
-}
+constexpr int kChunk = 2048;  // member indices staged per LDS chunk
 
 // a.X / a.L_uni: the library series; a.idx / a.w: tables [set][m][K]
 // (stride a.tbl_stride); members of set s: sets[off[s] .. off[s+1]).
 template <int E_T, int K>
 __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_t *__restrict__ sets,
                                                          const int64_t *__restrict__ off) {
-  extern __shared__ float sub_smem[];
+  extern __shared__ __attribute__((aligned(16))) float sub_smem[];
   const int E = E_T;
   const int tau = a.tau;
   const int L = static_cast<int>(a.L_uni);
@@ -63,7 +50,7 @@ __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_
   const int blk0 = static_cast<int>(blockIdx.x) * kThreads;
   if (blk0 >= m) return;
   float *xs = sub_smem;
-  int32_t *mem = reinterpret_cast<int32_t *>(sub_smem + L);
+  int32_t *mem = reinterpret_cast<int32_t *>(sub_smem + (L + 1) / 2 * 2);
   const float *__restrict__ x = a.X;
   bool bad = false;
   for (int i = threadIdx.x; i < L; i += kThreads) {
@@ -78,13 +65,11 @@ __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_
   float vp[E_T];
 #pragma unroll
   for (int j = 0; j < E_T; ++j) vp[j] = 0.0f;
-  float qk[K];
-  int qi[K];
+  double l[K];
 #pragma unroll
-  for (int i = 0; i < K; ++i) {
-    qk[i] = active ? __builtin_inff() : -1.0f;  // -1: an idle lane never inserts
-    qi[i] = -1;
-  }
+  for (int i = 0; i < K; ++i) l[i] = active ? entry_empty() : entry_idle();
+  Pending pend(reinterpret_cast<double *>(mem + kChunk));
+  auto flush = [&]() { pend.drain([&](double e) { list_insert<0, K, K>(l, e); }); };
   const int64_t b0 = off[set], b1 = off[set + 1];
   __syncthreads();
 #pragma unroll
@@ -94,8 +79,7 @@ __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_
     __syncthreads();  // the previous chunk is consumed
     for (int i = threadIdx.x; i < n; i += kThreads) mem[i] = sets[c0 + i];
     __syncthreads();
-#pragma unroll 2
-    for (int i = 0; i < n; ++i) {
+    auto member = [&](int i) {
       const int q = mem[i];  // wave-uniform
       float acc = 0.0f;
 #pragma unroll
@@ -103,12 +87,25 @@ __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_
         const float d = vp[j] - xs[q + j * tau];
         acc = acc + d * d;
       }
-      const bool want = abs(q - p) > excl && acc < qk[K - 1];
-      if (__builtin_amdgcn_ballot_w64(want)) sub_insert<K>(qk, qi, want ? acc : __builtin_inff(), q);
+      pend.push(entry(acc, q), abs(q - p) > excl && acc < entry_key(l[K - 1]));
+    };
+    int i = 0;
+    for (; i + kPendStep <= n; i += kPendStep) {
+#pragma unroll
+      for (int u = 0; u < kPendStep; ++u) member(i + u);
+      if (pend.full()) flush();
+    }
+    for (; i < n; ++i) {
+      member(i);
+      if (pend.full()) flush();
     }
   }
+  flush();
   if (!active) return;
 
+  int qi[K];
+#pragma unroll
+  for (int i = 0; i < K; ++i) qi[i] = entry_idx(l[i]);
   // Epilogue: float64 distances of the K winners, d_min, weights (Section
   // 2.1 step 3), in the fused scan's order.
   double D[K];
@@ -169,7 +166,8 @@ hipError_t launch_knn_subsets(const KnnArgs &a, const int32_t *sets, const int64
     return hipErrorInvalidValue;
   const int64_t m = a.L_uni - static_cast<int64_t>(a.E - 1) * a.tau - a.Tp;
   if (m < 1) return hipSuccess;
-  const size_t shm = static_cast<size_t>(a.L_uni) * sizeof(float) + kChunk * sizeof(int32_t);
+  const size_t shm = static_cast<size_t>((a.L_uni + 1) / 2 * 2) * sizeof(float) + kChunk * sizeof(int32_t) +
+                     static_cast<size_t>(kThreads / kWave) * kPendBytes;
   const void *fn = reinterpret_cast<const void *>(fns[a.E - 1]);
   if (shm > 65536) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));

@@ -10,10 +10,11 @@
 // so the correlations) are bit-identical to one scan per E, for
 // 3*E_hi + (E_hi - E_lo + 1) VALU ops per pair instead of sum_E (3E + 1).
 //
-// Everything else follows the per-E kernel in knn.hip: library staged in LDS,
-// one query per lane, diagonal candidate order (lane l sees q = s + l), a
-// sliding window of samples in registers, insertions under a wave-uniform
-// ballot, float64 weights of the winners, the self-prediction and its Pearson
+// Everything else follows the per-E kernel in knn_kernel.h: library staged in
+// LDS, one query per lane, diagonal candidate order (lane l sees q = s + l), a
+// sliding window of samples in registers, improving candidates queued in LDS
+// and inserted in batches (10000 x 2000, Tp = 1: E 1-4 27.2 -> 22.1 ms, all
+// five groups 890 -> 391 ms against insertion as they come), float64 weights of the winners, the self-prediction and its Pearson
 // co-moments reduced per block.  tau = 1 only (the sweep's lag); other lags
 // use the per-E kernel.
 #include <array>
@@ -22,6 +23,7 @@
 #include "../../include/edm.h"
 #include "device_common.h"
 #include "kernels.h"
+#include "group_scan.h"
 #include "scan_common.h"
 
 #pragma clang fp contract(off)
@@ -29,169 +31,20 @@
 namespace edm {
 namespace {
 
-constexpr int kUnroll = 8;
-
-// One workgroup's share of a batched scan: query block `bx` of row `row`,
-// every E in [ELO, EHI].  Called by the grid kernel and by the persistent
-// kernel; every early return is uniform across the workgroup.
-template <int ELO, int EHI>
-__device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, const int bx,
-                                           float *__restrict__ xs) {
-  constexpr int NG = EHI - ELO + 1;
-  constexpr int TOT = list_off<ELO>(EHI + 1);
-  __shared__ Mom wmom[kKnnThreads / kWave][NG];
-  const uint32_t need = a.need_dev ? a.need_dev[row] : a.need;
-  const float *__restrict__ x = a.X + static_cast<int64_t>(row) * a.ldx;
-  const int L = static_cast<int>(a.L_dev ? a.L_dev[row] : a.L_uni);
-  const int Tp = a.Tp;
-  // m(E) = queries = candidates at dimension E (tau = 1)
-  const int m_lo = L - (ELO - 1) - Tp;
-  const int m_hi = L - (EHI - 1) - Tp;
-  if (m_lo - 1 < ELO + 1) return;  // no E of the group is feasible
-  const int blk0 = bx * kKnnThreads;
-  if (blk0 >= m_lo) return;
-
-  bool bad = false;
-  for (int i = threadIdx.x; i < L; i += kKnnThreads) {
-    const float v = x[i];
-    bad |= !isfinite(v);
-    xs[i] = v;
-  }
-  if (bad) atomicOr(a.status, 1);
-  __syncthreads();
-
-  const int lane = threadIdx.x & (kWave - 1);
-  // wave-uniform: readfirstlane lets the compiler keep it (and the self step) scalar
-  const int p0 = __builtin_amdgcn_readfirstlane(blk0 + static_cast<int>(threadIdx.x & ~(kWave - 1)));
-  const int p = p0 + lane;
-
-  float vp[EHI];
-#pragma unroll
-  for (int j = 0; j < EHI; ++j) vp[j] = (p < m_lo && p + j < L) ? xs[p + j] : 0.0f;
-
-  float qk[TOT];
-  int qi[TOT];
-  static_for<ELO, EHI>([&](auto EC) {
-    constexpr int E = decltype(EC)::value;
-    constexpr int OFF = list_off<ELO>(E);
-    // table mode: lists of E that are not needed stay idle (kth = -1)
-    const bool act = p < L - (E - 1) - Tp && (a.mom != nullptr || ((need >> (E - 1)) & 1u));
-#pragma unroll
-    for (int i = 0; i < E + 1; ++i) {
-      qk[OFF + i] = act ? __builtin_inff() : -1.0f;
-      qi[OFF + i] = -1;
-    }
-  });
-
-  if (p0 < m_lo) {
-    // Candidates whose window may run past some E's range: per-E validity.
-    auto step_masked = [&](int s) {
-      const int q = s + lane;
-      const int qc = q < 0 ? 0 : q;
-      float acc = 0.0f;
-      static_for<0, EHI - 1>([&](auto JC) {
-        constexpr int j = decltype(JC)::value;
-        const int ix = qc + j < L ? qc + j : L - 1;
-        const float d = vp[j] - xs[ix];
-        acc = acc + d * d;
-        if constexpr (j + 1 >= ELO) {
-          constexpr int E = j + 1;
-          const bool valid = q >= 0 && q < L - (E - 1) - Tp && s != p0;
-          slice_offer<list_off<ELO>(E), E + 1, TOT>(qk, qi, acc, q, valid);
-        }
-      });
-    };
-
-    int s = -(kWave - 1);
-#pragma unroll 1
-    for (; s < 0; ++s) step_masked(s);
-    const int s_full = m_hi - (kWave - 1);  // every lane's q < m_hi: valid for all E
-    if (s + kUnroll <= s_full) {
-      float win[EHI + kUnroll - 1];
-#pragma unroll
-      for (int j = 0; j < EHI - 1; ++j) win[j] = xs[s + lane + j];
-      for (; s + kUnroll <= s_full; s += kUnroll) {
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) win[EHI - 1 + u] = xs[s + lane + EHI - 1 + u];
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-          const bool notself = s + u != p0;
-          const int q = s + u + lane;
-          float acc = 0.0f;
-          float key[NG];
-          static_for<0, EHI - 1>([&](auto JC) {
-            constexpr int j = decltype(JC)::value;
-            const float d = vp[j] - win[u + j];
-            acc = acc + d * d;
-            if constexpr (j + 1 >= ELO) key[j + 1 - ELO] = acc;
-          });
-          // One wave-uniform test for the whole group: some list improves iff
-          // min over E of (key_E - kth_E) < 0 in some lane.  For finite keys
-          // the sign of the float32 difference is exact; an empty list
-          // (kth = +inf) gives -inf and an idle one (kth = -1) a positive
-          // value.  The common step improves no list at all.
-          if (notself) {
-            float dm = key[0] - qk[list_off<ELO>(ELO) + ELO];
-            static_for<ELO + 1, EHI>([&](auto EC) {
-              constexpr int E = decltype(EC)::value;
-              dm = fminf(dm, key[E - ELO] - qk[list_off<ELO>(E) + E]);
-            });
-            if (__builtin_amdgcn_ballot_w64(dm < 0.0f)) {
-              static_for<ELO, EHI>([&](auto EC) {
-                constexpr int E = decltype(EC)::value;
-                slice_offer<list_off<ELO>(E), E + 1, TOT>(qk, qi, key[E - ELO], q, true);
-              });
-            }
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < EHI - 1; ++j) win[j] = win[j + kUnroll];
-      }
-    }
-#pragma unroll 1
-    for (; s < m_lo; ++s) step_masked(s);
-  }
-
-  // Epilogue per E: float64 distances and weights of the winners, the
-  // self-prediction Tp ahead, and the block's co-moments.
-  const int wave = threadIdx.x / kWave;
-  static_for<ELO, EHI>([&](auto EC) {
-    constexpr int E = decltype(EC)::value;
-    const Mom mine = finish_list<E, list_off<ELO>(E), TOT, EHI>(a, row, p, L, Tp, need, vp, qi, xs);
-    if (a.mom) {  // uniform
-      const Mom wv = mom_wave_reduce(mine);
-      if (lane == 0) wmom[wave][E - ELO] = wv;
-    }
-  });
-  if (a.mom == nullptr) return;
-  __syncthreads();
-  if (static_cast<int>(threadIdx.x) < NG) {
-    const int E = ELO + static_cast<int>(threadIdx.x);
-    const int mE = L - (E - 1) - Tp;
-    if (mE - 1 >= E + 1 && blk0 < mE) {
-      Mom t = wmom[0][threadIdx.x];
-#pragma unroll
-      for (int w = 1; w < kKnnThreads / kWave; ++w) t = mom_merge(t, wmom[w][threadIdx.x]);
-      a.mom[(static_cast<int64_t>(row) * a.E_max + (E - 1)) * a.mom_blocks + bx] = t;
-    }
-  }
-}
-
-template <int ELO, int EHI>
-__global__ __launch_bounds__(kKnnThreads) void k_sweep_multi(KnnArgs a, int slot0) {
-  extern __shared__ float xs[];
-  group_scan<ELO, EHI>(a, slot0 + static_cast<int>(blockIdx.y), static_cast<int>(blockIdx.x), xs);
+template <int ELO, int EHI, int Q, int S>
+__global__ __launch_bounds__(kWave * Q * S) void k_sweep_multi(KnnArgs a, int slot0) {
+  extern __shared__ __attribute__((aligned(16))) float scan_smem[];
+  group_scan<ELO, EHI, Q, S>(a, slot0 + static_cast<int>(blockIdx.y), static_cast<int>(blockIdx.x), scan_smem);
 }
 
 // Persistent form: each workgroup pulls (row, block) items of one E group,
 // ordered by the host longest first, from a device counter until the list is
 // exhausted (every workgroup reaches the exit).  The item index travels
 // through LDS and is made wave-uniform.
-template <int ELO, int EHI>
-__global__ __launch_bounds__(kKnnThreads) void k_tables_persistent(KnnArgs a,
-                                                                   const TableItem *__restrict__ items,
-                                                                   int n_items, int *counter) {
-  extern __shared__ float xs[];
+template <int ELO, int EHI, int Q>
+__global__ __launch_bounds__(kWave * Q) void k_tables_persistent(KnnArgs a, const TableItem *__restrict__ items,
+                                                                 int n_items, int *counter) {
+  extern __shared__ __attribute__((aligned(16))) float scan_smem[];
   __shared__ int item_s;
   for (int trip = 0;; ++trip) {  // one call site for the body (see lookup.hip)
     int it;
@@ -207,7 +60,7 @@ __global__ __launch_bounds__(kKnnThreads) void k_tables_persistent(KnnArgs a,
     }
     const int row = __builtin_amdgcn_readfirstlane(items[it].row);
     const int blk = __builtin_amdgcn_readfirstlane(static_cast<int>(items[it].blk));
-    group_scan<ELO, EHI>(a, row, blk, xs);
+    group_scan<ELO, EHI, Q, 1>(a, row, blk / (Q / 4), scan_smem);  // (blk: a multiple of Q / 4)
   }
 }
 
@@ -215,18 +68,54 @@ __global__ __launch_bounds__(kKnnThreads) void k_tables_persistent(KnnArgs a,
 // ~54 entries (108 VGPRs).
 constexpr int kGroups[][2] = {{1, 8}, {9, 12}, {13, 15}, {16, 18}, {19, 20}};
 
-using LaunchFn = hipError_t (*)(const KnnArgs &, dim3, size_t, int, hipStream_t);
-
+// Workgroup of a plain group scan: 4 waves (one block of 256 queries); above
+// kLongSeries samples 16 waves for E 1-4 and 8 for the groups whose lists do
+// not fit 128 registers.
+constexpr int long_waves(int ehi) { return ehi <= 4 ? 16 : 8; }
+// LDS of a launch: the series, then one queue per lane (S = 1).
+template <int ELO, int EHI, int Q>
+size_t group_lds(int64_t L_max) {
+  return static_cast<size_t>(scan_floats(L_max)) * sizeof(float) + group_extra_lds<ELO, EHI, Q, 1>();
+}
 template <int ELO, int EHI>
-hipError_t launch_group(const KnnArgs &a, dim3 grid, size_t shm, int slot0, hipStream_t st) {
-  const void *fn = reinterpret_cast<const void *>(&k_sweep_multi<ELO, EHI>);
-  if (shm > 65536) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(shm));
+bool long_layout(int64_t L_max) {
+  return L_max > kLongSeries && group_lds<ELO, EHI, long_waves(EHI)>(L_max) <= static_cast<size_t>(kScanLdsMax);
+}
+
+template <class F>
+hipError_t allow_lds(F fn, size_t shm) {
+  if (shm <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             static_cast<int>(shm));
+}
+
+template <int ELO, int EHI, int Q, int S>
+hipError_t launch_group_q(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  const size_t shm = static_cast<size_t>(a.lds_x) * sizeof(float) + group_extra_lds<ELO, EHI, Q, S>();
+  hipError_t e = allow_lds(&k_sweep_multi<ELO, EHI, Q, S>, shm);
+  if (e != hipSuccess) return e;
+  const unsigned gx = static_cast<unsigned>((L_max + kWave * Q - 1) / (kWave * Q));
+  constexpr int kMaxY = 32768;
+  for (int s0 = 0; s0 < nslots; s0 += kMaxY) {
+    const int ny = nslots - s0 < kMaxY ? nslots - s0 : kMaxY;
+    hipLaunchKernelGGL((k_sweep_multi<ELO, EHI, Q, S>), dim3(gx, static_cast<unsigned>(ny)), dim3(kWave * Q * S),
+                       shm, st, a, s0);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_sweep_multi<ELO, EHI>), grid, dim3(kKnnThreads), shm, st, a, slot0);
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+using LaunchFn = hipError_t (*)(const KnnArgs &, int, int64_t, hipStream_t);
+
+template <int ELO, int EHI>
+hipError_t launch_group(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  if constexpr (EHI <= 4) {  // (larger groups' lists do not fit the registers of 16 waves)
+    if (scan_layout(nslots, L_max, EHI + 1, true) == ScanLayout::kSplit4)
+      return launch_group_q<ELO, EHI, 4, 4>(a, nslots, L_max, st);
+  }
+  return long_layout<ELO, EHI>(L_max) ? launch_group_q<ELO, EHI, long_waves(EHI), 1>(a, nslots, L_max, st)
+                                      : launch_group_q<ELO, EHI, 4, 1>(a, nslots, L_max, st);
 }
 
 // table[lo-1][hi-lo]: every (lo, hi) with lo a group start and hi inside it.
@@ -244,10 +133,11 @@ hipError_t launch_sweep_multi(const KnnArgs &a, int nslots, int64_t L_max, hipSt
   static const std::array<LaunchFn, 8> t16 = row_for<16>(std::make_index_sequence<3>{});
   static const std::array<LaunchFn, 8> t19 = row_for<19>(std::make_index_sequence<2>{});
   if (nslots <= 0) return hipSuccess;
-  const unsigned gx = static_cast<unsigned>((L_max + kKnnThreads - 1) / kKnnThreads);
-  const size_t shm = static_cast<size_t>(L_max) * sizeof(float);
+  KnnArgs b = a;
+  b.lds_x = scan_floats(L_max);
   // With the matrix-core filter, E >= kGramEMin runs in the filtered groups.
   const bool gram = a.gram_nrm != nullptr && L_max <= kGramLMax;
+  if (gram && gram_sweep_is_small(nslots, L_max)) return launch_gram_small(a, nslots, L_max, st);
   auto hi_of = [&](int lo, int top) {
     int hi = top < a.E_max ? top : a.E_max;
     if (a.mom == nullptr) {  // table mode: the group's scan must reach its largest needed E
@@ -264,14 +154,9 @@ hipError_t launch_sweep_multi(const KnnArgs &a, int nslots, int64_t L_max, hipSt
     if (hi == 0) continue;
     if (lo > hi) break;
     const std::array<LaunchFn, 8> &t = lo == 1 ? t1 : lo == 9 ? t9 : lo == 13 ? t13 : lo == 16 ? t16 : t19;
-    LaunchFn fn = t[hi - lo];
     TimedLaunch timed(EDM_KF_BATCHED_SCAN, st);
-    constexpr int kMaxY = 32768;
-    for (int s0 = 0; s0 < nslots; s0 += kMaxY) {
-      const int ny = nslots - s0 < kMaxY ? nslots - s0 : kMaxY;
-      hipError_t e = fn(a, dim3(gx, static_cast<unsigned>(ny)), shm, s0, st);
-      if (e != hipSuccess) return e;
-    }
+    hipError_t e = t[hi - lo](b, nslots, L_max, st);
+    if (e != hipSuccess) return e;
   }
   if (!gram) return hipSuccess;
   for (const auto &g : kGramGroups) {
@@ -285,33 +170,63 @@ hipError_t launch_sweep_multi(const KnnArgs &a, int nslots, int64_t L_max, hipSt
   return hipSuccess;
 }
 
+namespace {
+
+// groups 0-4: the exact E groups; 5: E 1-4 (below the filtered groups)
+constexpr int kTables = 6;
+
+using TablesFn = void (*)(KnnArgs, const TableItem *, int, int *);
+struct Tables {
+  TablesFn fn;
+  int waves;
+  size_t lds;
+};
+
+template <int ELO, int EHI>
+Tables tables_of(int64_t L_max) {
+  if (long_layout<ELO, EHI>(L_max))
+    return {&k_tables_persistent<ELO, EHI, long_waves(EHI)>, long_waves(EHI),
+            group_lds<ELO, EHI, long_waves(EHI)>(L_max)};
+  return {&k_tables_persistent<ELO, EHI, 4>, 4, group_lds<ELO, EHI, 4>(L_max)};
+}
+
+Tables tables_for(int group, int64_t L_max) {
+  switch (group) {
+    case 0: return tables_of<1, 8>(L_max);
+    case 1: return tables_of<9, 12>(L_max);
+    case 2: return tables_of<13, 15>(L_max);
+    case 3: return tables_of<16, 18>(L_max);
+    case 4: return tables_of<19, 20>(L_max);
+    default: return tables_of<1, 4>(L_max);
+  }
+}
+
+}  // namespace
+
+int tables_item_blocks(int group, int64_t L_max) {
+  return group < 0 || group >= kTables ? 1 : tables_for(group, L_max).waves / 4;
+}
+
 hipError_t launch_tables_persistent(const KnnArgs &a, int group, const TableItem *items,
                                     int n_items, int *counter, int64_t L_max, int wg_per_cu,
                                     int n_cu, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
-  using Fn = void (*)(KnnArgs, const TableItem *, int, int *);
-  // groups 0-4: the exact E groups; 5: E 1-4 (below the filtered groups)
-  static const Fn fns[6] = {&k_tables_persistent<1, 8>, &k_tables_persistent<9, 12>,
-                            &k_tables_persistent<13, 15>, &k_tables_persistent<16, 18>,
-                            &k_tables_persistent<19, 20>, &k_tables_persistent<1, 4>};
-  if (group < 0 || group > 5) return hipErrorInvalidValue;
-  const size_t shm = static_cast<size_t>(L_max) * sizeof(float);
-  const void *fn = reinterpret_cast<const void *>(fns[group]);
+  if (group < 0 || group >= kTables) return hipErrorInvalidValue;
+  KnnArgs b = a;
+  b.lds_x = scan_floats(L_max);
+  const Tables t = tables_for(group, L_max);
   TimedLaunch timed(EDM_KF_BATCHED_SCAN, st);
-  if (shm > 65536) {
-    hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       static_cast<int>(shm));
-    if (e != hipSuccess) return e;
-  }
+  hipError_t e = allow_lds(t.fn, t.lds);
+  if (e != hipSuccess) return e;
+  const dim3 threads(static_cast<unsigned>(kWave * t.waves));
   if (wg_per_cu <= 0) {  // one workgroup per item
-    hipLaunchKernelGGL(fns[group], dim3(static_cast<unsigned>(n_items)), dim3(kKnnThreads), shm, st,
-                       a, items, n_items, static_cast<int *>(nullptr));
+    hipLaunchKernelGGL(t.fn, dim3(static_cast<unsigned>(n_items)), threads, t.lds, st, b, items, n_items,
+                       static_cast<int *>(nullptr));
     return hipGetLastError();
   }
   int grid = wg_per_cu * n_cu;
   if (grid > n_items) grid = n_items;
-  hipLaunchKernelGGL(fns[group], dim3(static_cast<unsigned>(grid)), dim3(kKnnThreads), shm, st, a,
-                     items, n_items, counter);
+  hipLaunchKernelGGL(t.fn, dim3(static_cast<unsigned>(grid)), threads, t.lds, st, b, items, n_items, counter);
   return hipGetLastError();
 }
 
