@@ -952,9 +952,12 @@ int check_net(edm_ctx *ctx, const void *params, int32_t C, const void *X, int64_
   return EDM_OK;
 }
 
-int net_ws(edm_ctx *ctx, int32_t C, int64_t B, int64_t L) {
-  const size_t bytes = sizeof(float) * static_cast<size_t>(edm::net_workspace_floats(C, B, L));
+// The limit is the same for training and inference; inference needs (and
+// reserves) far less than training.
+int net_ws(edm_ctx *ctx, int32_t C, int64_t B, int64_t L, bool infer = false) {
+  size_t bytes = sizeof(float) * static_cast<size_t>(edm::net_workspace_floats(C, B, L));
   if (bytes > workspace_limit()) return set_err(ctx, EDM_E_NOMEM, "network workspace exceeds EDM_WORKSPACE_LIMIT: use smaller batches");
+  if (infer) bytes = sizeof(float) * static_cast<size_t>(edm::net_infer_workspace_floats(C, B, L));
   return ws_reserve(ctx, bytes);
 }
 }  // namespace
@@ -979,7 +982,7 @@ int edm_net_forward_bf16(edm_ctx *ctx, const float *params, int32_t C, const flo
   if (B > 0 && !logits) return set_err(ctx, EDM_E_ARG, "NULL logits");
   EDM_RC(check_ctx(ctx));
   if (B == 0) return EDM_OK;
-  EDM_RC(net_ws(ctx, C, B, L));
+  EDM_RC(net_ws(ctx, C, B, L, true));
   EDM_HIP(ctx, edm::net_forward_bf16(params, C, X, B, L, ldx, reinterpret_cast<float *>(ctx->ws), logits, ctx->stream));
   return EDM_OK;
 }

@@ -113,104 +113,231 @@ __global__ __launch_bounds__(256) void k_conv(const float *__restrict__ x, int64
   }
 }
 
-// ---- BF16 inference form of the C -> C convolutions (matrix cores) --------
-// The contraction over (tap k, input channel i) runs as a GEMM on
-// v_mfma_f32_32x32x16_bf16: A = weights [co][k*C + i] (BF16), B = the input
-// window [k*C + i][t] = x[i][t + k - HALO] (BF16), FP32 accumulation.  One
-// workgroup = one series x 256 time steps x all C output channels; the input
-// window is staged in LDS transposed to [t][i] so every lane's eight K values
-// (eight consecutive channels at one tap) are one aligned 16-byte read, and
-// the weights are staged as [co][k][i].  Wave w owns time tiles 2w, 2w+1 and
-// every output-channel tile.  Rows are padded by 8 BF16 values (16 bytes)
-// against LDS bank conflicts.
+// ---- BF16 inference form (matrix cores) ------------------------------------
+// One kernel runs the whole stack on a tile of time steps; no activation
+// leaves the compute unit.  (Three convolution kernels with float32
+// activations in HBM moved 2.4 GB for 1024 series of 1500 samples, C = 64, and
+// took 2.39 ms; this form takes 0.28 ms, 0.1 of it matrix-core time.)
+//
+// The contraction over (tap k, input channel i) runs on
+// v_mfma_f32_32x32x16_bf16: A = weights [co][k*C + i], B = the input window
+// [k*C + i][t] = x[i][t + k - HALO], both BF16, FP32 accumulation.  Activations
+// live in LDS transposed to [t][channel], so every lane's eight K values
+// (eight consecutive channels at one tap) are one aligned 16-byte read; rows
+// are padded by 16 bytes against bank conflicts.  Layer 1 (one input channel)
+// is float32 FMAs; each layer's output is rounded to BF16 as the next layer's
+// input.
+//
+// A workgroup (8 waves, two a SIMD: one's products hide the other's reads and
+// rounding) computes TO time steps of layer 3: 256 rows of layer 2 (3 more on
+// either side) from 262 of layer 1.  Every wave owns one time tile and every
+// output-channel tile.  160 KB of LDS hold one layer's weights beside the two
+// activation tiles, so the weights alternate: the next layer's are loaded into
+// registers while this layer's products run.  Layer 3's outputs are summed
+// over time in registers; k_pool_parts adds the workgroups' sums of a series
+// in order and applies the linear layer.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int TB = 256;  // time steps per workgroup of the BF16 convolution
+constexpr int TR = 256;            // rows of layers 2 and 3 per tile
+constexpr int TO = TR - 2 * HALO;  // time steps finished per tile
+constexpr int R1 = TR + 2 * HALO;  // rows of layer 1
+constexpr int IT = 512;            // threads of a workgroup
+constexpr int kInferWgs = 512;     // workgroups wanted: a series' tiles are split until then
 
 __device__ __forceinline__ uint16_t to_bf16(float f) {  // round to nearest even (finite f)
   const uint32_t u = __float_as_uint(f);
   return static_cast<uint16_t>((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
 }
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  return static_cast<uint32_t>(to_bf16(lo)) | (static_cast<uint32_t>(to_bf16(hi)) << 16);
+}
 
-// w[co][ci][k] float32 -> wb[co][k][ci] BF16.
-__global__ void k_w_to_bf16(const float *__restrict__ w, int C, uint16_t *__restrict__ wb) {
+template <int C>
+struct Infer {
+  static constexpr int XS = C + 8;       // row stride of the activations (BF16 values)
+  static constexpr int WS = KW * C + 8;  // row stride of the weights
+  static constexpr int NCO = C / 32, NCC = C / 16;
+  static constexpr int NPF = (C * WS / 8 + IT - 1) / IT;  // 16-byte words of a layer's weights per thread
+  static constexpr int NW = NPF * IT;                   // ... padded to whole rounds of the workgroup
+  static constexpr int kA2 = R1 * XS, kW = 2 * R1 * XS, kX = kW + NW * 8;  // LDS offsets (BF16 values)
+  static constexpr size_t lds = sizeof(uint16_t) * kX + sizeof(float) * (R1 + 2 * HALO);
+};
+
+// w[co][ci][k] float32 -> wb[co][k][ci] BF16 of two layers, `words` 16-byte
+// words each: rows of KW*C + 8 values, padding zero.
+__global__ void k_w_to_bf16(const float *__restrict__ w2, const float *__restrict__ w3, int C, int words,
+                            uint16_t *__restrict__ wb) {
+  const int WS = KW * C + 8;
   const int i = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= C * C * KW) return;
-  const int co = i / (KW * C), r = i - co * (KW * C);
+  if (i >= 2 * words * 8) return;
+  const float *w = i < words * 8 ? w2 : w3;
+  const int e = i < words * 8 ? i : i - words * 8;
+  const int co = e / WS, r = e - co * WS;
   const int k = r / C, ci = r - k * C;
-  wb[i] = to_bf16(w[(co * C + ci) * KW + k]);
+  wb[i] = co < C && r < KW * C ? to_bf16(w[(co * C + ci) * KW + k]) : static_cast<uint16_t>(0);
 }
 
+// Sums over time of layer 3: part[b][split][C], split = blockIdx.x of gridDim.x.
 template <int C>
-constexpr size_t conv_bf16_lds() {
-  return sizeof(uint16_t) * ((TB + KW - 1) * (C + 8) + C * (KW * C + 8));
-}
-
-// y = relu(conv(x, w) + b) for x, y [B][C][L] float32 (inputs rounded to BF16).
-template <int C>
-__global__ __launch_bounds__(256) void k_conv_bf16(const float *__restrict__ x, int L,
-                                                   const uint16_t *__restrict__ wb,
-                                                   const float *__restrict__ bias,
-                                                   float *__restrict__ y) {
+__global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, int64_t ldx, int L,
+                                                   const float *__restrict__ w1, const float *__restrict__ b1,
+                                                   const float *__restrict__ b2, const float *__restrict__ b3,
+                                                   const u32x4_t *__restrict__ wb, int tiles,
+                                                   float *__restrict__ part) {
+  using I = Infer<C>;
   static_assert(C % 32 == 0 && C <= 64, "C must be 32 or 64");
-  constexpr int XR = TB + KW - 1, XS = C + 8, WR = KW * C, WS = WR + 8;
-  constexpr int NCO = C / 32, NCC = C / 16;
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_bf16[];
-  uint16_t *xs = lds_bf16;
-  uint16_t *ws = lds_bf16 + XR * XS;
-  const int b = blockIdx.y;
-  const int t0 = blockIdx.x * TB;
-  const int tid = threadIdx.x;
-  const float *xb = x + static_cast<int64_t>(b) * C * L;
-  for (int e = tid; e < C * WR; e += 256) {
-    const int co = e / WR, r = e - co * WR;
-    ws[co * WS + r] = wb[e];
+  uint16_t *a1 = lds_bf16, *a2 = lds_bf16 + I::kA2, *ws = lds_bf16 + I::kW;
+  float *xin = reinterpret_cast<float *>(lds_bf16 + I::kX);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const float *x = X + static_cast<int64_t>(blockIdx.y) * ldx;
+
+  u32x4_t pf[I::NPF];
+  auto load_w = [&](int layer) {  // the weights of layer 2 (0) or 3 (1) into registers
+#pragma unroll
+    for (int i = 0; i < I::NPF; ++i) pf[i] = wb[layer * I::NW + tid + IT * i];
+  };
+  auto store_w = [&]() {
+#pragma unroll
+    for (int i = 0; i < I::NPF; ++i) reinterpret_cast<u32x4_t *>(ws)[tid + IT * i] = pf[i];
+  };
+  // layer 1: a thread's 8 channels c0.. at times tid / (C/8) + ...
+  constexpr int CG = C / 8;
+  const int c0 = (tid % CG) * 8;
+  float w1r[8][KW], b1r[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    b1r[c] = b1[c0 + c];
+#pragma unroll
+    for (int k = 0; k < KW; ++k) w1r[c][k] = w1[(c0 + c) * KW + k];
   }
-  for (int e = tid; e < C * XR; e += 256) {
-    const int ci = e / XR, t = e - ci * XR;
-    const int tg = t0 + t - HALO;
-    const float v = (tg >= 0 && tg < L) ? xb[static_cast<int64_t>(ci) * L + tg] : 0.0f;
-    xs[t * XS + ci] = to_bf16(v);
+  // products of 256 rows of `in` (row 32 wave + n of this lane) with the staged weights
+  const int row = 32 * wave + n;
+  f32x16_t acc[I::NCO];
+  auto conv = [&](const uint16_t *in) {
+#pragma unroll
+    for (int c = 0; c < I::NCO; ++c) acc[c] = f32x16_t{};
+#pragma unroll
+    for (int k = 0; k < KW; ++k) {
+#pragma unroll
+      for (int cc = 0; cc < I::NCC; ++cc) {
+        bf16x8_t aop[I::NCO];
+        const bf16x8_t bop = *reinterpret_cast<const bf16x8_t *>(in + (row + k) * I::XS + 16 * cc + 8 * h);
+#pragma unroll
+        for (int c = 0; c < I::NCO; ++c)
+          aop[c] = *reinterpret_cast<const bf16x8_t *>(ws + (32 * c + n) * I::WS + k * C + 16 * cc + 8 * h);
+#pragma unroll
+        for (int c = 0; c < I::NCO; ++c)
+          acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[c], bop, acc[c], 0, 0, 0);
+      }
+    }
+  };
+  float sum[I::NCO][16];  // this lane's column sums: channel 32 c + 8 (v >> 2) + 4 h + (v & 3)
+#pragma unroll
+  for (int c = 0; c < I::NCO; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[c][v] = 0.0f;
+  auto bias = [&](const float *b, int c, int v) { return b[32 * c + 8 * (v >> 2) + 4 * h + (v & 3)]; };
+
+  load_w(0);
+  // rows 256 .. 261 of layer 2 only feed discarded time steps; they stay zero
+  for (int i = tid; i < 2 * HALO * I::XS; i += IT) a2[TR * I::XS + i] = 0;
+#pragma unroll 1
+  for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int t0 = tile * TO;
+    // xin[i] = x[t0 - 3 HALO + i], zero outside the series
+    for (int i = tid; i < R1 + 2 * HALO; i += IT) {
+      const int t = t0 - 3 * HALO + i;
+      xin[i] = t >= 0 && t < L ? x[t] : 0.0f;
+    }
+    __syncthreads();  // (also: the previous tile's layer 3 is done with the weights)
+    store_w();
+    load_w(1);
+    // layer 1: row r is time t0 - 2 HALO + r
+    for (int r = tid / CG; r < R1; r += IT / CG) {
+      const int t = t0 - 2 * HALO + r;
+      float xv[KW];
+#pragma unroll
+      for (int k = 0; k < KW; ++k) xv[k] = xin[r + k];
+      uint32_t o[4] = {0u, 0u, 0u, 0u};
+      if (t >= 0 && t < L) {
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          float s = 0.0f;
+#pragma unroll
+          for (int k = 0; k < KW; ++k) s = fmaf(w1r[c][k], xv[k], s);
+          v[c] = fmaxf(s + b1r[c], 0.0f);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = pack_bf16(v[2 * q], v[2 * q + 1]);
+      }
+      *reinterpret_cast<uint4 *>(a1 + r * I::XS + c0) = uint4{o[0], o[1], o[2], o[3]};
+    }
+    __syncthreads();
+    conv(a1);  // layer 2: row r is time t0 - HALO + r
+    {
+      const int t = t0 - HALO + row;
+      const bool in = t >= 0 && t < L;
+#pragma unroll
+      for (int c = 0; c < I::NCO; ++c)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          float v[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) v[u] = in ? fmaxf(acc[c][4 * q + u] + bias(b2, c, 4 * q + u), 0.0f) : 0.0f;
+          *reinterpret_cast<uint2 *>(a2 + row * I::XS + 32 * c + 8 * q + 4 * h) =
+              uint2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        }
+    }
+    __syncthreads();  // layer 2 is complete and done with its weights
+    store_w();
+    load_w(0);
+    __syncthreads();
+    conv(a2);  // layer 3: row r is time t0 + r
+    const bool in = row < TO && t0 + row < L;
+#pragma unroll
+    for (int c = 0; c < I::NCO; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) sum[c][v] += in ? fmaxf(acc[c][v] + bias(b3, c, v), 0.0f) : 0.0f;
+  }
+  // sums over the 32 columns of a lane half, then over the waves
+  float *red = reinterpret_cast<float *>(a1);  // [wave][C]
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < I::NCO; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      float s = sum[c][v];
+#pragma unroll
+      for (int m = 1; m < 32; m <<= 1) s += __shfl_xor(s, m);
+      if (n == 0) red[wave * C + 32 * c + 8 * (v >> 2) + 4 * h + (v & 3)] = s;
+    }
+  __syncthreads();
+  if (tid < C)
+    part[(static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * C + tid] =
+        ((red[tid] + red[C + tid]) + (red[2 * C + tid] + red[3 * C + tid])) +
+        ((red[4 * C + tid] + red[5 * C + tid]) + (red[6 * C + tid] + red[7 * C + tid]));
+}
+
+// logits[b][j] = bo[j] + sum_c wo[j][c] g[c], g the mean over time from the splits' sums.
+__global__ __launch_bounds__(64) void k_pool_parts(const float *__restrict__ part, int splits, int C, int L,
+                                                   const float *__restrict__ wo, const float *__restrict__ bo,
+                                                   float *__restrict__ logits) {
+  __shared__ float gs[64];
+  const int b = blockIdx.x, c = threadIdx.x;
+  if (c < C) {
+    float s = 0.0f;
+    for (int i = 0; i < splits; ++i) s += part[(static_cast<int64_t>(b) * splits + i) * C + c];
+    gs[c] = s / static_cast<float>(L);
   }
   __syncthreads();
-  const int wave = tid >> 6, lane = tid & 63, n = lane & 31, h = lane >> 5;
-  f32x16_t acc[2][NCO];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int c = 0; c < NCO; ++c) acc[j][c] = f32x16_t{};
-#pragma unroll 1
-  for (int k = 0; k < KW; ++k) {
-#pragma unroll
-    for (int cc = 0; cc < NCC; ++cc) {
-      bf16x8_t bop[2], aop[NCO];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int tl = 64 * wave + 32 * j + n;
-        bop[j] = *reinterpret_cast<const bf16x8_t *>(xs + (tl + k) * XS + 16 * cc + 8 * h);
-      }
-#pragma unroll
-      for (int c = 0; c < NCO; ++c)
-        aop[c] = *reinterpret_cast<const bf16x8_t *>(ws + (32 * c + n) * WS + k * C + 16 * cc + 8 * h);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int c = 0; c < NCO; ++c)
-          acc[j][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aop[c], bop[j], acc[j][c], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int t = t0 + 64 * wave + 32 * j + n;
-    if (t >= L) continue;
-#pragma unroll
-    for (int c = 0; c < NCO; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int co = 32 * c + 8 * (v >> 2) + 4 * h + (v & 3);
-        y[(static_cast<int64_t>(b) * C + co) * L + t] = fmaxf(acc[j][c][v] + bias[co], 0.0f);
-      }
+  if (c < NCLS) {
+    float v = bo[c];
+    for (int i = 0; i < C; ++i) v = fmaf(wo[c * C + i], gs[i], v);
+    logits[static_cast<int64_t>(b) * NCLS + c] = v;
   }
 }
 
@@ -505,38 +632,52 @@ hipError_t net_forward(const float *theta, int C, const float *X, int64_t B, int
   return hipGetLastError();
 }
 
+namespace {
+// Tiles of a series and the workgroups that share them.
+int infer_tiles(int64_t L) { return static_cast<int>((L + TO - 1) / TO); }
+int infer_splits(int64_t B, int64_t L) {
+  const int64_t want = (kInferWgs + B - 1) / B;
+  return static_cast<int>(want < infer_tiles(L) ? want : infer_tiles(L));
+}
+
+int64_t infer_words(int C) { return C == 64 ? Infer<64>::NW : Infer<32>::NW; }
+
 template <int C>
-hipError_t conv_bf16_layer(const float *in, int64_t B, int64_t L, const uint16_t *wb,
-                           const float *bias, float *out, hipStream_t st) {
-  const void *fn = reinterpret_cast<const void *>(&k_conv_bf16<C>);
-  const size_t shm = conv_bf16_lds<C>();
-  hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
-  if (e != hipSuccess) return e;
-  const dim3 grid(static_cast<unsigned>((L + TB - 1) / TB), static_cast<unsigned>(B));
-  hipLaunchKernelGGL(k_conv_bf16<C>, grid, dim3(256), shm, st, in, static_cast<int>(L), wb, bias, out);
+hipError_t launch_infer(const NetParams &P, const float *X, int64_t B, int64_t L, int64_t ldx, const uint16_t *wb,
+                        float *part, hipStream_t st) {
+  constexpr size_t shm = Infer<C>::lds;
+  if (shm > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_net_infer<C>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid(static_cast<unsigned>(infer_splits(B, L)), static_cast<unsigned>(B));
+  hipLaunchKernelGGL(k_net_infer<C>, grid, dim3(IT), shm, st, X, ldx, static_cast<int>(L), P.w1, P.b1, P.b2, P.b3,
+                     reinterpret_cast<const u32x4_t *>(wb), infer_tiles(L), part);
   return hipGetLastError();
+}
+}  // namespace
+
+int64_t net_infer_workspace_floats(int C, int64_t B, int64_t L) {
+  // BF16 weights of two layers, sums per split
+  return 2 * 4 * infer_words(C) + B * infer_splits(B, L) * C;
 }
 
 hipError_t net_forward_bf16(const float *theta, int C, const float *X, int64_t B, int64_t L,
                             int64_t ldx, float *ws, float *logits, hipStream_t st) {
   if (C != 32 && C != 64) return hipErrorInvalidValue;
   const NetParams P = net_params(theta, C);
-  float *a1 = ws, *a2 = a1 + B * C * L, *a3 = a2 + B * C * L;
-  float *g = a3 + B * C * L;
-  uint16_t *wb2 = reinterpret_cast<uint16_t *>(g + B * C);
-  uint16_t *wb3 = wb2 + C * C * KW;
-  const unsigned nw = static_cast<unsigned>((C * C * KW + 255) / 256);
-  hipLaunchKernelGGL(k_w_to_bf16, dim3(nw), dim3(256), 0, st, P.w2, C, wb2);
-  hipLaunchKernelGGL(k_w_to_bf16, dim3(nw), dim3(256), 0, st, P.w3, C, wb3);
-  const dim3 grid(static_cast<unsigned>((L + TT - 1) / TT), static_cast<unsigned>(B));
-  hipLaunchKernelGGL(k_conv<0>, grid, dim3(256), 0, st, X, ldx, 0, 1, C, static_cast<int>(L), P.w1, P.b1, nullptr, a1);
+  uint16_t *wb = reinterpret_cast<uint16_t *>(ws);  // the workspace is 256-byte aligned
+  const int words = static_cast<int>(infer_words(C));
+  float *part = ws + 2 * 4 * words;
+  hipLaunchKernelGGL(k_w_to_bf16, dim3(static_cast<unsigned>(2 * words * 8 / 256)), dim3(256), 0, st, P.w2, P.w3, C,
+                     words, wb);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  e = C == 64 ? conv_bf16_layer<64>(a1, B, L, wb2, P.b2, a2, st) : conv_bf16_layer<32>(a1, B, L, wb2, P.b2, a2, st);
+  e = C == 64 ? launch_infer<64>(P, X, B, L, ldx, wb, part, st) : launch_infer<32>(P, X, B, L, ldx, wb, part, st);
   if (e != hipSuccess) return e;
-  e = C == 64 ? conv_bf16_layer<64>(a2, B, L, wb3, P.b3, a3, st) : conv_bf16_layer<32>(a2, B, L, wb3, P.b3, a3, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pool_linear, dim3(static_cast<unsigned>(B)), dim3(256), 0, st, a3, C, static_cast<int>(L), P.wo, P.bo, g, logits);
+  hipLaunchKernelGGL(k_pool_parts, dim3(static_cast<unsigned>(B)), dim3(64), 0, st, part, infer_splits(B, L), C,
+                     static_cast<int>(L), P.wo, P.bo, logits);
   return hipGetLastError();
 }
 
