@@ -955,10 +955,10 @@ int check_net(edm_ctx *ctx, const void *params, int32_t C, const void *X, int64_
 // The limit is the same for training and inference; inference needs (and
 // reserves) far less than training.
 int net_ws(edm_ctx *ctx, int32_t C, int64_t B, int64_t L, bool infer = false) {
-  size_t bytes = sizeof(float) * static_cast<size_t>(edm::net_workspace_floats(C, B, L));
-  if (bytes > workspace_limit()) return set_err(ctx, EDM_E_NOMEM, "network workspace exceeds EDM_WORKSPACE_LIMIT: use smaller batches");
-  if (infer) bytes = sizeof(float) * static_cast<size_t>(edm::net_infer_workspace_floats(C, B, L));
-  return ws_reserve(ctx, bytes);
+  if (sizeof(float) * static_cast<size_t>(edm::net_limit_floats(C, B, L)) > workspace_limit())
+    return set_err(ctx, EDM_E_NOMEM, "network workspace exceeds EDM_WORKSPACE_LIMIT: use smaller batches");
+  const int64_t floats = infer ? edm::net_infer_workspace_floats(C, B, L) : edm::net_workspace_floats(C, B, L);
+  return ws_reserve(ctx, sizeof(float) * static_cast<size_t>(floats));
 }
 }  // namespace
 

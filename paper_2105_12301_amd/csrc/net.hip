@@ -7,15 +7,13 @@
 //        -> ReLU -> mean over time -> linear(C->20) -> logits over E = 1..20
 // with zero "same" padding.  Activations are [B][C][L] row-major.
 //
-// Convolutions are tiled for one workgroup = one series x 128 time steps x all
-// output channels: the input window (channel chunk x (128 + KW - 1)) and the
-// weight chunk are staged in LDS, and each thread accumulates a 4-channel x
-// 8-step register tile (224 FMAs per 42 LDS reads).  The backward pass over
-// the data is the same contraction with the weights transposed and flipped in
-// the staging step and the ReLU mask of the previous layer applied on output.
-// Weight gradients reduce over (series, time) in slices with a second pass
-// over the slices, so no float atomics are involved and results are
-// deterministic.
+// Training (float32): activations and their gradients are [B][L][C] in the
+// workspace, channels fastest.  The C -> C convolutions, their data gradients
+// (the same contraction with the weights transposed and flipped) and their
+// weight gradients run on v_mfma_f32_32x32x2_f32: float32 operands, float32
+// accumulation.  Weight gradients reduce over (series, time) in slices with a
+// second pass over the slices, so no float atomics are involved and results
+// are deterministic.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -28,88 +26,196 @@ namespace {
 
 constexpr int KW = EDM_NET_KW;
 constexpr int HALO = KW / 2;
-constexpr int TT = 128;   // time steps per workgroup
-constexpr int CCH = 16;   // input channels staged per chunk
 constexpr int NCLS = EDM_NET_CLASSES;
 
-// MODE 0: y = relu(conv(x, w) + b)                  (forward)
-// MODE 1: y = conv(x, w^T flipped) * (aprev > 0)    (backward over the data)
-// MODE 2: y = conv(x, w) + b                        (forward without ReLU; tests)
-template <int MODE>
-__global__ __launch_bounds__(256) void k_conv(const float *__restrict__ x, int64_t ldx_b,
-                                              int64_t ldx_c, int Ci, int Co, int L,
-                                              const float *__restrict__ w,
-                                              const float *__restrict__ bias,
-                                              const float *__restrict__ aprev,
-                                              float *__restrict__ y) {
-  __shared__ float xs[CCH][TT + KW - 1];
-  __shared__ float ws[64][CCH][KW];
-  const int b = blockIdx.y;
-  const int t0 = blockIdx.x * TT;
-  const int tid = threadIdx.x;
-  const int ty = tid >> 4;  // 16 groups of 4 output channels
-  const int tx = tid & 15;  // 16 groups of 8 time steps
-  float acc[4][8];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = 0.0f;
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-  const float *xb = x + static_cast<int64_t>(b) * ldx_b;
-  for (int c0 = 0; c0 < Ci; c0 += CCH) {
-    const int cn = Ci - c0 < CCH ? Ci - c0 : CCH;
-    __syncthreads();
-    for (int e = tid; e < CCH * (TT + KW - 1); e += 256) {
-      const int c = e / (TT + KW - 1), t = e - c * (TT + KW - 1);
-      const int tg = t0 + t - HALO;
-      float v = 0.0f;
-      if (c < cn && tg >= 0 && tg < L) v = xb[static_cast<int64_t>(c0 + c) * ldx_c + tg];
-      xs[c][t] = v;
-    }
-    for (int e = tid; e < 64 * CCH * KW; e += 256) {
-      const int o = e / (CCH * KW), r = e - o * (CCH * KW);
-      const int c = r / KW, k = r - c * KW;
-      float v = 0.0f;
-      if (o < Co && c < cn) {
-        if (MODE == 1)  // w_eff[o][i][k] = w[i][o][KW-1-k], w is [Ci_fwd = Co][Co_fwd = Ci][KW]
-          v = w[(static_cast<int64_t>(c0 + c) * Co + o) * KW + (KW - 1 - k)];
-        else
-          v = w[(static_cast<int64_t>(o) * Ci + (c0 + c)) * KW + k];
+constexpr int kMaxC = EDM_NET_C_MAX;
+__host__ __device__ constexpr int pad32(int C) { return (C + 31) / 32 * 32; }
+
+// Layer 1: y[b][t][c] = relu(sum_k w[c][k] x[b][t + k - HALO] + bias[c]).
+// Bound by its output's HBM writes; a thread holds its channel's weights.
+constexpr int T1 = 128;  // time steps per workgroup
+__global__ __launch_bounds__(256) void k_conv1(const float *__restrict__ x, int64_t ldx, int C, int L,
+                                               const float *__restrict__ w, const float *__restrict__ bias,
+                                               float *__restrict__ y) {
+  __shared__ float xs[T1 + KW - 1];
+  const int b = blockIdx.y, t0 = blockIdx.x * T1, tid = threadIdx.x;
+  for (int i = tid; i < T1 + KW - 1; i += 256) {
+    const int t = t0 + i - HALO;
+    xs[i] = t >= 0 && t < L ? x[static_cast<int64_t>(b) * ldx + t] : 0.0f;
+  }
+  __syncthreads();
+  const int c = tid & 63;
+  if (c >= C) return;
+  float wr[KW];
+#pragma unroll
+  for (int k = 0; k < KW; ++k) wr[k] = w[c * KW + k];
+  const float bc = bias[c];
+  float *out = y + (static_cast<int64_t>(b) * L + t0) * C + c;
+  const int n = L - t0 < T1 ? L - t0 : T1;
+#pragma unroll 4
+  for (int t = tid >> 6; t < n; t += 4) {
+    float s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) s = fmaf(wr[k], xs[t + k], s);
+    out[static_cast<int64_t>(t) * C] = fmaxf(s + bc, 0.0f);
+  }
+}
+
+// The contraction of a C -> C layer runs over e = 7 ci + k in ascending order
+// (channels, then taps), two at a time: v_mfma_f32_32x32x2_f32 adds its two
+// products one after the other with a rounding each, as two fused
+// multiply-adds, so every output is the same chain of fused multiply-adds that a
+// vector kernel walking the channels and taps in order computes.
+//
+// Weights in fragment order: element q of wf[u][cot][lane] (float4) holds
+// A[co = 32 cot + lane % 32][e = 2 (4 u + q) + lane / 32], A[co][7 ci + k] =
+// w[co][ci][k], or with `flip` w[ci][co][KW - 1 - k]; zero outside C.
+__global__ void k_weight_frags(const float *__restrict__ w, int C, int flip, float *__restrict__ wf) {
+  const int CP = pad32(C), n_cot = CP / 32;
+  const int i = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= KW * CP * CP) return;
+  const int q = i & 3, lane = (i >> 2) & 63, cot = (i >> 8) % n_cot, u = (i >> 8) / n_cot;
+  const int e = 2 * (4 * u + q) + (lane >> 5);
+  const int co = 32 * cot + (lane & 31), ci = e / KW, k = e % KW;
+  float v = 0.0f;
+  if (co < C && ci < C) v = flip ? w[(ci * C + co) * KW + (KW - 1 - k)] : w[(co * C + ci) * KW + k];
+  wf[i] = v;
+}
+
+// C -> C convolution over time, x, y [B][L][C]:
+//   kBack = false: y = relu(conv(x) + bias)
+//   kBack = true:  y = conv(x) where aprev > 0, else 0
+// kMask: the input is x > 0 ? chan[b][c] : 0 (the pooled layer's gradient,
+// which is one value per channel on the layer's support; never stored).
+//
+// A workgroup (4 waves) computes CR time steps; the input window sits in LDS
+// [t][channel] (odd row stride: a wave's 32 rows fall on distinct banks), every
+// wave owns two time tiles and all output-channel tiles.  Per step one LDS
+// word per time tile and a quarter of a 16-byte load per channel tile (weights
+// from L2, one block of 8 channels ahead) feed 2 x 2 products of 64 cycles, so
+// the matrix cores bound it: 22 GFLOP at C = 64, 256 x 1500, whose vector form
+// took 0.45-0.49 ms.
+constexpr int CR = 256;
+template <int NCO, bool kBack, bool kMask>
+__global__ __launch_bounds__(256, 2) void k_conv_f32(const float *__restrict__ x, const float *__restrict__ chan, int C,
+                                                  int L, const f32x4_t *__restrict__ wf,
+                                                  const float *__restrict__ bias, const float *__restrict__ aprev,
+                                                  float *__restrict__ y) {
+  constexpr int CP = 32 * NCO, XS = CP + 1;
+  extern __shared__ __attribute__((aligned(16))) float conv_lds[];
+  const int b = blockIdx.y, t0 = blockIdx.x * CR, tid = threadIdx.x;
+  const float *xb = x + static_cast<int64_t>(b) * L * C;
+  // Staging: a thread's channel is fixed; eight clamped loads are in flight at
+  // once, and what lies outside the series or the channels becomes zero after.
+  {
+    constexpr int RP = 256 / CP;  // rows per round of the workgroup
+    constexpr int kRows = CR + KW - 1, kBatch = 8;
+    const int c = tid % CP;
+    const bool has = c < C;
+    const float *xc = xb + (has ? c : 0);
+    const float ch = kMask && has ? chan[b * C + c] : 0.0f;
+#pragma unroll 1
+    for (int r0 = tid / CP; r0 < kRows; r0 += RP * kBatch) {
+      float v[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int t = t0 + r0 + RP * i - HALO;
+        v[i] = xc[static_cast<int64_t>(t < 0 ? 0 : (t < L ? t : L - 1)) * C];
       }
-      ws[o][c][k] = v;
-    }
-    __syncthreads();
-    for (int c = 0; c < cn; ++c) {
-      float xv[8 + KW - 1];
 #pragma unroll
-      for (int j = 0; j < 8 + KW - 1; ++j) xv[j] = xs[c][tx * 8 + j];
-#pragma unroll
-      for (int k = 0; k < KW; ++k) {
-        float wv[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) wv[i] = ws[ty * 4 + i][c][k];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(wv[i], xv[j + k], acc[i][j]);
+      for (int i = 0; i < kBatch; ++i) {
+        const int r = r0 + RP * i, t = t0 + r - HALO;
+        float w = v[i];
+        if constexpr (kMask) w = w > 0.0f ? ch : 0.0f;
+        if (r < kRows) conv_lds[r * XS + c] = has && t >= 0 && t < L ? w : 0.0f;
       }
     }
   }
+  __syncthreads();
+  const int wave = tid >> 6, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  if (t0 + 64 * wave >= L) return;
+  f32x16_t acc[2][NCO];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int o = ty * 4 + i;
-    if (o >= Co) continue;
-    const float bo = (MODE != 1 && bias) ? bias[o] : 0.0f;
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int t = t0 + tx * 8 + j;
-      if (t >= L) continue;
-      const int64_t at = (static_cast<int64_t>(b) * Co + o) * L + t;
-      float v = acc[i][j] + bo;
-      if (MODE == 0) v = fmaxf(v, 0.0f);
-      if (MODE == 1) v = aprev[at] > 0.0f ? v : 0.0f;
-      y[at] = v;
+    for (int c = 0; c < NCO; ++c) acc[j][c] = f32x16_t{};
+  const f32x4_t *wl = wf + lane;
+  constexpr int kQ = KW;  // float4 rounds of a block of 8 channels: 56 products' pairs / 2 / 4
+  // lane's LDS word of step s of a block: e = 2 s + h, row n + k, channel e / 7
+  const float *xr[KW];
+#pragma unroll
+  for (int s = 0; s < KW; ++s) {
+    const int e = 2 * s + h;
+    xr[s] = conv_lds + (64 * wave + n + e % KW) * XS + e / KW;
+  }
+  f32x4_t av[kQ][NCO];
+#pragma unroll
+  for (int u = 0; u < kQ; ++u)
+#pragma unroll
+    for (int c = 0; c < NCO; ++c) av[u][c] = wl[(u * NCO + c) * 64];
+#pragma unroll 1
+  for (int blk = 0; blk < CP / 8; ++blk) {
+    const int nb = blk + 1 < CP / 8 ? blk + 1 : blk;
+    f32x4_t an[kQ][NCO];
+#pragma unroll
+    for (int u = 0; u < kQ; ++u)
+#pragma unroll
+      for (int c = 0; c < NCO; ++c) an[u][c] = wl[((nb * kQ + u) * NCO + c) * 64];
+#pragma unroll
+    for (int s = 0; s < 4 * kQ; ++s) {
+      float bv[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) bv[j] = xr[s % KW][32 * j * XS + 2 * (s / KW)];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+          acc[j][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s / 4][c][s % 4], bv[j], acc[j][c], 0, 0, 0);
     }
+#pragma unroll
+    for (int s = 0; s < KW; ++s) xr[s] += 8;
+#pragma unroll
+    for (int u = 0; u < kQ; ++u)
+#pragma unroll
+      for (int c = 0; c < NCO; ++c) av[u][c] = an[u][c];
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int t = t0 + 64 * wave + 32 * j + n;
+    if (t >= L) continue;
+    const int64_t at = (static_cast<int64_t>(b) * L + t) * C;
+#pragma unroll
+    for (int c = 0; c < NCO; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int co = 32 * c + 8 * q + 4 * h;
+        if (co >= C) continue;
+        // four channels at a time where they are one aligned word of 16 bytes
+        if ((C & 3) == 0) {
+          f32x4_t v;
+          f32x4_t m = {1.0f, 1.0f, 1.0f, 1.0f};
+          if constexpr (kBack) m = *reinterpret_cast<const f32x4_t *>(aprev + at + co);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            v[u] = acc[j][c][4 * q + u];
+            if constexpr (kBack) v[u] = m[u] > 0.0f ? v[u] : 0.0f;
+            else v[u] = fmaxf(v[u] + bias[co + u], 0.0f);
+          }
+          *reinterpret_cast<f32x4_t *>(y + at + co) = v;
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (co + u >= C) continue;
+            float v = acc[j][c][4 * q + u];
+            if constexpr (kBack) v = aprev[at + co + u] > 0.0f ? v : 0.0f;
+            else v = fmaxf(v + bias[co + u], 0.0f);
+            y[at + co + u] = v;
+          }
+        }
+      }
   }
 }
 
@@ -137,7 +243,6 @@ __global__ __launch_bounds__(256) void k_conv(const float *__restrict__ x, int64
 // over time in registers; k_pool_parts adds the workgroups' sums of a series
 // in order and applies the linear layer.
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int TR = 256;            // rows of layers 2 and 3 per tile
@@ -341,174 +446,228 @@ __global__ __launch_bounds__(64) void k_pool_parts(const float *__restrict__ par
   }
 }
 
-// Partial weight gradients of one slice of (series, time):
-// part[s][o][i][k] = sum over the slice of dz[b][o][t] * x[b][i][t + k - HALO],
-// part_b[s][o] = sum over the slice of dz[b][o][t] (from the i-chunk-0 blocks).
-// Block = 8 input channels x all (<= 64) output channels; 256 threads =
-// 16 output groups (4 channels) x 4 input pairs x 4 time quarters.
-constexpr int WT = 64;  // time steps staged per tile
-__global__ __launch_bounds__(256) void k_conv_wgrad(const float *__restrict__ x, int64_t ldx_b,
-                                                    int64_t ldx_c, int Ci, int Co, int L, int B,
-                                                    const float *__restrict__ dz,
-                                                    int64_t tiles_per_slice,
-                                                    float *__restrict__ part,
-                                                    float *__restrict__ part_b) {
-  __shared__ float ds[64][WT];
-  __shared__ float xs2[8][WT + KW - 1];
-  __shared__ float red[64 * 4 * 2 * KW];  // one quarter's accumulators
-  const int ic0 = blockIdx.x * 8;
-  const int slice = blockIdx.y;
-  const int tid = threadIdx.x;
-  const int og = tid & 15, ip = (tid >> 4) & 3, tq = tid >> 6;
-  float acc[4][2][KW];
-  float accb[4];
+// Partial weight gradients of one slice of (series, time) of a C -> C layer:
+// part[slice][k][co][ci] = sum of dz[b][t][co] x[b][t + k - HALO][ci] and
+// part_b[slice][co] = sum of dz[b][t][co] (rows padded to 32 channels).
+// kMask: dz is given as z > 0 ? chan[b][c] : 0.
+//
+// One wave per pair of channel tiles: lane (n, h) feeds channel n of both
+// operands at the time steps of parity h, straight from memory (32 channels
+// are one 128-byte line), and one sliding window of x serves all seven taps:
+// 12 loads per 28 products of 64 cycles, so the matrix cores bound it.  (The
+// VALU form took 1.2 ms per layer at C = 64, 256 x 1500, and as long for the
+// first layer's 7 x 64 weights.)
+constexpr int WT = 128;         // time steps of a slice's unit
+constexpr int kSlices64 = 512;  // slices at C > 32 (four waves each), at most
+template <int NCO, bool kMask>
+__global__ __launch_bounds__(64 * NCO * NCO) void k_wgrad(const float *__restrict__ x, const float *__restrict__ dz,
+                                                          const float *__restrict__ chan, int C, int L,
+                                                          int64_t units, int64_t units_per_slice,
+                                                          float *__restrict__ part, float *__restrict__ part_b) {
+  constexpr int CP = 32 * NCO;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const int cot = wave % NCO, cit = wave / NCO;
+  const int co = 32 * cot + n, ci = 32 * cit + n;
+  const bool has_co = co < C, has_ci = ci < C;
+  f32x16_t acc[KW];
 #pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    accb[a] = 0.0f;
+  for (int k = 0; k < KW; ++k) acc[k] = f32x16_t{};
+  float bsum = 0.0f;
+  const int per_series = (L + WT - 1) / WT;
+  const int64_t u0 = static_cast<int64_t>(blockIdx.x) * units_per_slice;
+  const int64_t u1 = u0 + units_per_slice < units ? u0 + units_per_slice : units;
+  for (int64_t u = u0; u < u1; ++u) {
+    const int b = static_cast<int>(u / per_series);
+    const int t0 = static_cast<int>(u - static_cast<int64_t>(b) * per_series) * WT;
+    const float *xb = x + static_cast<int64_t>(b) * L * C + (has_ci ? ci : 0);
+    const float *zb = dz + static_cast<int64_t>(b) * L * C + (has_co ? co : 0);
+    float cz = 0.0f;
+    if constexpr (kMask) cz = has_co ? chan[b * C + co] : 0.0f;
+    // Loads are unconditional (clamped) and two groups ahead; what lies outside
+    // the series or the channels is replaced when a group becomes current.
+    auto raw_x = [&](int t) { return xb[static_cast<int64_t>(t < 0 ? 0 : (t < L ? t : L - 1)) * C]; };
+    auto raw_z = [&](int t) { return zb[static_cast<int64_t>(t < L ? t : L - 1) * C]; };
+    auto use_x = [&](float v, int t) { return has_ci && t >= 0 && t < L ? v : 0.0f; };
+    auto use_z = [&](float v, int t) {
+      if constexpr (kMask) v = v > 0.0f ? cz : 0.0f;
+      return has_co && t < L ? v : 0.0f;
+    };
+    // groups of 4 steps (8 time steps); step i of the group at T covers time
+    // T + 2 i + h and needs x at that time - 3 .. + 3
+    const int th = t0 + h;
+    float xw[13], zw[4], x1[8], z1[4];  // this group's, and the next one's (raw)
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int i = 0; i < 13; ++i) xw[i] = raw_x(th - HALO + i);
 #pragma unroll
-      for (int k = 0; k < KW; ++k) acc[a][c][k] = 0.0f;
-  }
-  const int tiles_per_series = (L + WT - 1) / WT;
-  const int64_t total_tiles = static_cast<int64_t>(B) * tiles_per_series;
-  const int64_t tile_begin = static_cast<int64_t>(slice) * tiles_per_slice;
-  int64_t tile_end = tile_begin + tiles_per_slice;
-  if (tile_end > total_tiles) tile_end = total_tiles;
-  for (int64_t tile = tile_begin; tile < tile_end; ++tile) {
-    const int b = static_cast<int>(tile / tiles_per_series);
-    const int t0 = static_cast<int>(tile - static_cast<int64_t>(b) * tiles_per_series) * WT;
-    __syncthreads();
-    for (int e = tid; e < 64 * WT; e += 256) {
-      const int o = e / WT, t = e - o * WT;
-      float v = 0.0f;
-      if (o < Co && t0 + t < L) v = dz[(static_cast<int64_t>(b) * Co + o) * L + t0 + t];
-      ds[o][t] = v;
-    }
-    for (int e = tid; e < 8 * (WT + KW - 1); e += 256) {
-      const int c = e / (WT + KW - 1), t = e - c * (WT + KW - 1);
-      const int tg = t0 + t - HALO;
-      float v = 0.0f;
-      if (ic0 + c < Ci && tg >= 0 && tg < L)
-        v = x[static_cast<int64_t>(b) * ldx_b + static_cast<int64_t>(ic0 + c) * ldx_c + tg];
-      xs2[c][t] = v;
-    }
-    __syncthreads();
-    const int tb = tq * (WT / 4);
-    float win[2][KW];
+    for (int i = 0; i < 4; ++i) zw[i] = raw_z(th + 2 * i);
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int i = 0; i < 8; ++i) x1[i] = raw_x(th + 8 - HALO + 5 + i);
 #pragma unroll
-      for (int k = 0; k < KW - 1; ++k) win[c][k] = xs2[ip * 2 + c][tb + k];
-    for (int tt = 0; tt < WT / 4; ++tt) {
-      const int t = tb + tt;
+    for (int i = 0; i < 4; ++i) z1[i] = raw_z(th + 8 + 2 * i);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) win[c][KW - 1] = xs2[ip * 2 + c][t + KW - 1];
-      float dv[4];
+    for (int i = 0; i < 13; ++i) xw[i] = use_x(xw[i], th - HALO + i);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) dv[a] = ds[og * 4 + a][t];
+    for (int i = 0; i < 4; ++i) zw[i] = use_z(zw[i], th + 2 * i);
+    const int te = L - t0 < WT ? L - t0 : WT;
+#pragma unroll 1
+    for (int T = 0; T < te; T += 8) {
+      float x2[8], z2[4];  // two groups ahead (raw)
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        accb[a] += dv[a];
+      for (int i = 0; i < 8; ++i) x2[i] = raw_x(th + T + 16 - HALO + 5 + i);
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+      for (int i = 0; i < 4; ++i) z2[i] = raw_z(th + T + 16 + 2 * i);
 #pragma unroll
-          for (int k = 0; k < KW; ++k) acc[a][c][k] = fmaf(dv[a], win[c][k], acc[a][c][k]);
+      for (int i = 0; i < 4; ++i) {
+        bsum += zw[i];
+#pragma unroll
+        for (int k = 0; k < KW; ++k)
+          acc[k] = __builtin_amdgcn_mfma_f32_32x32x2f32(zw[i], xw[2 * i + k], acc[k], 0, 0, 0);
       }
 #pragma unroll
-      for (int c = 0; c < 2; ++c)
+      for (int i = 0; i < 5; ++i) xw[i] = xw[i + 8];
 #pragma unroll
-        for (int k = 0; k < KW - 1; ++k) win[c][k] = win[c][k + 1];
+      for (int i = 0; i < 8; ++i) {
+        xw[5 + i] = use_x(x1[i], th + T + 8 - HALO + 5 + i);
+        x1[i] = x2[i];
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        zw[i] = use_z(z1[i], th + T + 8 + 2 * i);
+        z1[i] = z2[i];
+      }
     }
   }
-  // reduce the 4 time quarters through LDS (one quarter per round), then
-  // write this slice's partials
-  constexpr int per = 4 * 2 * KW;  // accumulators per thread
-  const int lt = tid & 63;         // thread index within its quarter
-  for (int q = 1; q < 4; ++q) {
+  float *out = part + static_cast<int64_t>(blockIdx.x) * KW * CP * CP;
+#pragma unroll
+  for (int k = 0; k < KW; ++k)
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      out[(k * CP + 32 * cot + 8 * (v >> 2) + 4 * h + (v & 3)) * CP + ci] = acc[k][v];
+  bsum += __shfl_xor(bsum, 32);
+  if (cit == 0 && h == 0) part_b[static_cast<int64_t>(blockIdx.x) * CP + co] = bsum;
+}
+
+// Layer 1's partial gradients: part[slice][c][k < KW] weights, [c][KW] the
+// bias.  Bound by reading dz once; a thread holds one channel of one residue
+// of time modulo 4.
+constexpr int kSlices1 = 2048;
+__global__ __launch_bounds__(256) void k_wgrad1(const float *__restrict__ x, int64_t ldx, const float *__restrict__ dz,
+                                                int C, int L, int64_t units, int64_t units_per_slice,
+                                                float *__restrict__ part) {
+  __shared__ float xs[WT + KW - 1];
+  __shared__ float red[4][kMaxC][KW + 1];
+  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
+  float acc[KW + 1];
+#pragma unroll
+  for (int k = 0; k <= KW; ++k) acc[k] = 0.0f;
+  const int per_series = (L + WT - 1) / WT;
+  const int64_t u0 = static_cast<int64_t>(blockIdx.x) * units_per_slice;
+  const int64_t u1 = u0 + units_per_slice < units ? u0 + units_per_slice : units;
+  for (int64_t u = u0; u < u1; ++u) {
+    const int b = static_cast<int>(u / per_series);
+    const int t0 = static_cast<int>(u - static_cast<int64_t>(b) * per_series) * WT;
     __syncthreads();
-    if (tq == q) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int k = 0; k < KW; ++k) red[lt * per + (a * 2 + c) * KW + k] = acc[a][c][k];
+    static_assert(WT + KW - 1 <= 256, "one thread per staged sample");
+    if (threadIdx.x < WT + KW - 1) {
+      const int t = t0 + static_cast<int>(threadIdx.x) - HALO;
+      xs[threadIdx.x] = t >= 0 && t < L ? x[static_cast<int64_t>(b) * ldx + t] : 0.0f;
     }
     __syncthreads();
-    if (tq == 0) {
+    const int te = L - t0 < WT ? L - t0 : WT;
+    const float *z = dz + (static_cast<int64_t>(b) * L + t0) * C + (c < C ? c : 0);
+#pragma unroll 8
+    for (int t = q; t < te; t += 4) {
+      const float v = z[static_cast<int64_t>(t) * C];
 #pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int k = 0; k < KW; ++k) acc[a][c][k] += red[lt * per + (a * 2 + c) * KW + k];
+      for (int k = 0; k < KW; ++k) acc[k] = fmaf(v, xs[t + k], acc[k]);
+      acc[KW] += v;
     }
   }
-  if (tq == 0) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int k = 0; k < KW; ++k) {
-          const int o = og * 4 + a, i = ic0 + ip * 2 + c;
-          if (o < Co && i < Ci)
-            part[((static_cast<int64_t>(slice) * Co + o) * Ci + i) * KW + k] = acc[a][c][k];
-        }
-  }
-  // bias partials (first input chunk only): sum over the time quarters of
-  // the ip == 0 threads, which hold output channel o at og = o / 4, a = o % 4
+  for (int k = 0; k <= KW; ++k) red[q][c][k] = acc[k];
   __syncthreads();
-  if (blockIdx.x == 0) {
-#pragma unroll
-    for (int a = 0; a < 4; ++a) red[tid * 4 + a] = ip == 0 ? accb[a] : 0.0f;
-    __syncthreads();
-    if (tid < 64) {
-      const int o = tid;
-      float v = 0.0f;
-      for (int q = 0; q < 4; ++q) v += red[(q * 64 + (o >> 2)) * 4 + (o & 3)];
-      if (o < Co) part_b[static_cast<int64_t>(slice) * Co + o] = v;
-    }
+  for (int i = threadIdx.x; i < C * (KW + 1); i += 256) {
+    const int cc = i / (KW + 1), k = i % (KW + 1);
+    part[static_cast<int64_t>(blockIdx.x) * C * (KW + 1) + i] =
+        (red[0][cc][k] + red[1][cc][k]) + (red[2][cc][k] + red[3][cc][k]);
   }
 }
 
-__global__ void k_sum_slices(const float *__restrict__ part, int64_t n, int slices,
-                             float *__restrict__ out) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+// Sum of the slices' value i of n, by the workgroup's 4 waves (64 values each
+// workgroup, slices modulo 4 per wave); valid in wave 0.
+__device__ __forceinline__ float sum_slices(const float *__restrict__ part, int64_t n, int slices, int64_t i) {
+  __shared__ float red[4][64];
+  const int q = threadIdx.x >> 6, l = threadIdx.x & 63;
   float v = 0.0f;
-  for (int s = 0; s < slices; ++s) v += part[static_cast<int64_t>(s) * n + i];
-  out[i] = v;
+  if (i < n) {
+#pragma unroll 8
+    for (int s = q; s < slices; s += 4) v += part[static_cast<int64_t>(s) * n + i];
+  }
+  red[q][l] = v;
+  __syncthreads();
+  v = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
+  __syncthreads();
+  return v;
 }
 
-// g[b][c] = mean_t a[b][c][t]; logits[b][j] = bo[j] + sum_c wo[j][c] g[b][c].
-// One workgroup per series.
-__global__ __launch_bounds__(256) void k_pool_linear(const float *__restrict__ a, int C, int L,
-                                                     const float *__restrict__ wo,
-                                                     const float *__restrict__ bo,
-                                                     float *__restrict__ g,
-                                                     float *__restrict__ logits) {
-  __shared__ float gs[64];
-  const int b = blockIdx.x;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int c = wave; c < C; c += 4) {
-    const float *row = a + (static_cast<int64_t>(b) * C + c) * L;
-    float s = 0.0f;
-    for (int t = lane; t < L; t += 64) s += row[t];
+// dw[co][ci][k] and db[co] of a C -> C layer from k_wgrad's slices.
+__global__ __launch_bounds__(256) void k_sum_wgrad(const float *__restrict__ part, const float *__restrict__ part_b,
+                                                   int C, int slices, float *__restrict__ dw,
+                                                   float *__restrict__ db) {
+  const int CP = pad32(C);
+  const int64_t n = static_cast<int64_t>(KW) * CP * CP;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const bool tail = static_cast<int64_t>(blockIdx.x) * 64 >= n;  // (uniform: n is a multiple of 64)
+  const float v = tail ? sum_slices(part_b, CP, slices, i - n) : sum_slices(part, n, slices, i);
+  if (threadIdx.x >= 64) return;
+  if (tail) {
+    if (i - n < C) db[i - n] = v;
+    return;
+  }
+  const int ci = static_cast<int>(i % CP), co = static_cast<int>(i / CP % CP), k = static_cast<int>(i / (CP * CP));
+  if (co < C && ci < C) dw[(co * C + ci) * KW + k] = v;
+}
+
+__global__ __launch_bounds__(256) void k_sum_wgrad1(const float *__restrict__ part, int C, int slices,
+                                                    float *__restrict__ dw, float *__restrict__ db) {
+  const int64_t n = static_cast<int64_t>(C) * (KW + 1);
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const float v = sum_slices(part, n, slices, i);
+  if (threadIdx.x >= 64 || i >= n) return;
+  const int c = static_cast<int>(i / (KW + 1)), k = static_cast<int>(i % (KW + 1));
+  if (k < KW) dw[c * KW + k] = v;
+  else db[c] = v;
+}
+
+// g[b][c] = mean_t a[b][t][c]; logits[b][j] = bo[j] + sum_c wo[j][c] g[b][c].
+// One workgroup per series; a wave takes every 16th time step.
+__global__ __launch_bounds__(1024) void k_pool_linear(const float *__restrict__ a, int C, int L,
+                                                      const float *__restrict__ wo, const float *__restrict__ bo,
+                                                      float *__restrict__ g, float *__restrict__ logits) {
+  __shared__ float red[16][kMaxC];
+  __shared__ float gs[kMaxC];
+  const int b = blockIdx.x, tid = threadIdx.x;
+  const int c = tid & 63, q = tid >> 6;
+  float s = 0.0f;
+  if (c < C) {
+    const float *row = a + static_cast<int64_t>(b) * L * C + c;
+#pragma unroll 8
+    for (int t = q; t < L; t += 16) s += row[static_cast<int64_t>(t) * C];
+  }
+  red[q][c] = s;
+  __syncthreads();
+  if (tid < C) {
+    float v = 0.0f;
 #pragma unroll
-    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) {
-      gs[c] = s / static_cast<float>(L);
-      g[static_cast<int64_t>(b) * C + c] = s / static_cast<float>(L);
-    }
+    for (int i = 0; i < 16; ++i) v += red[i][tid];
+    gs[tid] = v / static_cast<float>(L);
+    g[static_cast<int64_t>(b) * C + tid] = gs[tid];
   }
   __syncthreads();
-  if (threadIdx.x < NCLS) {
-    const int j = threadIdx.x;
-    float v = bo[j];
-    for (int c = 0; c < C; ++c) v = fmaf(wo[j * C + c], gs[c], v);
-    logits[static_cast<int64_t>(b) * NCLS + j] = v;
+  if (tid < NCLS) {
+    float v = bo[tid];
+    for (int i = 0; i < C; ++i) v = fmaf(wo[tid * C + i], gs[i], v);
+    logits[static_cast<int64_t>(b) * NCLS + tid] = v;
   }
 }
 
@@ -529,37 +688,33 @@ __global__ void k_softmax_ce(const float *__restrict__ logits, const int32_t *__
     dlog[static_cast<int64_t>(b) * NCLS + j] = (expf(z[j] - mx) / s - (j == y ? 1.0f : 0.0f)) / B;
 }
 
-// Linear + pool backward.  Output-layer gradients (one thread per weight),
-// then dz3[b][c][t] = dg[b][c] / L * (a3 > 0) over the activations.
-__global__ void k_linear_bwd(const float *__restrict__ dlog, const float *__restrict__ g, int B,
-                             int C, float *__restrict__ dwo, float *__restrict__ dbo) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < NCLS * C) {
-    const int j = e / C, c = e - j * C;
-    float v = 0.0f;
-    for (int b = 0; b < B; ++b) v = fmaf(dlog[b * NCLS + j], g[static_cast<int64_t>(b) * C + c], v);
-    dwo[e] = v;
-  } else if (e < NCLS * C + NCLS) {
-    const int j = e - NCLS * C;
-    float v = 0.0f;
-    for (int b = 0; b < B; ++b) v += dlog[b * NCLS + j];
-    dbo[j] = v;
-  }
+// Output-layer gradients, one wave per weight: dwo[j][c], then dbo[j].
+__global__ __launch_bounds__(256) void k_linear_bwd(const float *__restrict__ dlog, const float *__restrict__ g, int B,
+                                                    int C, float *__restrict__ dwo, float *__restrict__ dbo) {
+  const int e = static_cast<int>(blockIdx.x) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (e >= NCLS * (C + 1)) return;
+  const int j = e / (C + 1), c = e - j * (C + 1);
+  float v = 0.0f;
+  for (int b = lane; b < B; b += 64)
+    v = fmaf(dlog[b * NCLS + j], c < C ? g[static_cast<int64_t>(b) * C + c] : 1.0f, v);
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+  if (lane != 0) return;
+  if (c < C) dwo[j * C + c] = v;
+  else dbo[j] = v;
 }
 
-__global__ void k_pool_bwd(const float *__restrict__ dlog, const float *__restrict__ wo,
-                           const float *__restrict__ a3, int64_t B, int C, int L,
-                           float *__restrict__ dz3) {
-  const int64_t total = B * C * L;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; e < total;
-       e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t bc = e / L;
-    const int b = static_cast<int>(bc / C), c = static_cast<int>(bc - static_cast<int64_t>(b) * C);
-    float dg = 0.0f;
+// Pool backward: the gradient of every time step of channel c, where its
+// activation is positive: dch[b][c] = sum_j dlog[b][j] wo[j][c] / L.
+__global__ void k_pool_bwd(const float *__restrict__ dlog, const float *__restrict__ wo, int64_t B, int C, int L,
+                           float *__restrict__ dch) {
+  const int64_t e = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= B * C) return;
+  const int b = static_cast<int>(e / C), c = static_cast<int>(e - static_cast<int64_t>(b) * C);
+  float dg = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NCLS; ++j) dg = fmaf(dlog[b * NCLS + j], wo[j * C + c], dg);
-    dz3[e] = a3[e] > 0.0f ? dg / static_cast<float>(L) : 0.0f;
-  }
+  for (int j = 0; j < NCLS; ++j) dg = fmaf(dlog[b * NCLS + j], wo[j * C + c], dg);
+  dch[e] = dg / static_cast<float>(L);
 }
 
 __global__ void k_mean(const float *__restrict__ v, int n, float *__restrict__ out) {
@@ -614,21 +769,106 @@ NetParams net_params(const float *theta, int C) {
   return p;
 }
 
-int64_t net_workspace_floats(int C, int64_t B, int64_t L) {
-  // a1, a2, a3, dz (x2), g, logits, dlog, loss_b, partials
+namespace {
+// Workspace of a training pass (floats).
+struct NetWs {
+  int64_t act, frags, slices, slices1, units;
+  int64_t a1, a2, a3, d2, g, dch, logits, dlog, loss_b, wf, part, part_b, part1, total;
+  NetWs(int C, int64_t B, int64_t L) {
+    const int64_t CP = pad32(C);
+    act = B * C * L;
+    frags = KW * CP * CP;
+    units = B * ((L + WT - 1) / WT);
+    // the partial gradients take the room that a stored gradient of the pooled
+    // layer would: more slices than that do not pay for their sums
+    const int64_t most = CP > 32 ? kSlices64 : 4 * kSlices64;
+    const int64_t room = (act + kNetSlices * static_cast<int64_t>(C) * (C * KW + 1)) / (frags + CP);
+    slices = units < most ? units : most;
+    slices = slices < room ? slices : room;
+    slices = slices > 1 ? slices : 1;
+    slices1 = units < kSlices1 ? units : kSlices1;
+    int64_t at = 0;
+    auto take = [&](int64_t n) {
+      const int64_t o = at;
+      at += (n + 63) / 64 * 64;
+      return o;
+    };
+    a1 = take(act); a2 = take(act); a3 = take(act); d2 = take(act);
+    g = take(B * C); dch = take(B * C);
+    logits = take(B * NCLS); dlog = take(B * NCLS); loss_b = take(B);
+    wf = take(4 * frags);
+    part = take(slices * frags); part_b = take(slices * CP); part1 = take(slices1 * C * (KW + 1));
+    total = at;
+  }
+};
+
+template <bool kBack, bool kMask>
+hipError_t launch_conv(const float *x, const float *chan, int C, int64_t B, int64_t L, const float *wf,
+                       const float *bias, const float *aprev, float *y, hipStream_t st) {
+  const dim3 grid(static_cast<unsigned>((L + CR - 1) / CR), static_cast<unsigned>(B));
+  const f32x4_t *w = reinterpret_cast<const f32x4_t *>(wf);
+  const size_t shm = sizeof(float) * (CR + KW - 1) * (pad32(C) + 1);
+  if (C > 32) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_conv_f32<2, kBack, kMask>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_conv_f32<2, kBack, kMask>), grid, dim3(256), shm, st, x, chan, C, static_cast<int>(L), w,
+                       bias, aprev, y);
+  } else {
+    hipLaunchKernelGGL((k_conv_f32<1, kBack, kMask>), grid, dim3(256), shm, st, x, chan, C, static_cast<int>(L), w,
+                       bias, aprev, y);
+  }
+  return hipGetLastError();
+}
+
+template <bool kMask>
+hipError_t launch_wgrad(const NetWs &W, const float *x, const float *dz, const float *chan, int C, int64_t L,
+                        float *ws, float *dw, float *db, hipStream_t st) {
+  const int64_t per = (W.units + W.slices - 1) / W.slices;
+  const unsigned used = static_cast<unsigned>((W.units + per - 1) / per);  // slices with work
+  if (C > 32)
+    hipLaunchKernelGGL((k_wgrad<2, kMask>), dim3(used), dim3(256), 0, st, x, dz, chan, C, static_cast<int>(L), W.units,
+                       per, ws + W.part, ws + W.part_b);
+  else
+    hipLaunchKernelGGL((k_wgrad<1, kMask>), dim3(used), dim3(64), 0, st, x, dz, chan, C, static_cast<int>(L), W.units,
+                       per, ws + W.part, ws + W.part_b);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const unsigned gx = static_cast<unsigned>(W.frags / 64 + (pad32(C) + 63) / 64);
+  hipLaunchKernelGGL(k_sum_wgrad, dim3(gx), dim3(256), 0, st, ws + W.part, ws + W.part_b, C, static_cast<int>(used),
+                     dw, db);
+  return hipGetLastError();
+}
+
+hipError_t launch_frags(const float *w, int C, int flip, float *wf, hipStream_t st) {
+  const unsigned n = static_cast<unsigned>(KW * pad32(C) * pad32(C) / 256);
+  hipLaunchKernelGGL(k_weight_frags, dim3(n), dim3(256), 0, st, w, C, flip, wf);
+  return hipGetLastError();
+}
+}  // namespace
+
+int64_t net_limit_floats(int C, int64_t B, int64_t L) {
   return 5 * B * C * L + B * C + 3 * B * NCLS + B + kNetSlices * (static_cast<int64_t>(C) * C * KW + C) + 64;
 }
+
+int64_t net_workspace_floats(int C, int64_t B, int64_t L) { return NetWs(C, B, L).total; }
 
 hipError_t net_forward(const float *theta, int C, const float *X, int64_t B, int64_t L,
                        int64_t ldx, float *ws, float *logits, hipStream_t st) {
   const NetParams P = net_params(theta, C);
-  float *a1 = ws, *a2 = a1 + B * C * L, *a3 = a2 + B * C * L;
-  float *g = a3 + 3 * B * C * L;  // after a3 and the two dz buffers
-  const dim3 grid(static_cast<unsigned>((L + TT - 1) / TT), static_cast<unsigned>(B));
-  hipLaunchKernelGGL(k_conv<0>, grid, dim3(256), 0, st, X, ldx, 0, 1, C, static_cast<int>(L), P.w1, P.b1, nullptr, a1);
-  hipLaunchKernelGGL(k_conv<0>, grid, dim3(256), 0, st, a1, C * L, L, C, C, static_cast<int>(L), P.w2, P.b2, nullptr, a2);
-  hipLaunchKernelGGL(k_conv<0>, grid, dim3(256), 0, st, a2, C * L, L, C, C, static_cast<int>(L), P.w3, P.b3, nullptr, a3);
-  hipLaunchKernelGGL(k_pool_linear, dim3(static_cast<unsigned>(B)), dim3(256), 0, st, a3, C, static_cast<int>(L), P.wo, P.bo, g, logits);
+  const NetWs W(C, B, L);
+  float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *wf = ws + W.wf;
+  hipError_t e = launch_frags(P.w2, C, 0, wf, st);
+  if (e == hipSuccess) e = launch_frags(P.w3, C, 0, wf + W.frags, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_conv1, dim3(static_cast<unsigned>((L + T1 - 1) / T1), static_cast<unsigned>(B)), dim3(256), 0, st,
+                     X, ldx, C, static_cast<int>(L), P.w1, P.b1, a1);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = launch_conv<false, false>(a1, nullptr, C, B, L, wf, P.b2, nullptr, a2, st);
+  if (e == hipSuccess) e = launch_conv<false, false>(a2, nullptr, C, B, L, wf + W.frags, P.b3, nullptr, a3, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_pool_linear, dim3(static_cast<unsigned>(B)), dim3(1024), 0, st, a3, C, static_cast<int>(L), P.wo,
+                     P.bo, ws + W.g, logits);
   return hipGetLastError();
 }
 
@@ -684,43 +924,37 @@ hipError_t net_forward_bf16(const float *theta, int C, const float *X, int64_t B
 hipError_t net_loss_grad(const float *theta, int C, const float *X, const int32_t *labels,
                          int64_t B, int64_t L, int64_t ldx, float *ws, float *loss,
                          float *grad, hipStream_t st) {
-  const NetParams P = net_params(theta, C);
-  float *a1 = ws, *a2 = a1 + B * C * L, *a3 = a2 + B * C * L;
-  float *dzA = a3 + B * C * L, *dzB = dzA + B * C * L;
-  float *g = dzB + B * C * L, *logits = g + B * C, *dlog = logits + B * NCLS;
-  float *loss_b = dlog + B * NCLS;
-  float *part = loss_b + B;
-  float *part_b = part + static_cast<int64_t>(kNetSlices) * C * C * KW;
+  const NetParams P = net_params(theta, C), G = net_params(grad, C);
+  const NetWs W(C, B, L);
+  auto mut = [](const float *p) { return const_cast<float *>(p); };
+  float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *d2 = ws + W.d2;
+  float *g = ws + W.g, *dch = ws + W.dch, *logits = ws + W.logits, *dlog = ws + W.dlog, *loss_b = ws + W.loss_b;
+  float *wf3 = ws + W.wf + 2 * W.frags, *wf2 = ws + W.wf + 3 * W.frags;
   hipError_t e = net_forward(theta, C, X, B, L, ldx, ws, logits, st);
+  if (e == hipSuccess) e = launch_frags(P.w3, C, 1, wf3, st);
+  if (e == hipSuccess) e = launch_frags(P.w2, C, 1, wf2, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_softmax_ce, dim3(blocks_for(B, 128)), dim3(128), 0, st, logits, labels, static_cast<int>(B), loss_b, dlog);
   hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, loss_b, static_cast<int>(B), loss);
-  const NetParams G = net_params(grad, C);
-  float *dwo = const_cast<float *>(G.wo), *dbo = const_cast<float *>(G.bo);
-  hipLaunchKernelGGL(k_linear_bwd, dim3(blocks_for(NCLS * C + NCLS, 256)), dim3(256), 0, st, dlog, g, static_cast<int>(B), C, dwo, dbo);
-  hipLaunchKernelGGL(k_pool_bwd, dim3(blocks_for(B * C * L, 256)), dim3(256), 0, st, dlog, P.wo, a3, B, C, static_cast<int>(L), dzA);
-
-  const int tiles = static_cast<int>(B * ((L + WT - 1) / WT));
-  const int64_t tps = (tiles + kNetSlices - 1) / kNetSlices;
-  const dim3 cgrid(static_cast<unsigned>((L + TT - 1) / TT), static_cast<unsigned>(B));
-  struct Layer { const float *in; int64_t ldb, ldc; int Ci; const float *w; float *dw; float *db; };
-  const Layer layers[3] = {
-      {a2, C * L, L, C, P.w3, const_cast<float *>(G.w3), const_cast<float *>(G.b3)},
-      {a1, C * L, L, C, P.w2, const_cast<float *>(G.w2), const_cast<float *>(G.b2)},
-      {X, ldx, 0, 1, P.w1, const_cast<float *>(G.w1), const_cast<float *>(G.b1)}};
-  float *dz = dzA, *dz_next = dzB;
-  for (int l = 0; l < 3; ++l) {
-    const Layer &Ly = layers[l];
-    hipLaunchKernelGGL(k_conv_wgrad, dim3(static_cast<unsigned>((Ly.Ci + 7) / 8), kNetSlices), dim3(256), 0, st,
-                       Ly.in, Ly.ldb, Ly.ldc, Ly.Ci, C, static_cast<int>(L), static_cast<int>(B), dz, tps, part, part_b);
-    const int64_t nw = static_cast<int64_t>(C) * Ly.Ci * KW;
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks_for(nw, 256)), dim3(256), 0, st, part, nw, kNetSlices, Ly.dw);
-    hipLaunchKernelGGL(k_sum_slices, dim3(blocks_for(C, 256)), dim3(256), 0, st, part_b, static_cast<int64_t>(C), kNetSlices, Ly.db);
-    if (l < 2) {  // gradient with respect to this layer's input, masked by its ReLU
-      hipLaunchKernelGGL(k_conv<1>, cgrid, dim3(256), 0, st, dz, C * L, L, C, C, static_cast<int>(L), Ly.w, nullptr, Ly.in, dz_next);
-      float *t = dz; dz = dz_next; dz_next = t;
-    }
-  }
+  hipLaunchKernelGGL(k_linear_bwd, dim3(static_cast<unsigned>((NCLS * (C + 1) + 3) / 4)), dim3(256), 0, st, dlog, g,
+                     static_cast<int>(B), C, mut(G.wo), mut(G.bo));
+  hipLaunchKernelGGL(k_pool_bwd, dim3(static_cast<unsigned>((B * C + 255) / 256)), dim3(256), 0, st, dlog, P.wo, B, C,
+                     static_cast<int>(L), dch);
+  e = hipGetLastError();
+  // layer 3: its gradient is dch where a3 > 0
+  if (e == hipSuccess) e = launch_wgrad<true>(W, a2, a3, dch, C, L, ws, mut(G.w3), mut(G.b3), st);
+  if (e == hipSuccess) e = launch_conv<true, true>(a3, dch, C, B, L, wf3, nullptr, a2, d2, st);
+  // layer 2, then layer 1 (its gradient takes the place of a3)
+  if (e == hipSuccess) e = launch_wgrad<false>(W, a1, d2, nullptr, C, L, ws, mut(G.w2), mut(G.b2), st);
+  float *d1 = a3;
+  if (e == hipSuccess) e = launch_conv<true, false>(d2, nullptr, C, B, L, wf2, nullptr, a1, d1, st);
+  if (e != hipSuccess) return e;
+  const int64_t per = (W.units + W.slices1 - 1) / W.slices1;
+  const unsigned used = static_cast<unsigned>((W.units + per - 1) / per);
+  hipLaunchKernelGGL(k_wgrad1, dim3(used), dim3(256), 0, st, X, ldx, d1, C, static_cast<int>(L), W.units, per,
+                     ws + W.part1);
+  hipLaunchKernelGGL(k_sum_wgrad1, dim3(static_cast<unsigned>((C * (KW + 1) + 63) / 64)), dim3(256), 0, st,
+                     ws + W.part1, C, static_cast<int>(used), mut(G.w1), mut(G.b1));
   return hipGetLastError();
 }
 

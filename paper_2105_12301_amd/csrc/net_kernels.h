@@ -13,11 +13,14 @@ struct NetParams {
   const float *w1, *b1, *w2, *b2, *w3, *b3, *wo, *bo;
 };
 
-constexpr int kNetSlices = 64;  // (series, time) slices of the weight-gradient reduction
+constexpr int kNetSlices = 64;  // (series, time) slices of a weight gradient the limit counts with
 
 int64_t net_param_count(int C);
 NetParams net_params(const float *theta, int C);
-// Workspace (floats) of one forward/backward pass over B series of length L.
+// Workspace (floats) of one forward/backward pass over B series of length L,
+// and the size that is held against the workspace limit (a stored gradient of
+// the pooled layer included, without the padding of the weights' fragments).
+int64_t net_limit_floats(int C, int64_t B, int64_t L);
 int64_t net_workspace_floats(int C, int64_t B, int64_t L);
 // Workspace of net_forward_bf16.
 int64_t net_infer_workspace_floats(int C, int64_t B, int64_t L);
