@@ -5,19 +5,19 @@
 // as many as fit 160 KB of LDS for the window) over the window that its
 // libraries' tables can touch, interleaved: vs[e][t] = y_t[off + e] - c_t with
 // c_t the target's mean (k_target_means, one value per target and call, the
-// same for every kernel), off = (E-1)*tau + Tp, rows S = tile_stride(T) floats
-// apart.
+// same for every kernel), off = (E-1)*tau + Tp.
 // One neighbour index q then addresses the T targets' samples as one
 // contiguous LDS segment, so a wave reads them with one 128-, 64- or 32-bit
-// access per lane instead of T scattered 32-bit gathers.  (Rows padded to
-// T + 4 floats, which spreads the random rows over more bank offsets, made
-// the headline lookups 5 % slower on gfx950; the rows are unpadded.)
+// access per lane instead of T scattered 32-bit gathers.  (The gathers' bank
+// conflicts do not bound it: rows padded to T + 4 floats were 5 % slower, and
+// made-up indices without any conflict took the same time.)
 //
 // Lane layout.  A wave walks one library's table: lane = 4 g + s, query group
 // g = 0..15 handles the queries p = g, g + 16, g + 32, ... and sub-lane s the
 // targets s*TPL .. s*TPL + TPL - 1 of the tile (TPL = T/4 targets per lane, at
-// least 1; for T < 4 some sub-lanes idle).  Per query the lane reads the table
-// row (K indices and weights, shared by the 4 lanes of the group), gathers
+// least 1; for T < 4 some sub-lanes idle).  Per query the four lanes of a group
+// each load a quarter of the table row (K indices and weights), one query
+// ahead, and pass it round by DPP; a lane gathers
 // vs[q_i][targets] for i = 0..K-1 and accumulates the prediction
 // yhat = sum_i w_i (y(t(q_i)+Tp) - c) with one float32 fused multiply-add per
 // neighbour in index order, and the sums of the observation o = vs[p] and
@@ -36,7 +36,12 @@
 //
 // Grid kernel: blockIdx.x = tile of targets, blockIdx.y = group of 16
 // library slots (one wave each); consecutive workgroups share their
-// libraries' tables in L2.  Work-list kernel (batched plan): one item = a
+// libraries' tables in L2; a wave that is done with its library loads its part
+// of the next tile meanwhile.  10000 series of 2000 samples: 199 -> 177 ms for
+// all E (rows loaded in quarters, tiles staged in lines: 97 -> 13 of 313 -> 240
+// thousand cycles a tile at K = 8); of the rest, 75 % is the walk itself
+// (issue: gathers, broadcasts and 4 fused adds a neighbour) and 19 % waiting for
+// the workgroup's slowest wave.  Work-list kernel (batched plan): one item = a
 // group of up to 16 libraries of similar length (longest first) against one
 // tile, workgroups persistent or one per item.
 #include <array>
@@ -67,9 +72,6 @@ struct Sums {
   double so, sp, soo, spp, sop;
 };
 
-// Row stride (floats) of a staged tile of T targets.
-__host__ __device__ constexpr int tile_stride(int T) { return T; }
-
 template <int N>
 struct VecOf;
 template <>
@@ -84,6 +86,37 @@ template <>
 struct VecOf<4> {
   using type = float4;
 };
+
+// A table row of K entries held by the 4 lanes of a query group: lane s loads
+// kPart consecutive entries from kStart(s) on (the last parts overlap instead
+// of passing the row's end), and entry i is read from its lane with a DPP
+// broadcast within the quad.  (Every lane loading the whole row moves four times
+// the bytes through the vector L1, 64 bytes a clock: 72 cycles a wave and query
+// at K = 9 against 36 of LDS reads; and rows loaded whole one query ahead do not
+// fit the registers.)
+template <int K>
+struct RowPart {
+  static constexpr int kPart = (K + 3) / 4;
+  static constexpr int start(int s) { return s * kPart < K - kPart ? s * kPart : K - kPart; }
+  static constexpr int lane_of(int i) { return i / kPart; }
+  static constexpr int at(int i) { return i - start(lane_of(i)); }
+};
+template <int S>
+__device__ __forceinline__ int quad_get(int v) {
+  return __builtin_amdgcn_mov_dpp(v, S * 0x55, 0xf, 0xf, false);  // quad_perm [S, S, S, S]
+}
+template <int S>
+__device__ __forceinline__ float quad_get(float v) {
+  return __int_as_float(quad_get<S>(__float_as_int(v)));
+}
+
+template <int I0, int I1, typename F>
+__device__ __forceinline__ void each(F &&f) {  // f(I0), ..., f(I1 - 1) as constants
+  if constexpr (I0 < I1) {
+    f(std::integral_constant<int, I0>{});
+    each<I0 + 1, I1>(f);
+  }
+}
 
 template <int TPL>
 __device__ __forceinline__ void lds_read(const float *p, float (&v)[TPL]) {
@@ -109,7 +142,7 @@ __device__ __forceinline__ void lds_read(const float *p, float (&v)[TPL]) {
 template <int K, int TPL, bool kPred>
 __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
                                            const float *__restrict__ tw, const int m,
-                                           const float *vs, const int T, const int S,
+                                           const float *vs, const int T,
                                            float *const (&pred)[TPL], const float (&c)[TPL],
                                            Sums (&s)[TPL]) {
   const int lane = threadIdx.x & (kWave - 1);
@@ -118,6 +151,25 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
   // idle sub-lanes (T < 4) read sub-lane 0's targets; their sums are unused
   const int col = sub * TPL < T ? sub * TPL : 0;
   const float *base = vs + col;
+  // Row q of the tile, T (a power of two) floats apart: constant for the widths 8 and 16.
+  const int lgS = TPL == 1 ? 31 - __builtin_clz(T) : (TPL == 2 ? 3 : 4);
+  auto row_of = [&](int q) { return base + (static_cast<uint32_t>(q) << lgS); };
+  using Row = RowPart<K>;
+  const int part0 = sub * Row::kPart < K - Row::kPart ? sub * Row::kPart : K - Row::kPart;
+  const int32_t *__restrict__ ti = tidx + part0;
+  const float *__restrict__ tv = tw + part0;
+  // The next query's part is loaded while this one's gathers run.
+  int qn[Row::kPart];
+  float wn[Row::kPart];
+  auto load_row = [&](int p) {
+    const int64_t row = static_cast<int64_t>(p) * K;
+#pragma unroll
+    for (int i = 0; i < Row::kPart; ++i) {
+      qn[i] = ti[row + i];
+      wn[i] = tv[row + i];
+    }
+  };
+  if (g < m) load_row(g);
 #pragma unroll
   for (int u = 0; u < TPL; ++u) s[u] = Sums{0.0, 0.0, 0.0, 0.0, 0.0};
   for (int p0 = g; p0 < m; p0 += kGroups * kRun) {
@@ -128,39 +180,42 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
 #pragma unroll
       for (int j = 0; j < 5; ++j) f[u][j] = 0.0f;
     for (int p = p0; p < pe; p += kGroups) {
-      const int64_t row = static_cast<int64_t>(p) * K;
-      int q[K];
-      float w[K];
+      uint32_t qo[Row::kPart];  // LDS offset of the neighbour's row (floats)
+      float w[Row::kPart];
 #pragma unroll
-      for (int i = 0; i < K; ++i) {
-        q[i] = tidx[row + i];
-        w[i] = tw[row + i];
+      for (int i = 0; i < Row::kPart; ++i) {
+        qo[i] = static_cast<uint32_t>(qn[i]) << lgS;
+        w[i] = wn[i];
       }
+      load_row(p + kGroups < m ? p + kGroups : p);
       float yh[TPL];
 #pragma unroll
       for (int u = 0; u < TPL; ++u) yh[u] = 0.0f;
+      float ov[TPL];
+      lds_read<TPL>(row_of(p), ov);
       // gathers in chunks of kChunk neighbours (bounds the registers in flight)
-      constexpr int kChunk = TPL == 4 ? 4 : (TPL == 2 ? 8 : 16);
-#pragma unroll
-      for (int i0 = 0; i0 < K; i0 += kChunk) {
+      constexpr int kChunk = TPL == 4 ? 6 : (TPL == 2 ? 8 : 16);
+      each<0, (K + kChunk - 1) / kChunk>([&](auto CC) {
+        constexpr int i0 = decltype(CC)::value * kChunk;
+        constexpr int i1 = i0 + kChunk < K ? i0 + kChunk : K;
         float v[kChunk][TPL];
         // The chunk's gathers are issued at a raised wave priority, so the
-        // SIMD's waves keep the LDS queue fed before their arithmetic (the
-        // lookups are bound by LDS throughput; 3 % faster on the
-        // 10000 x 2000 step, results unchanged).
+        // SIMD's waves keep the LDS queue fed before their arithmetic.
         __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int i = i0; i < (i0 + kChunk < K ? i0 + kChunk : K); ++i)
-          lds_read<TPL>(base + __umul24(q[i], S), v[i - i0]);  // q < 2^24: one full-rate multiply
+        each<i0, i1>([&](auto IC) {
+          constexpr int i = decltype(IC)::value;
+          const int o = quad_get<Row::lane_of(i)>(static_cast<int>(qo[Row::at(i)]));
+          lds_read<TPL>(base + static_cast<uint32_t>(o), v[i - i0]);
+        });
         __builtin_amdgcn_s_setprio(0);
+        each<i0, i1>([&](auto IC) {
+          constexpr int i = decltype(IC)::value;
+          const float wi = quad_get<Row::lane_of(i)>(w[Row::at(i)]);
 #pragma unroll
-        for (int i = i0; i < (i0 + kChunk < K ? i0 + kChunk : K); ++i)
-#pragma unroll
-          for (int u = 0; u < TPL; ++u) yh[u] = fmaf(w[i], v[i - i0][u], yh[u]);
+          for (int u = 0; u < TPL; ++u) yh[u] = fmaf(wi, v[i - i0][u], yh[u]);
+        });
         if (K > kChunk) __builtin_amdgcn_sched_barrier(0);
-      }
-      float ov[TPL];
-      lds_read<TPL>(base + __umul24(p, S), ov);
+      });
 #pragma unroll
       for (int u = 0; u < TPL; ++u) {
         // explicit fused forms: the same operations in every instantiation
@@ -201,36 +256,117 @@ __device__ __forceinline__ float pair_rho(int m, const Sums &s) {
       mom_rho(mom_from_shifted_sums(static_cast<double>(m), 0.0, 0.0, s.so, s.sp, s.soo, s.spp, s.sop)));
 }
 
-// Stage targets tgt[0..Tn) over the window [off, off + n) into vs[e][t]
-// (row stride S = tile_stride(T), targets Tn..T-1 zero), relative to
-// cs[t] = a.cmean[target]; zero past a target's own length.  Ends with a
-// barrier.
-__device__ __forceinline__ void stage_tile(const LookupArgs &a, const int *tgt, int Tn, int T,
-                                           int lgT, int off, int n, float *vs, float *cs) {
-  const int S = tile_stride(T);
-  if (static_cast<int>(threadIdx.x) < T) {
-    const int t = threadIdx.x;
-    cs[t] = t < Tn ? a.cmean[tgt[t]] : 0.0f;
+// A tile of T targets over the window [off, off + n), staged relative to
+// cs[t] = a.cmean[target] as vs[e][t] (targets Tn..T-1 and samples past a
+// target's own length zero).  A unit is 64 consecutive samples of 4 targets: a
+// wave loads them as four 256-byte lines and writes one 16-byte word per lane,
+// and a wave's units all belong to the same 4 targets, whose ids, lengths and
+// means are wave-uniform.  The loads of a whole tile (at most 40 floats a
+// thread) are in flight at once, separate from the LDS writes, so that a wave
+// that is done with its library loads its share of the next tile while the
+// others finish.  (Staged element by element, target fastest, a tile of 16 x
+// 2000 took 97 of 313 thousand cycles.)
+constexpr int kUnits = static_cast<int>((kLdsFloats + kThreads * 4 - 1) / (kThreads * 4)) + 1;
+struct Tile {
+  const int32_t *ids;  // the launch's target list, or nullptr: identity
+  int t0, Tn;          // targets ids[t0 .. t0 + Tn)
+};
+template <int TQ>
+struct TileLoad {
+  float r[kUnits][4];
+  __device__ __forceinline__ static int block_of(int j) {
+    return __builtin_amdgcn_readfirstlane((static_cast<int>(threadIdx.x) / kWave + kWaves * j) / TQ);
   }
-  __syncthreads();
-  bool bad = false;
-  const int total = n * T;
-  for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-    const int e = idx >> lgT;
-    const int t = idx & (T - 1);
-    float v = 0.0f;
-    if (t < Tn) {
-      const int64_t Ly = a.Ly_dev ? a.Ly_dev[tgt[t]] : a.ldy;
-      if (off + e < Ly) {
-        const float y = a.Y[static_cast<int64_t>(tgt[t]) * a.ldy + off + e];
-        bad |= !isfinite(y);
-        v = y - cs[t];
+  __device__ __forceinline__ static int first_target() {  // of the wave's four
+    return __builtin_amdgcn_readfirstlane((static_cast<int>(threadIdx.x) / kWave) % TQ * 4);
+  }
+  __device__ __forceinline__ static int id_of(const Tile &tile, int u) {
+    const int t = first_target() + u < tile.Tn ? first_target() + u : 0;
+    return __builtin_amdgcn_readfirstlane(tile.ids ? tile.ids[tile.t0 + t] : tile.t0 + t);
+  }
+  __device__ __forceinline__ void load(const LookupArgs &a, const Tile &tile, int off, int n) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const float *row[4];
+    int last[4];  // the target's last sample: no address past it
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int id = id_of(tile, u);
+      const int64_t end = off + static_cast<int64_t>(n);
+      const int64_t len = a.Ly_dev && a.Ly_dev[id] < end ? a.Ly_dev[id] : (a.ldy < end ? a.ldy : end);
+      row[u] = len > 0 ? a.Y + static_cast<int64_t>(id) * a.ldy : a.cmean + id;
+      last[u] = len > 0 ? static_cast<int>(len) - 1 : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < kUnits; ++j) {
+      const int e0 = block_of(j) * kWave;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r[j][u] = 0.0f;
+      if (e0 >= n) continue;  // uniform
+      const int i = off + e0 + lane;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r[j][u] = row[u][i < last[u] ? i : last[u]];  // unused where clamped
+    }
+  }
+  __device__ __forceinline__ void store(const LookupArgs &a, const Tile &tile, int off, int n, float *vs, int T) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int tq = first_target();
+    float c[4];
+    int end[4];  // samples of the window that the target has
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int id = id_of(tile, u);
+      c[u] = a.cmean[id];
+      const int64_t len = (a.Ly_dev ? a.Ly_dev[id] : a.ldy) - off;
+      end[u] = tq + u < tile.Tn ? static_cast<int>(len < n ? len : n) : 0;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < kUnits; ++j) {
+      const int e0 = block_of(j) * kWave;
+      if (e0 >= n) continue;  // uniform
+      const int e = e0 + lane;
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool in = e < end[u];
+        bad |= in && !isfinite(r[j][u]);
+        v[u] = in ? r[j][u] - c[u] : 0.0f;
+      }
+      if (e >= n) continue;
+      float *out = vs + static_cast<int64_t>(e) * T + tq;
+      if (T >= 4) {
+        *reinterpret_cast<float4 *>(out) = float4{v[0], v[1], v[2], v[3]};
+      } else {  // 1 or 2 targets
+        out[0] = v[0];
+        if (T == 2) out[1] = v[1];
       }
     }
-    vs[e * S + t] = v;
+    if (bad) atomicOr(a.status, 1);
   }
-  if (bad) atomicOr(a.status, 1);
-  __syncthreads();
+};
+// Units of a tile beyond kUnits (one or two targets over a long window: the
+// window outgrows the units' four targets) are staged by further rounds.
+template <int TQ>
+__device__ __forceinline__ void stage_rest(const LookupArgs &a, const Tile &tile, int off, int n, float *vs, int T) {
+  if (TQ > 1) return;
+  for (int at = kUnits * kThreads; at < n; at += kUnits * kThreads) {
+    TileLoad<TQ> l;
+    l.load(a, tile, off + at, n - at);
+    l.store(a, tile, off + at, n - at, vs + static_cast<int64_t>(at) * T, T);
+  }
+}
+template <int TPL>
+constexpr int tile_quads() {
+  return TPL;  // T = 16, 8, and 4 or fewer targets: 4, 2, 1 groups of four
+}
+// Ids and means of a staged tile, for the epilogues.
+__device__ __forceinline__ void tile_ids(const LookupArgs &a, const Tile &tile, int T, int *tgt, float *cs) {
+  const int t = static_cast<int>(threadIdx.x);
+  if (t < T) {
+    const int id = t < tile.Tn ? (tile.ids ? tile.ids[tile.t0 + t] : tile.t0 + t) : 0;
+    tgt[t] = id;
+    cs[t] = t < tile.Tn ? a.cmean[id] : 0.0f;
+  }
 }
 
 // One wave's library (m queries, table tidx/tw) against the staged tile
@@ -241,7 +377,6 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
                                              const float *tw, int lib, int64_t Lx, int m,
                                              const float *vs, const float *cs, const int *tgt,
                                              int Tn, int T) {
-  const int S = tile_stride(T);
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane & (kSubs - 1);
   bool ok[TPL];
@@ -261,9 +396,9 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
   // predictions are written only with one target per lane (tiles of at most
   // 4 targets), which keeps the wider instantiations free of their registers
   if (TPL == 1 && a.pred)
-    tile_pairs<K, TPL, TPL == 1>(tidx, tw, m, vs, T, S, pred, c, s);
+    tile_pairs<K, TPL, TPL == 1>(tidx, tw, m, vs, T, pred, c, s);
   else
-    tile_pairs<K, TPL, false>(tidx, tw, m, vs, T, S, pred, c, s);
+    tile_pairs<K, TPL, false>(tidx, tw, m, vs, T, pred, c, s);
   if (a.rho && lane < kSubs) {
 #pragma unroll
     for (int u = 0; u < TPL; ++u)
@@ -299,7 +434,6 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
     grp = kXcds * (k / kTileCols) + i % kXcds;
   }
   const int sbase = slot0 + grp * kWaves;
-  const int lgT = 31 - __builtin_clz(T);
   int n_blk = 0;  // widest query range of the workgroup's libraries
   for (int w = 0; w < kWaves; ++w) {
     const int slot = sbase + w;
@@ -321,14 +455,25 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
   const int64_t tbl = static_cast<int64_t>(slot) * a.tbl_stride;
   // tiles blockIdx.x, blockIdx.x + gridDim.x, ... (one per workgroup when the
   // host sized the grid to the target count)
-  for (int tile = col; tile * T < ntgt; tile += ncol) {
+  if (col * T >= ntgt) return;
+  constexpr int TQ = tile_quads<TPL>();
+  auto tile_at = [&](int tile) {
     const int t0 = tile * T;
-    const int Tn = ntgt - t0 < T ? ntgt - t0 : T;
+    return Tile{tids, t0, ntgt - t0 < T ? ntgt - t0 : T};
+  };
+  TileLoad<TQ> load;
+  load.load(a, tile_at(col), off, n_blk);
+  for (int tile = col;;) {
+    const Tile now = tile_at(tile);
     if (tile != col) __syncthreads();  // the previous tile is consumed
-    if (static_cast<int>(threadIdx.x) < Tn)
-      tgt[threadIdx.x] = tids ? tids[t0 + threadIdx.x] : t0 + static_cast<int>(threadIdx.x);
-    stage_tile(a, tgt, Tn, T, lgT, off, n_blk, vs, cs);
-    if (on) wave_library<K, TPL>(a, a.idx + tbl, a.w + tbl, lib, Lx, m, vs, cs, tgt, Tn, T);
+    tile_ids(a, now, T, tgt, cs);
+    load.store(a, now, off, n_blk, vs, T);
+    stage_rest<TQ>(a, now, off, n_blk, vs, T);
+    __syncthreads();
+    if (on) wave_library<K, TPL>(a, a.idx + tbl, a.w + tbl, lib, Lx, m, vs, cs, tgt, now.Tn, T);
+    tile += ncol;
+    if (tile * T >= ntgt) break;
+    load.load(a, tile_at(tile), off, n_blk);
   }
 }
 
@@ -366,14 +511,23 @@ __global__ __launch_bounds__(kThreads) void k_lookup_items(LookupArgs a,
     const int first = __builtin_amdgcn_readfirstlane(items[it].first);
     const int count = __builtin_amdgcn_readfirstlane(items[it].count);
     const int Tn = count < T ? count : T;
-    const int lgT = 31 - __builtin_clz(T);
     // the first library of an item is its longest: its window covers all
     const int lib0 = __builtin_amdgcn_readfirstlane(a.item_libs[at]);
     const int ms = static_cast<int>((a.Lx_dev ? a.Lx_dev[lib0] : a.Lx_uni) - off);
-    if (static_cast<int>(threadIdx.x) < Tn) tgt[threadIdx.x] = a.bucket_ids[a.bucket_at[E] + first + threadIdx.x];
-    __syncthreads();
     if (ms < 1) continue;  // uniform: nothing of this item can be defined
-    stage_tile(a, tgt, Tn, T, lgT, off, ms, vs, cs);
+    const Tile tile{a.bucket_ids + a.bucket_at[E], first, Tn};
+    tile_ids(a, tile, T, tgt, cs);
+    auto stage = [&](auto QC) {
+      constexpr int TQ = decltype(QC)::value;
+      TileLoad<TQ> load;
+      load.load(a, tile, off, ms);
+      load.store(a, tile, off, ms, vs, T);
+      stage_rest<TQ>(a, tile, off, ms, vs, T);
+    };
+    if (T >= 16) stage(std::integral_constant<int, 4>{});
+    else if (T == 8) stage(std::integral_constant<int, 2>{});
+    else stage(std::integral_constant<int, 1>{});
+    __syncthreads();
     if (wave < nlib) {  // uniform per wave
       const int lib = __builtin_amdgcn_readfirstlane(a.item_libs[at + wave]);
       const int64_t Lx = a.Lx_dev ? a.Lx_dev[lib] : a.Lx_uni;
@@ -447,11 +601,11 @@ hipError_t launch_target_means(const float *Y, int64_t ldy, const int64_t *Ly_de
 
 int lookup_tile_targets(int64_t m) {
   int T = kLookupItemMaxTargets;
-  while (T > 1 && static_cast<int64_t>(tile_stride(T)) * m > kLdsFloats) T >>= 1;
+  while (T > 1 && static_cast<int64_t>(T) * m > kLdsFloats) T >>= 1;
   return T;
 }
 
-int64_t lookup_tile_floats(int T, int64_t m) { return static_cast<int64_t>(tile_stride(T)) * m; }
+int64_t lookup_tile_floats(int T, int64_t m) { return static_cast<int64_t>(T) * m; }
 
 hipError_t launch_lookup(const LookupArgs &a, int nslots, int64_t m_max, hipStream_t st) {
   static const auto t4 = make_table<4>(std::make_index_sequence<EDM_K_MAX>{});
