@@ -135,16 +135,28 @@ __device__ __forceinline__ void lds_read(const float *p, float (&v)[TPL]) {
   }
 }
 
+// A library's queries split over waves: wave `part` of `parts` (a power of two)
+// takes the runs part, part + parts, ... of every query group and leaves their
+// float32 sums in LDS (ex: kRunSums floats a wave); after each of `rounds`
+// rounds the library's first wave adds them in the order of the runs, so the
+// sums are those of one wave.
+struct Split {
+  int part = 0, parts = 1, rounds = 0;
+  float *ex = nullptr;  // of the library's first wave
+};
+constexpr int kRunSums = 5 * kWave;
+
 // Skill sums of one wave's library against the staged tile (row stride T
 // floats).  Lane (g, s) handles targets s*TPL + u of the tile; every lane
 // returns the wave totals of its targets.  pred[u] (or null): prediction row
 // of target u of the lane, written as yhat + c[u].
-template <int K, int TPL, bool kPred>
+template <int K, int TPL, bool kPred, bool kSplit>
 __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
                                            const float *__restrict__ tw, const int m,
                                            const float *vs, const int T,
                                            float *const (&pred)[TPL], const float (&c)[TPL],
-                                           Sums (&s)[TPL]) {
+                                           Sums (&s)[TPL], const Split &split) {
+  static_assert(!kSplit || TPL == 1, "exchange area: one target a lane");
   const int lane = threadIdx.x & (kWave - 1);
   const int g = lane >> 2;
   const int sub = lane & (kSubs - 1);
@@ -169,12 +181,10 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
       wn[i] = tv[row + i];
     }
   };
-  if (g < m) load_row(g);
 #pragma unroll
   for (int u = 0; u < TPL; ++u) s[u] = Sums{0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int p0 = g; p0 < m; p0 += kGroups * kRun) {
+  auto run = [&](int p0, float (&f)[TPL][5]) {
     const int pe = m < p0 + kGroups * kRun ? m : p0 + kGroups * kRun;
-    float f[TPL][5];
 #pragma unroll
     for (int u = 0; u < TPL; ++u)
 #pragma unroll
@@ -229,13 +239,39 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
         }
       }
     }
+  };
+  auto add = [&](Sums &t, const float *f, int step) {
+    t.so += static_cast<double>(f[0]);
+    t.sp += static_cast<double>(f[step]);
+    t.soo += static_cast<double>(f[2 * step]);
+    t.spp += static_cast<double>(f[3 * step]);
+    t.sop += static_cast<double>(f[4 * step]);
+  };
+  constexpr int kStep = kGroups * kRun;
+  float f[TPL][5];
+  if constexpr (kSplit) {
+    float *mine = split.ex + split.part * kRunSums + lane;
+    for (int r0 = 0; r0 < split.rounds * split.parts; r0 += split.parts) {
+      const int p0 = g + (r0 + split.part) * kStep;
+      if (p0 < m) {
+        load_row(p0);
+        run(p0, f);
 #pragma unroll
-    for (int u = 0; u < TPL; ++u) {
-      s[u].so += static_cast<double>(f[u][0]);
-      s[u].sp += static_cast<double>(f[u][1]);
-      s[u].soo += static_cast<double>(f[u][2]);
-      s[u].spp += static_cast<double>(f[u][3]);
-      s[u].sop += static_cast<double>(f[u][4]);
+        for (int j = 0; j < 5; ++j) mine[j * kWave] = f[0][j];
+      }
+      __syncthreads();
+      if (split.part == 0)
+        for (int w = 0; w < split.parts; ++w)
+          if (g + (r0 + w) * kStep < m) add(s[0], mine + w * kRunSums, kWave);
+      __syncthreads();
+    }
+    if (split.part != 0) return;
+  } else {
+    if (g < m) load_row(g);
+    for (int p0 = g; p0 < m; p0 += kStep) {
+      run(p0, f);
+#pragma unroll
+      for (int u = 0; u < TPL; ++u) add(s[u], f[u], 1);
     }
   }
 #pragma unroll
@@ -372,11 +408,11 @@ __device__ __forceinline__ void tile_ids(const LookupArgs &a, const Tile &tile, 
 // One wave's library (m queries, table tidx/tw) against the staged tile
 // tgt[0..Tn): sums, then rho (and predictions) for the pairs that are
 // defined (target at least as long as the library).
-template <int K, int TPL>
+template <int K, int TPL, bool kSplit = false>
 __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t *tidx,
                                              const float *tw, int lib, int64_t Lx, int m,
                                              const float *vs, const float *cs, const int *tgt,
-                                             int Tn, int T) {
+                                             int Tn, int T, const Split &split = Split{}) {
   const int lane = threadIdx.x & (kWave - 1);
   const int sub = lane & (kSubs - 1);
   bool ok[TPL];
@@ -396,9 +432,10 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
   // predictions are written only with one target per lane (tiles of at most
   // 4 targets), which keeps the wider instantiations free of their registers
   if (TPL == 1 && a.pred)
-    tile_pairs<K, TPL, TPL == 1>(tidx, tw, m, vs, T, pred, c, s);
+    tile_pairs<K, TPL, TPL == 1, kSplit>(tidx, tw, m, vs, T, pred, c, s, split);
   else
-    tile_pairs<K, TPL, false>(tidx, tw, m, vs, T, pred, c, s);
+    tile_pairs<K, TPL, false, kSplit>(tidx, tw, m, vs, T, pred, c, s, split);
+  if (kSplit && (split.part != 0 || m <= 0)) return;
   if (a.rho && lane < kSubs) {
 #pragma unroll
     for (int u = 0; u < TPL; ++u)
@@ -408,9 +445,12 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
 
 // Grid kernel: blockIdx.x = tile of T targets (bucket positions
 // [x*T, x*T + T)), blockIdx.y = group of kWaves library slots from slot0;
-// ms bounds every staged window (the dynamic LDS holds T * ms floats).
-template <int K, int TPL>
-__global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int nslots, int slot0) {
+// ms bounds every staged window (the dynamic LDS holds T * ms floats, and the
+// split form's exchange area from ex_at on).  kSplit: 1 << lg_parts waves walk
+// one library.
+template <int K, int TPL, bool kSplit>
+__global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int nslots, int slot0, int lg_parts,
+                                                     int ex_at) {
   extern __shared__ float4 lds4[];
   float *vs = reinterpret_cast<float *>(lds4);
   __shared__ float cs[kLookupItemMaxTargets];
@@ -433,9 +473,11 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
     ncol = kTileCols;
     grp = kXcds * (k / kTileCols) + i % kXcds;
   }
-  const int sbase = slot0 + grp * kWaves;
+  const int lgp = kSplit ? lg_parts : 0;
+  const int nlib = kWaves >> lgp;  // libraries of the workgroup
+  const int sbase = slot0 + grp * nlib;
   int n_blk = 0;  // widest query range of the workgroup's libraries
-  for (int w = 0; w < kWaves; ++w) {
+  for (int w = 0; w < nlib; ++w) {
     const int slot = sbase + w;
     if (slot >= slot0 + nslots) break;
     const int lib = a.lib_ids ? a.lib_ids[slot] : slot;
@@ -446,7 +488,7 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
   if (n_blk - 1 - 2 * a.excl < K) return;  // no table in this workgroup (uniform)
 
   const int wave = static_cast<int>(threadIdx.x) / kWave;
-  const int slot = __builtin_amdgcn_readfirstlane(sbase + wave);
+  const int slot = __builtin_amdgcn_readfirstlane(sbase + (wave >> lgp));
   const bool in = slot < slot0 + nslots;
   const int lib = in ? (a.lib_ids ? a.lib_ids[slot] : slot) : 0;
   const int64_t Lx = in ? (a.Lx_dev ? a.Lx_dev[lib] : a.Lx_uni) : 0;
@@ -470,7 +512,16 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
     load.store(a, now, off, n_blk, vs, T);
     stage_rest<TQ>(a, now, off, n_blk, vs, T);
     __syncthreads();
-    if (on) wave_library<K, TPL>(a, a.idx + tbl, a.w + tbl, lib, Lx, m, vs, cs, tgt, now.Tn, T);
+    if constexpr (kSplit) {  // every wave reaches the rounds' barriers
+      Split split;
+      split.parts = 1 << lgp;
+      split.part = wave & (split.parts - 1);
+      split.rounds = (n_blk + kGroups * kRun * split.parts - 1) / (kGroups * kRun * split.parts);
+      split.ex = vs + ex_at + (wave - split.part) * kRunSums;
+      wave_library<K, TPL, true>(a, a.idx + tbl, a.w + tbl, lib, Lx, on ? m : 0, vs, cs, tgt, now.Tn, T, split);
+    } else {
+      if (on) wave_library<K, TPL>(a, a.idx + tbl, a.w + tbl, lib, Lx, m, vs, cs, tgt, now.Tn, T);
+    }
     tile += ncol;
     if (tile * T >= ntgt) break;
     load.load(a, tile_at(tile), off, n_blk);
@@ -566,24 +617,75 @@ __global__ __launch_bounds__(256) void k_target_means(const float *__restrict__ 
   if (lane == 0) cmean[t] = L > 0 ? static_cast<float>(sum / static_cast<double>(L)) : 0.0f;
 }
 
-using LaunchFn = hipError_t (*)(const LookupArgs &, dim3, size_t, int, int, int, hipStream_t);
+using LaunchFn = hipError_t (*)(const LookupArgs &, dim3, size_t, int, int, int, int, int, hipStream_t);
 
-template <int K, int TPL>
-hipError_t launch_k(const LookupArgs &a, dim3 grid, size_t shm, int T, int nslots, int slot0,
-                    hipStream_t st) {
-  const void *fn = reinterpret_cast<const void *>(&k_lookup<K, TPL>);
+template <int K, int TPL, bool kSplit>
+hipError_t launch_k(const LookupArgs &a, dim3 grid, size_t shm, int T, int nslots, int slot0, int lg_parts,
+                    int ex_at, hipStream_t st) {
+  const void *fn = reinterpret_cast<const void *>(&k_lookup<K, TPL, kSplit>);
   if (shm > 65536) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        static_cast<int>(shm));
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((k_lookup<K, TPL>), grid, dim3(kThreads), shm, st, a, T, nslots, slot0);
+  hipLaunchKernelGGL((k_lookup<K, TPL, kSplit>), grid, dim3(kThreads), shm, st, a, T, nslots, slot0, lg_parts,
+                     ex_at);
   return hipGetLastError();
 }
 
-template <int TPL, size_t... I>
+template <int TPL, bool kSplit, size_t... I>
 constexpr auto make_table(std::index_sequence<I...>) {
-  return std::array<LaunchFn, sizeof...(I)>{&launch_k<static_cast<int>(I) + 1, TPL>...};
+  return std::array<LaunchFn, sizeof...(I)>{&launch_k<static_cast<int>(I) + 1, TPL, kSplit>...};
+}
+
+LaunchFn launch_fn(int k, int T, bool split) {
+  constexpr auto ks = std::make_index_sequence<EDM_K_MAX>{};
+  static const auto t4 = make_table<4, false>(ks);
+  static const auto t2 = make_table<2, false>(ks);
+  static const auto t1 = make_table<1, false>(ks);
+  static const auto s1 = make_table<1, true>(ks);
+  return (split ? s1 : T >= 16 ? t4 : T == 8 ? t2 : t1)[static_cast<size_t>(k - 1)];
+}
+
+// Shape of a launch: T targets a tile, 1 << lg_parts waves a library.
+struct Shape {
+  int T, lg_parts, ex_at;
+  size_t lds;
+  bool split() const { return lg_parts > 0; }
+  int libs() const { return kWaves >> lg_parts; }
+};
+
+// A wave walks a library's queries one after the other, about 0.6 us a step of
+// 16 queries whether it has its SIMD for itself or shares it with three others, so a launch
+// of few libraries or few tiles takes one whole walk (1000 queries: 40 us) while most waves or CUs idle.
+// A library's runs of 128 queries then go to 2 to 16 waves, over tiles of at
+// most 4 targets: the form with the least estimated time of its workgroups in
+// rounds of one per CU, a round taking (in walks) 1/W for the walk by W waves,
+// three quarters of that at 4 targets, and 0.15 for staging and exchange.  One
+// library of 1000 queries against 2000 targets: 48 -> 18 us with the
+// predictions; eight libraries: 374 -> 334 us for sweep and cross map.
+constexpr int64_t kCus = 256;
+Shape shape_for(int T, int nslots, int64_t m_max, int64_t ntgt) {
+  while (T > 1 && T / 2 >= ntgt) T >>= 1;  // no wider than the target count needs
+  auto lds = [](int64_t floats) { return sizeof(float) * static_cast<size_t>(floats); };
+  auto rounds = [&](int t, int waves) {
+    const int64_t groups = (static_cast<int64_t>(nslots) * waves + kWaves - 1) / kWaves;
+    return (groups * ((ntgt + t - 1) / t) + kCus - 1) / kCus;
+  };
+  Shape best{T, 0, 0, lds(lookup_tile_floats(T, m_max))};
+  int64_t cost = rounds(T, 1) * (80 + 12);  // in 1/80 of a walk
+  int Ts = T < 4 ? T : 4;
+  while (Ts > 1 && lookup_tile_floats(Ts, m_max) + kWaves * kRunSums > kLdsFloats) Ts >>= 1;
+  const int64_t tile = lookup_tile_floats(Ts, m_max);
+  if (tile + kWaves * kRunSums > kLdsFloats) return best;
+  const int64_t runs = (m_max + kGroups * kRun - 1) / (kGroups * kRun);
+  for (int lg = 1; (1 << lg) <= kWaves && (1 << (lg - 1)) < runs; ++lg) {
+    const int64_t c = rounds(Ts, 1 << lg) * ((60 >> lg) + 12);
+    if (c >= cost) continue;
+    cost = c;
+    best = Shape{Ts, lg, static_cast<int>(tile), lds(tile + kWaves * kRunSums)};
+  }
+  return best;
 }
 
 }  // namespace
@@ -608,23 +710,19 @@ int lookup_tile_targets(int64_t m) {
 int64_t lookup_tile_floats(int T, int64_t m) { return static_cast<int64_t>(T) * m; }
 
 hipError_t launch_lookup(const LookupArgs &a, int nslots, int64_t m_max, hipStream_t st) {
-  static const auto t4 = make_table<4>(std::make_index_sequence<EDM_K_MAX>{});
-  static const auto t2 = make_table<2>(std::make_index_sequence<EDM_K_MAX>{});
-  static const auto t1 = make_table<1>(std::make_index_sequence<EDM_K_MAX>{});
   if (nslots <= 0 || a.ntgt <= 0 || m_max <= 0) return hipSuccess;
   if (a.k < 1 || a.k > EDM_K_MAX || m_max > kLdsFloats) return hipErrorInvalidValue;
   int T = lookup_tile_targets(m_max);
-  if (a.pred && T > 4) T = 4;                 // the prediction-writing form
-  while (T > 1 && T / 2 >= a.ntgt) T >>= 1;  // no wider than the target count needs
-  const size_t shm = static_cast<size_t>(lookup_tile_floats(T, m_max)) * sizeof(float);
-  const unsigned gx = static_cast<unsigned>((a.ntgt + T - 1) / T);
-  const auto &table = T >= 16 ? t4 : (T == 8 ? t2 : t1);
+  if (a.pred && T > 4) T = 4;  // the prediction-writing form
+  const Shape s = shape_for(T, nslots, m_max, a.ntgt);
+  const unsigned gx = static_cast<unsigned>((a.ntgt + s.T - 1) / s.T);
+  const LaunchFn fn = launch_fn(a.k, s.T, s.split());
   TimedLaunch timed(EDM_KF_LOOKUP, st);
-  constexpr int kMaxY = 32768 * kWaves;
-  for (int s0 = 0; s0 < nslots; s0 += kMaxY) {
-    const int ns = nslots - s0 < kMaxY ? nslots - s0 : kMaxY;
-    const unsigned gy = static_cast<unsigned>((ns + kWaves - 1) / kWaves);
-    hipError_t e = table[a.k - 1](a, dim3(gx, gy), shm, T, ns, s0, st);
+  const int max_y = 32768 * s.libs();
+  for (int s0 = 0; s0 < nslots; s0 += max_y) {
+    const int ns = nslots - s0 < max_y ? nslots - s0 : max_y;
+    const unsigned gy = static_cast<unsigned>((ns + s.libs() - 1) / s.libs());
+    hipError_t e = fn(a, dim3(gx, gy), s.lds, s.T, ns, s0, s.lg_parts, s.ex_at, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -632,27 +730,23 @@ hipError_t launch_lookup(const LookupArgs &a, int nslots, int64_t m_max, hipStre
 
 hipError_t launch_lookup_bucket(const LookupArgs &a, int nslots, int64_t m_max, int64_t n_tgt_max,
                                 hipStream_t st) {
-  static const auto t4 = make_table<4>(std::make_index_sequence<EDM_K_MAX>{});
-  static const auto t2 = make_table<2>(std::make_index_sequence<EDM_K_MAX>{});
-  static const auto t1 = make_table<1>(std::make_index_sequence<EDM_K_MAX>{});
   if (nslots <= 0 || n_tgt_max <= 0 || m_max <= 0) return hipSuccess;
   if (a.k < 1 || a.k > EDM_K_MAX || m_max > kLdsFloats || !a.bucket_at || !a.bucket_ids || a.tbl_off ||
       a.pred)
     return hipErrorInvalidValue;
-  int T = lookup_tile_targets(m_max);
-  while (T > 1 && T / 2 >= n_tgt_max) T >>= 1;
-  const size_t shm = static_cast<size_t>(lookup_tile_floats(T, m_max)) * sizeof(float);
+  const Shape s = shape_for(lookup_tile_targets(m_max), nslots, m_max, n_tgt_max);
   // kTileCols tile columns per library group, each workgroup walking its
   // column's tiles; library groups padded to a multiple of the XCD count
   // (the kernel maps workgroups to groups XCD by XCD)
-  const auto &table = T >= 16 ? t4 : (T == 8 ? t2 : t1);
+  const LaunchFn fn = launch_fn(a.k, s.T, s.split());
   TimedLaunch timed(EDM_KF_LOOKUP, st);
-  constexpr int kMaxSlots = 65536 * kWaves;
-  for (int s0 = 0; s0 < nslots; s0 += kMaxSlots) {
-    const int ns = nslots - s0 < kMaxSlots ? nslots - s0 : kMaxSlots;
-    const int64_t groups = (ns + kWaves - 1) / kWaves;
+  const int max_slots = 65536 * s.libs();
+  for (int s0 = 0; s0 < nslots; s0 += max_slots) {
+    const int ns = nslots - s0 < max_slots ? nslots - s0 : max_slots;
+    const int64_t groups = (ns + s.libs() - 1) / s.libs();
     const int64_t padded = (groups + kXcds - 1) / kXcds * kXcds;
-    hipError_t e = table[a.k - 1](a, dim3(static_cast<unsigned>(padded * kTileCols), 1), shm, T, ns, s0, st);
+    hipError_t e = fn(a, dim3(static_cast<unsigned>(padded * kTileCols), 1), s.lds, s.T, ns, s0, s.lg_parts,
+                      s.ex_at, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

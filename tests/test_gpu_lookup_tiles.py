@@ -58,7 +58,7 @@ def test_lookup_matches_float64(edm, nq, k, N, E, tau, Tp):
 # a few libraries and many, targets shorter than some libraries (undefined
 # pairs) and than the offset, at the narrowest and widest tiles
 @pytest.mark.parametrize("Nl,Nt,L,tau,Tp", [(1, 5, 400, 1, 0), (2, 40, 700, 1, 1), (3, 7, 300, 2, 0), (5, 130, 500, 1, 0),
-                                            (9, 3, 450, 3, 1), (17, 33, 350, 1, 0), (40, 20, 200, 2, 1)])
+                                            (9, 3, 450, 3, 1), (3, 60, 1500, 1, 0), (17, 33, 350, 1, 0), (40, 20, 200, 2, 1)])
 def test_ragged_cross_maps_match_oracle(edm, Nl, Nt, L, tau, Tp):
     rng = np.random.default_rng(Nl * 100 + Nt)
     X, _, _ = synth.logistic_network(seed=2, N=max(Nl + Nt, 4), L=L)
