@@ -138,9 +138,11 @@ void edm_ctx_destroy(edm_ctx *ctx);
 enum {
   EDM_KF_EXACT_SCAN = 0,        /* k_knn: one candidate scan per (library, E)        */
   EDM_KF_BATCHED_SCAN = 1,      /* k_sweep_multi, k_tables_persistent: exact scans
-                                   of groups of E values                            */
+                                   of groups of E values; k_sweep_small's, which
+                                   timing runs as launches of their own             */
   EDM_KF_FILTER_PREP = 2,       /* k_gram_mean, k_gram_norms                         */
-  EDM_KF_FILTER_SCAN = 3,       /* k_gram, k_gram_items: matrix-core filtered scans  */
+  EDM_KF_FILTER_SCAN = 3,       /* k_gram, k_gram_items: matrix-core filtered scans;
+                                   k_sweep_small's                                  */
   EDM_KF_TABLES_FROM_SWEEP = 4, /* k_fix_from_sweep, k_scan_queries                  */
   EDM_KF_LOOKUP = 5,            /* k_lookup, k_lookup_items                          */
   EDM_KF_FINALIZE = 6,          /* k_sweep_finalize                                  */

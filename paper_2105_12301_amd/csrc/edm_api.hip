@@ -175,6 +175,8 @@ TimingScope::~TimingScope() { g_timed = prev; }
 
 }  // namespace host
 
+bool timing_on() { return host::g_timed != nullptr; }
+
 TimedLaunch::TimedLaunch(int fam, hipStream_t s) : family(fam), st(s) {
   edm_ctx *ctx = host::g_timed;
   if (!ctx) return;

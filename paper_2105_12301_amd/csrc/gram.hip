@@ -926,16 +926,16 @@ __global__ __launch_bounds__(kGramThreads) void k_gram(KnnArgs a, int slot0, int
 // they run side by side instead of one after the other on a mostly idle chip.
 // The exact E 1-4 scan splits each query's candidates over two waves.  The
 // longest groups start first.
-constexpr int kSmallZ = 7;
-__global__ __launch_bounds__(kGramThreads) void k_sweep_small(KnnArgs a) {
+constexpr int kSmallZ = 7, kSmallExactZ = 4;
+__global__ __launch_bounds__(kGramThreads) void k_sweep_small(KnnArgs a, int z0) {
   extern __shared__ __attribute__((aligned(16))) float gram_smem[];
   const int row = static_cast<int>(blockIdx.y), bx = static_cast<int>(blockIdx.x);
-  switch (blockIdx.z) {
+  switch (z0 + static_cast<int>(blockIdx.z)) {
     case 0: gram_scan<14, 16, false>(a, row, bx, gram_smem); break;
     case 1: gram_scan<19, 20, false>(a, row, bx, gram_smem); break;
     case 2: gram_scan<5, 8, false>(a, row, bx, gram_smem); break;
     case 3: gram_scan<17, 18, false>(a, row, bx, gram_smem); break;
-    case 4: group_scan<1, 4, 4, 2>(a, row, bx, gram_smem); break;
+    case kSmallExactZ: group_scan<1, 4, 4, 2>(a, row, bx, gram_smem); break;
     case 5: gram_scan<9, 11, false>(a, row, bx, gram_smem); break;
     default: gram_scan<12, 13, false>(a, row, bx, gram_smem); break;
   }
@@ -1069,10 +1069,19 @@ hipError_t launch_gram_small(const KnnArgs &a, int nslots, int64_t L_max, hipStr
                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
     if (e != hipSuccess) return e;
   }
-  TimedLaunch timed(EDM_KF_FILTER_SCAN, st);
   const unsigned gx = static_cast<unsigned>((L_max + kKnnThreads - 1) / kKnnThreads);
-  hipLaunchKernelGGL(k_sweep_small, dim3(gx, static_cast<unsigned>(nslots), kSmallZ), dim3(kGramThreads), shm, st, b);
-  return hipGetLastError();
+  auto launch = [&](int family, int z0, int z1) {
+    TimedLaunch timed(family, st);
+    hipLaunchKernelGGL(k_sweep_small, dim3(gx, static_cast<unsigned>(nslots), static_cast<unsigned>(z1 - z0)),
+                       dim3(kGramThreads), shm, st, b, z0);
+    return hipGetLastError();
+  };
+  if (!timing_on()) return launch(EDM_KF_FILTER_SCAN, 0, kSmallZ);
+  // timed: a launch per kernel family
+  hipError_t e = launch(EDM_KF_FILTER_SCAN, 0, kSmallExactZ);
+  if (e == hipSuccess) e = launch(EDM_KF_BATCHED_SCAN, kSmallExactZ, kSmallExactZ + 1);
+  if (e == hipSuccess) e = launch(EDM_KF_FILTER_SCAN, kSmallExactZ + 1, kSmallZ);
+  return e;
 }
 
 hipError_t launch_gram_prep(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {

@@ -24,6 +24,9 @@ struct TimedLaunch {
   hipEvent_t start = nullptr;
 };
 
+// The calling thread is inside a TimingScope of a context with timing on.
+bool timing_on();
+
 constexpr int kKnnThreads = 256;  // 4 waves of 64 query points per workgroup
 
 // Arguments of the fused embedding + distance + top-k + weights kernel.
