@@ -143,8 +143,8 @@ enum {
   EDM_KF_FILTER_PREP = 2,       /* k_gram_mean, k_gram_norms                         */
   EDM_KF_FILTER_SCAN = 3,       /* k_gram, k_gram_items: matrix-core filtered scans;
                                    k_sweep_small's                                  */
-  EDM_KF_TABLES_FROM_SWEEP = 4, /* k_fix_from_sweep, k_scan_queries                  */
-  EDM_KF_LOOKUP = 5,            /* k_lookup, k_lookup_items                          */
+  EDM_KF_TABLES_FROM_SWEEP = 4, /* k_fix_from_sweep, k_scan_queries, k_tables_all    */
+  EDM_KF_LOOKUP = 5,            /* k_lookup, k_lookup_items, k_lookup_all            */
   EDM_KF_FINALIZE = 6,          /* k_sweep_finalize                                  */
   EDM_KF_OTHER = 7,             /* fills, embedding, candidate sets, network         */
   EDM_KF_DISTANCES = 8,         /* two-kernel form: distance matrix (Algorithm 1)    */

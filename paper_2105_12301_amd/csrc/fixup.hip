@@ -53,10 +53,9 @@ __device__ __forceinline__ void stage(const KnnArgs &a, int row, int L, float *x
 // key is recomputed, m1 is inserted and the row is rewritten (the kept
 // entries are read before).
 template <int E>
-__global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
+__device__ __forceinline__ void fix_block(const KnnArgs &a, int row, int (&queue)[256], int &n_queue) {
   constexpr int K = E + 1;
   if (a.group_at && a.group_at[E + 1] == a.group_at[E]) return;  // no target of this E
-  const int row = slot0 + static_cast<int>(blockIdx.y);
   const int L = static_cast<int>(a.L_dev ? a.L_dev[row] : a.L_uni);
   const int m1 = L - E;
   if (m1 - 1 < K) return;  // no sweep list: k_scan_queries covers this series
@@ -73,8 +72,6 @@ __global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
   };
   // Queries where m1 enters the list (about 1 in 100) are queued in LDS and
   // rewritten by consecutive threads, so the slow path runs on few waves.
-  __shared__ int queue[256];
-  __shared__ int n_queue;
   if (threadIdx.x == 0) n_queue = 0;
   __syncthreads();
   const int p = static_cast<int>(blockIdx.x) * 256 + static_cast<int>(threadIdx.x);
@@ -116,8 +113,15 @@ __global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
     int qi[K];
 #pragma unroll
     for (int r = 0; r < K; ++r) qi[r] = r < pos ? kp[r] : (r == pos ? m1 : kp[r - 1 < 0 ? 0 : r - 1]);
-    finish_list<E, E>(a, row, pq, L, 0, a.need, vp, qi, x);
+    finish_list<E, E>(a, row, pq, L, 0, 1u << (E - 1), vp, qi, x);
   }
+}
+
+template <int E>
+__global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
+  __shared__ int queue[256];
+  __shared__ int n_queue;
+  fix_block<E>(a, slot0 + static_cast<int>(blockIdx.y), queue, n_queue);
 }
 
 // Full scans, one query per wave: the lanes walk the candidates in ascending
@@ -126,11 +130,9 @@ __global__ __launch_bounds__(256) void k_fix_from_sweep(KnnArgs a, int slot0) {
 // index).  Query m1 of every series, or every query of a series whose sweep
 // had no list at E.
 template <int E>
-__global__ __launch_bounds__(256) void k_scan_queries(KnnArgs a, int slot0) {
+__device__ __forceinline__ void scan_block(const KnnArgs &a, int row, float *fx_xs) {
   constexpr int K = E + 1;
-  extern __shared__ float fx_xs[];
   if (a.group_at && a.group_at[E + 1] == a.group_at[E]) return;  // no target of this E
-  const int row = slot0 + static_cast<int>(blockIdx.y);
   const int L = static_cast<int>(a.L_dev ? a.L_dev[row] : a.L_uni);
   const int m0 = L - (E - 1), m1 = m0 - 1;
   if (m0 - 1 < K) return;  // the cross map is undefined at E for this library
@@ -163,9 +165,35 @@ __global__ __launch_bounds__(256) void k_scan_queries(KnnArgs a, int slot0) {
       float vp[E];
 #pragma unroll
       for (int j = 0; j < E; ++j) vp[j] = fx_xs[p + j];
-      finish_list<E, E>(a, row, p, L, 0, a.need, vp, ri, fx_xs);
+      finish_list<E, E>(a, row, p, L, 0, 1u << (E - 1), vp, ri, fx_xs);
     }
   }
+}
+
+template <int E>
+__global__ __launch_bounds__(256) void k_scan_queries(KnnArgs a, int slot0) {
+  extern __shared__ float fx_xs[];
+  scan_block<E>(a, slot0 + static_cast<int>(blockIdx.y), fx_xs);
+}
+
+// Both for every E at once (blockIdx.z): few series, where each of the 2 E_max
+// launches would take a few microseconds and find most buckets empty.  The two
+// write different rows and read only the series and the sweep's lists.
+template <int... I>
+__device__ __forceinline__ void tables_block(const KnnArgs &a, int E, float *xs, int (&queue)[256], int &n_queue,
+                                             std::integer_sequence<int, I...>) {
+  const int row = static_cast<int>(blockIdx.y);
+  if (blockIdx.x + 1 < gridDim.x)
+    ((E == I + 1 ? fix_block<I + 1>(a, row, queue, n_queue) : void()), ...);
+  else
+    ((E == I + 1 ? scan_block<I + 1>(a, row, xs) : void()), ...);
+}
+__global__ __launch_bounds__(256) void k_tables_all(KnnArgs a) {
+  extern __shared__ float fx_xs[];
+  __shared__ int queue[256];
+  __shared__ int n_queue;
+  tables_block(a, static_cast<int>(blockIdx.z) + 1, fx_xs, queue, n_queue,
+               std::make_integer_sequence<int, EDM_E_MAX>{});
 }
 
 using FixFn = hipError_t (*)(const KnnArgs &, int, int64_t, hipStream_t);
@@ -198,6 +226,22 @@ constexpr std::array<FixFn, EDM_E_MAX> fix_table(std::index_sequence<I...>) {
 }
 
 }  // namespace
+
+hipError_t launch_tables_from_sweep_all(const KnnArgs &a, int E_max, int nslots, int64_t L_max, hipStream_t st) {
+  if (E_max < 1 || E_max > EDM_E_MAX || nslots > 65535 || a.tau != 1 || a.mom != nullptr) return hipErrorInvalidValue;
+  if (nslots <= 0) return hipSuccess;
+  const size_t shm = static_cast<size_t>(L_max) * sizeof(float);
+  if (shm > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_tables_all),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
+    if (e != hipSuccess) return e;
+  }
+  TimedLaunch timed(EDM_KF_TABLES_FROM_SWEEP, st);
+  const dim3 grid(static_cast<unsigned>((L_max + 255) / 256 + 1), static_cast<unsigned>(nslots),
+                  static_cast<unsigned>(E_max));
+  hipLaunchKernelGGL(k_tables_all, grid, dim3(256), shm, st, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_tables_from_sweep(const KnnArgs &a, int E, int nslots, int64_t L_max,
                                     hipStream_t st) {

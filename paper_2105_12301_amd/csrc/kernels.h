@@ -152,6 +152,8 @@ hipError_t launch_gram_items(const KnnArgs &a, int g, const TableItem *items, in
 // a.strideE[E], as the batched table mode writes them.
 hipError_t launch_tables_from_sweep(const KnnArgs &a, int E, int nslots, int64_t L_max,
                                     hipStream_t st);
+// ... for E = 1 .. E_max in one launch (idxE, wE, strideE and keep* of every E set).
+hipError_t launch_tables_from_sweep_all(const KnnArgs &a, int E_max, int nslots, int64_t L_max, hipStream_t st);
 
 // Launch the kNN kernel for `nslots` libraries whose longest series has
 // `L_max` samples.  Returns a hipError_t.
@@ -220,6 +222,18 @@ struct LookupArgs {
   // bucket_at set): the targets are bucket_ids[bucket_at[E] ..
   // bucket_at[E+1]) and ntgt is ignored.
 };
+
+// The grid kernel for E = 1 .. E_max in one launch, buckets on the device:
+// a's fields but idx, w, tbl_stride, E and k, and the tables by E.
+struct LookupAllArgs {
+  LookupArgs a;
+  const int32_t *idxE[EDM_E_MAX + 1];
+  const float *wE[EDM_E_MAX + 1];
+  int64_t strideE[EDM_E_MAX + 1];
+};
+bool lookup_all_fits(int nslots, int64_t m_max, int64_t n_tgt_max);
+hipError_t launch_lookup_all(const LookupAllArgs &all, int E_max, int nslots, int64_t m_max, int64_t n_tgt_max,
+                             hipStream_t st);
 
 // Lookups of the work list of one E: persistent (wg_per_cu * n_cu
 // workgroups pulling items from *counter) or one workgroup per item

@@ -448,13 +448,10 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
 // ms bounds every staged window (the dynamic LDS holds T * ms floats, and the
 // split form's exchange area from ex_at on).  kSplit: 1 << lg_parts waves walk
 // one library.
-template <int K, int TPL, bool kSplit>
-__global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int nslots, int slot0, int lg_parts,
-                                                     int ex_at) {
-  extern __shared__ float4 lds4[];
-  float *vs = reinterpret_cast<float *>(lds4);
-  __shared__ float cs[kLookupItemMaxTargets];
-  __shared__ int tgt[kLookupItemMaxTargets];
+// kAll: one launch for every E (blockIdx.z).
+template <int K, int TPL, bool kSplit, bool kAll>
+__device__ __forceinline__ void lookup_block(const LookupArgs &a, int T, int nslots, int slot0, int lg_parts,
+                                             int ex_at, float *vs, float *cs, int *tgt) {
   const int off = (a.E - 1) * a.tau + a.Tp;
   // targets of the launch: the host's list, or the bucket grouped on the device
   const bool dev = a.bucket_at != nullptr && a.tbl_off == nullptr;
@@ -467,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
   // its L2.
   int col = static_cast<int>(blockIdx.x), ncol = static_cast<int>(gridDim.x);
   int grp = static_cast<int>(blockIdx.y);
-  if (dev) {
+  if (dev && !kAll) {
     const int i = static_cast<int>(blockIdx.x), k = i / kXcds;
     col = k % kTileCols;
     ncol = kTileCols;
@@ -526,6 +523,37 @@ __global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int ns
     if (tile * T >= ntgt) break;
     load.load(a, tile_at(tile), off, n_blk);
   }
+}
+
+template <int K, int TPL, bool kSplit>
+__global__ __launch_bounds__(kThreads) void k_lookup(LookupArgs a, int T, int nslots, int slot0, int lg_parts,
+                                                     int ex_at) {
+  extern __shared__ float4 lds4[];
+  __shared__ float cs[kLookupItemMaxTargets];
+  __shared__ int tgt[kLookupItemMaxTargets];
+  lookup_block<K, TPL, kSplit, false>(a, T, nslots, slot0, lg_parts, ex_at, reinterpret_cast<float *>(lds4), cs, tgt);
+}
+
+// The split form for every E at once (blockIdx.z = E - 1), buckets on the
+// device: few series, where E_max launches of a few microseconds would find
+// most buckets empty.
+__global__ __launch_bounds__(kThreads) void k_lookup_all(LookupAllArgs all, int T, int nslots, int lg_parts,
+                                                         int ex_at) {
+  extern __shared__ float4 lds4[];
+  __shared__ float cs[kLookupItemMaxTargets];
+  __shared__ int tgt[kLookupItemMaxTargets];
+  const int E = static_cast<int>(blockIdx.z) + 1;
+  each<1, EDM_E_MAX + 1>([&](auto EC) {
+    constexpr int e = decltype(EC)::value;
+    if (E != e) return;
+    LookupArgs a = all.a;
+    a.E = e;
+    a.k = e + 1;
+    a.idx = all.idxE[e];
+    a.w = all.wE[e];
+    a.tbl_stride = all.strideE[e];
+    lookup_block<e + 1, 1, true, true>(a, T, nslots, 0, lg_parts, ex_at, reinterpret_cast<float *>(lds4), cs, tgt);
+  });
 }
 
 // Work-list kernel for one E (K = E + 1): persistent (counter != nullptr:
@@ -688,6 +716,10 @@ Shape shape_for(int T, int nslots, int64_t m_max, int64_t ntgt) {
   return best;
 }
 
+// Workgroups of one E up to which the E go into one launch: a round of the
+// chip, so that a launch of its own would not fill it.
+constexpr int64_t kAllBlocks = kCus;
+
 }  // namespace
 
 hipError_t launch_target_means(const float *Y, int64_t ldy, const int64_t *Ly_dev, int64_t L_uni,
@@ -750,6 +782,30 @@ hipError_t launch_lookup_bucket(const LookupArgs &a, int nslots, int64_t m_max, 
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+bool lookup_all_fits(int nslots, int64_t m_max, int64_t n_tgt_max) {
+  if (nslots <= 0 || nslots > 65535 || m_max <= 0 || m_max > kLdsFloats || n_tgt_max <= 0) return false;
+  const Shape s = shape_for(lookup_tile_targets(m_max), nslots, m_max, n_tgt_max);
+  return s.split() && (nslots + s.libs() - 1) / s.libs() * ((n_tgt_max + s.T - 1) / s.T) <= kAllBlocks;
+}
+
+hipError_t launch_lookup_all(const LookupAllArgs &all, int E_max, int nslots, int64_t m_max, int64_t n_tgt_max,
+                             hipStream_t st) {
+  if (!lookup_all_fits(nslots, m_max, n_tgt_max) || E_max < 1 || E_max > EDM_E_MAX || !all.a.bucket_at ||
+      !all.a.bucket_ids || all.a.tbl_off || all.a.pred)
+    return hipErrorInvalidValue;
+  const Shape s = shape_for(lookup_tile_targets(m_max), nslots, m_max, n_tgt_max);
+  if (s.lds > 65536) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_lookup_all),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(s.lds));
+    if (e != hipSuccess) return e;
+  }
+  TimedLaunch timed(EDM_KF_LOOKUP, st);
+  const dim3 grid(static_cast<unsigned>((n_tgt_max + s.T - 1) / s.T),
+                  static_cast<unsigned>((nslots + s.libs() - 1) / s.libs()), static_cast<unsigned>(E_max));
+  hipLaunchKernelGGL(k_lookup_all, grid, dim3(kThreads), s.lds, st, all, s.T, nslots, s.lg_parts, s.ex_at);
+  return hipGetLastError();
 }
 
 hipError_t launch_lookup_items(const LookupArgs &a, int E, const LookupItem *items, int n_items,
