@@ -28,7 +28,8 @@
 // * Improving candidates are queued in LDS and inserted in batches
 //   (topk_list.h).  What bounds the scan is VALU issue: 3 E + ~20 instructions a
 //   step (10000 x 2000, E = 20: 54 ms against 31 ms for its 61 operations a
-//   pair at one a lane and clock; E = 1..20 together about 1100 -> 595 ms).
+//   pair at one a lane and clock; the sweep over
+//   E = 1..20, epilogues included, 668 -> 595 ms against insertion as they come).
 // * Few workgroups (one series): the candidates of a query are split over 4 or
 //   16 waves whose lists are merged (one series of 1000, E = 3: 86 -> 15 us;
 //   10000 samples, E = 20: 560 us through the filter -> 277 us).

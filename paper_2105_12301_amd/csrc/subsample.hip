@@ -16,7 +16,7 @@
 //   work is O(queries x members x E) instead of a scan of every point.
 // * The key is the float32 sum of Algorithm 1 (lags ascending, one rounding
 //   per operation, this file compiled without contraction), the register
-//   list and its ballot-gated insertion are the fused scan's, and the
+//   list and its queued insertion are the fused scan's, and the
 //   float64 epilogue follows the same order, so a subsample holding every
 //   point gives the fused scan's table bit for bit.
 #include <array>

@@ -14,7 +14,8 @@
 // LDS, one query per lane, diagonal candidate order (lane l sees q = s + l), a
 // sliding window of samples in registers, improving candidates queued in LDS
 // and inserted in batches (10000 x 2000, Tp = 1: E 1-4 27.2 -> 22.1 ms, all
-// five groups 890 -> 391 ms against insertion as they come), float64 weights of the winners, the self-prediction and its Pearson
+// five groups 453 -> 388 ms against insertion as they come), float64 weights of
+// the winners, the self-prediction and its Pearson
 // co-moments reduced per block.  tau = 1 only (the sweep's lag); other lags
 // use the per-E kernel.
 #include <array>
