@@ -377,6 +377,7 @@ int edm_knn(edm_ctx *ctx, const float *x, int64_t L, int32_t E, int32_t tau, int
   std::string msg;
   const int rc = edm::check_knn(x, L, E, tau, Tp, k, idx, msg);
   if (rc != EDM_OK) return set_err(ctx, rc, msg);
+  edm::bound_lags(tau, Tp);
   EDM_RC(check_ctx(ctx));
   if (edm::n_query(L, E, tau, Tp) - 1 - 2 * static_cast<int64_t>(ctx->excl) < (k ? k : E + 1))
     return set_err(ctx, EDM_E_SHORT, "series too short for k neighbours outside the exclusion radius");
@@ -475,6 +476,7 @@ int edm_simplex_sweep(edm_ctx *ctx, const float *X, const int64_t *L, int64_t N,
   std::string msg;
   const int rc = edm::check_sweep(X, L, N, ldx, E_max, tau, Tp, rho, E_opt, msg);
   if (rc != EDM_OK) return set_err(ctx, rc, msg);
+  edm::bound_lags(tau, Tp);
   EDM_RC(check_ctx(ctx));
   if (N == 0) return EDM_OK;
   if (N > INT32_MAX) return set_err(ctx, EDM_E_ARG, "too many series");
@@ -670,6 +672,7 @@ int edm_ccm(edm_ctx *ctx, const float *X, const int64_t *Lx, int64_t Nl, int64_t
   std::string msg;
   const int rc = edm::check_ccm(X, Lx, Nl, ldx, Y, Ly, Nt, ldy, E_tgt, tau, Tp, rho, msg);
   if (rc != EDM_OK) return set_err(ctx, rc, msg);
+  edm::bound_lags(tau, Tp);
   EDM_RC(check_ctx(ctx));
   if (Nl == 0 || Nt == 0) return EDM_OK;
   if (Nl > INT32_MAX || Nt > INT32_MAX) return set_err(ctx, EDM_E_ARG, "too many series");
@@ -1030,6 +1033,7 @@ int edm_select_E(edm_ctx *ctx, const float *X, const int64_t *L, int64_t N, int6
   std::string msg;
   const int rc = edm::check_sweep(X, L, N, ldx, E_max, tau, Tp, rho, E_opt, msg);
   if (rc != EDM_OK) return set_err(ctx, rc, msg);
+  edm::bound_lags(tau, Tp);
   if (N > 0 && !logits) return set_err(ctx, EDM_E_ARG, "NULL logits");
   if (m_top < 1 || m_top > EDM_NET_CLASSES) return set_err(ctx, EDM_E_ARG, "m_top must be in 1..20");
   if (!(min_conf >= 0.0f && min_conf <= 1.0f)) return set_err(ctx, EDM_E_ARG, "min_conf must be in [0, 1]");

@@ -1,4 +1,4 @@
-// All-kNN scans with lag 1 (knn_kernel.h) and the dispatch over lags.
+// All-kNN scans with lag 1 or E = 1 (knn_kernel.h) and the dispatch over lags.
 #include <array>
 #include <utility>
 
@@ -25,7 +25,8 @@ hipError_t launch_knn(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t s
   KnnArgs b = a;
   b.lds_x = scan_floats(L_max);
   TimedLaunch timed(EDM_KF_EXACT_SCAN, st);
-  if (a.tau == 1 && a.k == a.E + 1 && a.E >= 1 && a.E <= EDM_E_MAX) return fast[a.E - 1](b, nslots, L_max, st);
+  // (E = 1 has no lag, and every lag is allowed with it: never a lagged scan)
+  if ((a.tau == 1 || a.E == 1) && a.k == a.E + 1 && a.E >= 1 && a.E <= EDM_E_MAX) return fast[a.E - 1](b, nslots, L_max, st);
   return launch_knn_lagged(b, nslots, L_max, st);
 }
 

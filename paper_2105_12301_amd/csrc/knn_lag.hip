@@ -20,7 +20,7 @@ hipError_t launch_generic(const KnnArgs &a, int nslots, int64_t L_max, hipStream
 template <size_t... I>
 constexpr auto make_lagged(std::index_sequence<I...>) {
   return std::array<LaunchFn, sizeof...(I)>{
-      &launch_layout<static_cast<int>(I) + 1, static_cast<int>(I) + 2, false>...};
+      &launch_layout<static_cast<int>(I) + 2, static_cast<int>(I) + 3, false>...};  // from E = 2
 }
 template <size_t... I>
 constexpr auto make_generic(std::index_sequence<I...>) {
@@ -30,10 +30,10 @@ constexpr auto make_generic(std::index_sequence<I...>) {
 }  // namespace
 
 hipError_t launch_knn_lagged(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
-  static const auto lagged = make_lagged(std::make_index_sequence<EDM_E_MAX>{});
+  static const auto lagged = make_lagged(std::make_index_sequence<EDM_E_MAX - 1>{});
   static const auto generic = make_generic(std::make_index_sequence<EDM_K_MAX>{});
-  const bool fast = a.k == a.E + 1 && a.E >= 1 && a.E <= EDM_E_MAX;
-  return fast ? lagged[a.E - 1](a, nslots, L_max, st) : generic[a.k - 1](a, nslots, L_max, st);
+  const bool fast = a.k == a.E + 1 && a.E >= 2 && a.E <= EDM_E_MAX;
+  return fast ? lagged[a.E - 2](a, nslots, L_max, st) : generic[a.k - 1](a, nslots, L_max, st);
 }
 
 }  // namespace edm

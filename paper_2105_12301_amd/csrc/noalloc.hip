@@ -68,6 +68,7 @@ extern "C" int edm_simplex_sweep_noalloc(edm_ctx *ctx, const float *X, const int
   std::string msg;
   const int rc = edm::check_sweep(X, L, N, ldx, E_max, tau, Tp, rho, E_opt, msg);
   if (rc != EDM_OK) return set_err(ctx, rc, msg);
+  edm::bound_lags(tau, Tp);
   EDM_RC(check_ctx(ctx));
   if (N == 0) return EDM_OK;
   if (N > INT32_MAX) return set_err(ctx, EDM_E_ARG, "too many series");

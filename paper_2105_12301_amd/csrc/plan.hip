@@ -22,6 +22,7 @@
 #include "../../include/edm.h"
 #include "ctx.h"
 #include "kernels.h"
+#include "validate.h"
 
 using namespace edm::host;
 
@@ -122,6 +123,8 @@ int edm_ccm_plan_create(edm_ctx *ctx, const int64_t *Lx, int64_t Nl, int64_t ldx
   if (Nl < 1 || Nt < 1 || !Lx || !Ly || !E_tgt) return set_err(ctx, EDM_E_ARG, "need Nl, Nt >= 1 and host Lx, Ly, E_tgt");
   if (Nl > INT32_MAX || Nt > INT32_MAX) return set_err(ctx, EDM_E_ARG, "too many series");
   if (Tp < 0) return set_err(ctx, EDM_E_ARG, "Tp must be >= 0");
+  int32_t lag = 1;
+  edm::bound_lags(lag, Tp);
   for (int64_t i = 0; i < Nl; ++i)
     if (Lx[i] < 1 || Lx[i] > ldx || Lx[i] > EDM_L_MAX) return set_err(ctx, EDM_E_ARG, "library length outside 1..min(ldx, EDM_L_MAX)");
   for (int64_t j = 0; j < Nt; ++j) {

@@ -17,6 +17,14 @@ inline int64_t n_query(int64_t L, int32_t E, int32_t tau, int32_t Tp) {
   return L - static_cast<int64_t>(E - 1) * tau - Tp;
 }
 
+// Kernels multiply lags and horizons in 32 bits.  A lag or horizon of the
+// longest series or more is as good as any larger one: with such a lag only
+// E = 1 (which has none) is feasible, with such a horizon nothing is.
+inline void bound_lags(int32_t &tau, int32_t &Tp) {
+  if (tau > EDM_L_MAX) tau = EDM_L_MAX;
+  if (Tp > EDM_L_MAX) Tp = EDM_L_MAX;
+}
+
 inline int fail(std::string &msg, int code, const std::string &why) {
   msg = why;
   return code;
