@@ -33,15 +33,54 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxC = EDM_NET_C_MAX;
 __host__ __device__ constexpr int pad32(int C) { return (C + 31) / 32 * 32; }
+// Blocks of 8 input channels that the products of a C -> C layer run over, and
+// the channels that a workgroup's threads are dealt out over (a power of two).
+__host__ __device__ constexpr int blocks8(int C) { return (C + 7) / 8; }
+__host__ __device__ constexpr int lg_lanes(int C) { return C <= 8 ? 3 : (C <= 16 ? 4 : (C <= 32 ? 5 : 6)); }
+
+// The contraction of a C -> C layer runs over e = 7 ci + k in ascending order
+// (channels, then taps), two at a time: v_mfma_f32_32x32x2_f32 adds its two
+// products one after the other with a rounding each, as two fused
+// multiply-adds, so every output is the same chain of fused multiply-adds that a
+// vector kernel walking the channels and taps in order computes.
+//
+// Weights in fragment order: element q of wf[u][cot][lane] (float4) holds
+// A[co = 32 cot + lane % 32][e = 2 (4 u + q) + lane / 32], A[co][7 ci + k] =
+// w[co][ci][k], or with `flip` w[ci][co][KW - 1 - k]; zero outside C.  Matrices
+// of a pass: layers 2 and 3, then (a training pass) layers 3 and 2 flipped.
+__host__ __device__ constexpr int frag_floats(int C) { return KW * 8 * blocks8(C) * pad32(C); }
+__device__ __forceinline__ void weight_frag(const float *__restrict__ w2, const float *__restrict__ w3, int C, int el,
+                                            float *__restrict__ wf) {
+  const int n_cot = pad32(C) / 32;
+  const int at = el / frag_floats(C), i = el - at * frag_floats(C);
+  const bool flip = at >= 2;
+  const float *__restrict__ w = at == 0 || at == 3 ? w2 : w3;
+  const int q = i & 3, lane = (i >> 2) & 63, cot = (i >> 8) % n_cot, u = (i >> 8) / n_cot;
+  const int e = 2 * (4 * u + q) + (lane >> 5);
+  const int co = 32 * cot + (lane & 31), ci = e / KW, k = e % KW;
+  float v = 0.0f;
+  if (co < C && ci < C) v = flip ? w[(ci * C + co) * KW + (KW - 1 - k)] : w[(co * C + ci) * KW + k];
+  wf[el] = v;
+}
 
 // Layer 1: y[b][t][c] = relu(sum_k w[c][k] x[b][t + k - HALO] + bias[c]).
 // Bound by its output's HBM writes; a thread holds its channel's weights.
+// Workgroup i: time tile i % tiles of series i / tiles, and from B * tiles on
+// 256 of the layers' weights in fragment order (a launch of their own was
+// 5 of 34 us where one short series passes a small network).
 constexpr int T1 = 128;  // time steps per workgroup
-__global__ __launch_bounds__(256) void k_conv1(const float *__restrict__ x, int64_t ldx, int C, int L,
+__global__ __launch_bounds__(256) void k_conv1(const float *__restrict__ x, int64_t ldx, int B, int C, int L,
                                                const float *__restrict__ w, const float *__restrict__ bias,
-                                               float *__restrict__ y) {
+                                               float *__restrict__ y, const float *__restrict__ w2,
+                                               const float *__restrict__ w3, float *__restrict__ wf) {
   __shared__ float xs[T1 + KW - 1];
-  const int b = blockIdx.y, t0 = blockIdx.x * T1, tid = threadIdx.x;
+  const int tid = threadIdx.x, tiles = (L + T1 - 1) / T1;
+  const int64_t wg = static_cast<int64_t>(blockIdx.x);
+  if (wg >= static_cast<int64_t>(B) * tiles) {
+    weight_frag(w2, w3, C, static_cast<int>(wg - static_cast<int64_t>(B) * tiles) * 256 + tid, wf);
+    return;
+  }
+  const int b = static_cast<int>(wg / tiles), t0 = static_cast<int>(wg % tiles) * T1;
   for (int i = tid; i < T1 + KW - 1; i += 256) {
     const int t = t0 + i - HALO;
     xs[i] = t >= 0 && t < L ? x[static_cast<int64_t>(b) * ldx + t] : 0.0f;
@@ -64,27 +103,6 @@ __global__ __launch_bounds__(256) void k_conv1(const float *__restrict__ x, int6
   }
 }
 
-// The contraction of a C -> C layer runs over e = 7 ci + k in ascending order
-// (channels, then taps), two at a time: v_mfma_f32_32x32x2_f32 adds its two
-// products one after the other with a rounding each, as two fused
-// multiply-adds, so every output is the same chain of fused multiply-adds that a
-// vector kernel walking the channels and taps in order computes.
-//
-// Weights in fragment order: element q of wf[u][cot][lane] (float4) holds
-// A[co = 32 cot + lane % 32][e = 2 (4 u + q) + lane / 32], A[co][7 ci + k] =
-// w[co][ci][k], or with `flip` w[ci][co][KW - 1 - k]; zero outside C.
-__global__ void k_weight_frags(const float *__restrict__ w, int C, int flip, float *__restrict__ wf) {
-  const int CP = pad32(C), n_cot = CP / 32;
-  const int i = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= KW * CP * CP) return;
-  const int q = i & 3, lane = (i >> 2) & 63, cot = (i >> 8) % n_cot, u = (i >> 8) / n_cot;
-  const int e = 2 * (4 * u + q) + (lane >> 5);
-  const int co = 32 * cot + (lane & 31), ci = e / KW, k = e % KW;
-  float v = 0.0f;
-  if (co < C && ci < C) v = flip ? w[(ci * C + co) * KW + (KW - 1 - k)] : w[(co * C + ci) * KW + k];
-  wf[i] = v;
-}
-
 // C -> C convolution over time, x, y [B][L][C]:
 //   kBack = false: y = relu(conv(x) + bias)
 //   kBack = true:  y = conv(x) where aprev > 0, else 0
@@ -97,7 +115,8 @@ __global__ void k_weight_frags(const float *__restrict__ w, int C, int flip, flo
 // word per time tile and a quarter of a 16-byte load per channel tile (weights
 // from L2, one block of 8 channels ahead) feed 2 x 2 products of 64 cycles, so
 // the matrix cores bound it: 22 GFLOP at C = 64, 256 x 1500, whose vector form
-// took 0.45-0.49 ms.
+// took 0.45-0.49 ms.  Only the blocks of 8 that hold input channels are staged
+// and multiplied (products of zeros change no bit).
 constexpr int CR = 256;
 template <int NCO, bool kBack, bool kMask>
 __global__ __launch_bounds__(256, 2) void k_conv_f32(const float *__restrict__ x, const float *__restrict__ chan, int C,
@@ -111,14 +130,16 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(const float *__restrict__ x
   // Staging: a thread's channel is fixed; eight clamped loads are in flight at
   // once, and what lies outside the series or the channels becomes zero after.
   {
-    constexpr int RP = 256 / CP;  // rows per round of the workgroup
-    constexpr int kRows = CR + KW - 1, kBatch = 8;
-    const int c = tid % CP;
+    constexpr int kBatch = 8;
+    // rows that some lane of a working wave uses: its 64 time steps and the halo
+    const int rows = (L - t0 < CR ? (L - t0 + 63) / 64 * 64 : CR) + KW - 1;
+    const int lgc = lg_lanes(C), RP = 256 >> lgc;  // rows per round of the workgroup
+    const int c = tid & ((1 << lgc) - 1);
     const bool has = c < C;
     const float *xc = xb + (has ? c : 0);
     const float ch = kMask && has ? chan[b * C + c] : 0.0f;
 #pragma unroll 1
-    for (int r0 = tid / CP; r0 < kRows; r0 += RP * kBatch) {
+    for (int r0 = tid >> lgc; r0 < rows; r0 += RP * kBatch) {
       float v[kBatch];
 #pragma unroll
       for (int i = 0; i < kBatch; ++i) {
@@ -130,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(const float *__restrict__ x
         const int r = r0 + RP * i, t = t0 + r - HALO;
         float w = v[i];
         if constexpr (kMask) w = w > 0.0f ? ch : 0.0f;
-        if (r < kRows) conv_lds[r * XS + c] = has && t >= 0 && t < L ? w : 0.0f;
+        if (r < rows) conv_lds[r * XS + c] = has && t >= 0 && t < L ? w : 0.0f;
       }
     }
   }
@@ -157,8 +178,8 @@ __global__ __launch_bounds__(256, 2) void k_conv_f32(const float *__restrict__ x
 #pragma unroll
     for (int c = 0; c < NCO; ++c) av[u][c] = wl[(u * NCO + c) * 64];
 #pragma unroll 1
-  for (int blk = 0; blk < CP / 8; ++blk) {
-    const int nb = blk + 1 < CP / 8 ? blk + 1 : blk;
+  for (int blk = 0, n_blk = blocks8(C); blk < n_blk; ++blk) {
+    const int nb = blk + 1 < n_blk ? blk + 1 : blk;
     f32x4_t an[kQ][NCO];
 #pragma unroll
     for (int u = 0; u < kQ; ++u)
@@ -286,7 +307,7 @@ __global__ void k_w_to_bf16(const float *__restrict__ w2, const float *__restric
 
 // Sums over time of layer 3: part[b][split][C], split = blockIdx.x of gridDim.x.
 template <int C>
-__global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, int64_t ldx, int L,
+__global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *__restrict__ X, int64_t ldx, int L,
                                                    const float *__restrict__ w1, const float *__restrict__ b1,
                                                    const float *__restrict__ b2, const float *__restrict__ b3,
                                                    const u32x4_t *__restrict__ wb, int tiles,
@@ -296,7 +317,8 @@ __global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, i
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_bf16[];
   uint16_t *a1 = lds_bf16, *a2 = lds_bf16 + I::kA2, *ws = lds_bf16 + I::kW;
   float *xin = reinterpret_cast<float *>(lds_bf16 + I::kX);
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float *x = X + static_cast<int64_t>(blockIdx.y) * ldx;
 
   u32x4_t pf[I::NPF];
@@ -308,12 +330,13 @@ __global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, i
 #pragma unroll
     for (int i = 0; i < I::NPF; ++i) reinterpret_cast<u32x4_t *>(ws)[tid + IT * i] = pf[i];
   };
-  // layer 1: a thread's 8 channels c0.. at times tid / (C/8) + ...
-  constexpr int CG = C / 8;
-  const int c0 = (tid % CG) * 8;
-  float w1r[8][KW], b1r[8];
+  // layer 1: a thread's CH channels c0.. at times tid / CG + ... (C = 32: four,
+  // so that two workgroups share a CU in 128 registers without spills)
+  constexpr int CH = C == 32 ? 4 : 8, CG = C / CH;
+  const int c0 = (tid % CG) * CH;
+  float w1r[CH][KW], b1r[CH];
 #pragma unroll
-  for (int c = 0; c < 8; ++c) {
+  for (int c = 0; c < CH; ++c) {
     b1r[c] = b1[c0 + c];
 #pragma unroll
     for (int k = 0; k < KW; ++k) w1r[c][k] = w1[(c0 + c) * KW + k];
@@ -352,6 +375,10 @@ __global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, i
 #pragma unroll 1
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int t0 = tile * TO;
+    // Rows of layer 3 that lie in the series: waves whose rows none of these
+    // need skip their products (their rows of LDS are never used), as in the
+    // tile of a short series, whose other seven waves would only be in the way.
+    const int rows = L - t0 < TO ? L - t0 : TO;
     // xin[i] = x[t0 - 3 HALO + i], zero outside the series
     for (int i = tid; i < R1 + 2 * HALO; i += IT) {
       const int t = t0 - 3 * HALO + i;
@@ -361,29 +388,30 @@ __global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, i
     store_w();
     load_w(1);
     // layer 1: row r is time t0 - 2 HALO + r
-    for (int r = tid / CG; r < R1; r += IT / CG) {
+    for (int r = tid / CG; r < rows + 4 * HALO; r += IT / CG) {
       const int t = t0 - 2 * HALO + r;
       float xv[KW];
 #pragma unroll
       for (int k = 0; k < KW; ++k) xv[k] = xin[r + k];
-      uint32_t o[4] = {0u, 0u, 0u, 0u};
+      uint32_t o[CH / 2] = {};
       if (t >= 0 && t < L) {
-        float v[8];
+        float v[CH];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
+        for (int c = 0; c < CH; ++c) {
           float s = 0.0f;
 #pragma unroll
           for (int k = 0; k < KW; ++k) s = fmaf(w1r[c][k], xv[k], s);
           v[c] = fmaxf(s + b1r[c], 0.0f);
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) o[q] = pack_bf16(v[2 * q], v[2 * q + 1]);
+        for (int q = 0; q < CH / 2; ++q) o[q] = pack_bf16(v[2 * q], v[2 * q + 1]);
       }
-      *reinterpret_cast<uint4 *>(a1 + r * I::XS + c0) = uint4{o[0], o[1], o[2], o[3]};
+      if constexpr (CH == 8) *reinterpret_cast<uint4 *>(a1 + r * I::XS + c0) = uint4{o[0], o[1], o[2], o[3]};
+      else *reinterpret_cast<uint2 *>(a1 + r * I::XS + c0) = uint2{o[0], o[1]};
     }
     __syncthreads();
-    conv(a1);  // layer 2: row r is time t0 - HALO + r
-    {
+    if (32 * wave < rows + 2 * HALO) {
+      conv(a1);  // layer 2: row r is time t0 - HALO + r
       const int t = t0 - HALO + row;
       const bool in = t >= 0 && t < L;
 #pragma unroll
@@ -401,8 +429,9 @@ __global__ __launch_bounds__(IT) void k_net_infer(const float *__restrict__ X, i
     store_w();
     load_w(0);
     __syncthreads();
+    if (32 * wave >= rows) continue;  // (the next tile's barriers are the same for every wave)
     conv(a2);  // layer 3: row r is time t0 + r
-    const bool in = row < TO && t0 + row < L;
+    const bool in = row < rows;
 #pragma unroll
     for (int c = 0; c < I::NCO; ++c)
 #pragma unroll
@@ -448,7 +477,9 @@ __global__ __launch_bounds__(64) void k_pool_parts(const float *__restrict__ par
 
 // Partial weight gradients of one slice of (series, time) of a C -> C layer:
 // part[slice][k][co][ci] = sum of dz[b][t][co] x[b][t + k - HALO][ci] and
-// part_b[slice][co] = sum of dz[b][t][co] (rows padded to 32 channels).
+// part_b[slice][co] = sum of dz[b][t][co], C x C and C values (padded to the
+// tiles of 32 they left room for one slice at C = 1: one wave did the whole
+// batch, 3.6 ms for 8 series of 1500).
 // kMask: dz is given as z > 0 ? chan[b][c] : 0.
 //
 // One wave per pair of channel tiles: lane (n, h) feeds channel n of both
@@ -464,7 +495,6 @@ __global__ __launch_bounds__(64 * NCO * NCO) void k_wgrad(const float *__restric
                                                           const float *__restrict__ chan, int C, int L,
                                                           int64_t units, int64_t units_per_slice,
                                                           float *__restrict__ part, float *__restrict__ part_b) {
-  constexpr int CP = 32 * NCO;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int cot = wave % NCO, cit = wave / NCO;
   const int co = 32 * cot + n, ci = 32 * cit + n;
@@ -537,14 +567,16 @@ __global__ __launch_bounds__(64 * NCO * NCO) void k_wgrad(const float *__restric
       }
     }
   }
-  float *out = part + static_cast<int64_t>(blockIdx.x) * KW * CP * CP;
+  float *out = part + static_cast<int64_t>(blockIdx.x) * KW * C * C;
 #pragma unroll
-  for (int k = 0; k < KW; ++k)
+  for (int v = 0; v < 16; ++v) {
+    const int o = 32 * cot + 8 * (v >> 2) + 4 * h + (v & 3);
+    if (o >= C || !has_ci) continue;
 #pragma unroll
-    for (int v = 0; v < 16; ++v)
-      out[(k * CP + 32 * cot + 8 * (v >> 2) + 4 * h + (v & 3)) * CP + ci] = acc[k][v];
+    for (int k = 0; k < KW; ++k) out[(k * C + o) * C + ci] = acc[k][v];
+  }
   bsum += __shfl_xor(bsum, 32);
-  if (cit == 0 && h == 0) part_b[static_cast<int64_t>(blockIdx.x) * CP + co] = bsum;
+  if (cit == 0 && h == 0 && has_co) part_b[static_cast<int64_t>(blockIdx.x) * C + co] = bsum;
 }
 
 // Layer 1's partial gradients: part[slice][c][k < KW] weights, [c][KW] the
@@ -614,18 +646,18 @@ __device__ __forceinline__ float sum_slices(const float *__restrict__ part, int6
 __global__ __launch_bounds__(256) void k_sum_wgrad(const float *__restrict__ part, const float *__restrict__ part_b,
                                                    int C, int slices, float *__restrict__ dw,
                                                    float *__restrict__ db) {
-  const int CP = pad32(C);
-  const int64_t n = static_cast<int64_t>(KW) * CP * CP;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 64 + (threadIdx.x & 63);
-  const bool tail = static_cast<int64_t>(blockIdx.x) * 64 >= n;  // (uniform: n is a multiple of 64)
-  const float v = tail ? sum_slices(part_b, CP, slices, i - n) : sum_slices(part, n, slices, i);
+  const int n = KW * C * C;
+  const int i = static_cast<int>(blockIdx.x) * 64 + static_cast<int>(threadIdx.x & 63);
+  const bool tail = blockIdx.x + 1 == gridDim.x;  // the last workgroup sums the bias
+  const int c = static_cast<int>(threadIdx.x & 63);
+  const float v = tail ? sum_slices(part_b, C, slices, c) : sum_slices(part, n, slices, i);
   if (threadIdx.x >= 64) return;
   if (tail) {
-    if (i - n < C) db[i - n] = v;
-    return;
+    if (c < C) db[c] = v;
+  } else if (i < n) {
+    const int ci = i % C, co = i / C % C, k = i / (C * C);
+    dw[(co * C + ci) * KW + k] = v;
   }
-  const int ci = static_cast<int>(i % CP), co = static_cast<int>(i / CP % CP), k = static_cast<int>(i / (CP * CP));
-  if (co < C && ci < C) dw[(co * C + ci) * KW + k] = v;
 }
 
 __global__ __launch_bounds__(256) void k_sum_wgrad1(const float *__restrict__ part, int C, int slices,
@@ -640,26 +672,26 @@ __global__ __launch_bounds__(256) void k_sum_wgrad1(const float *__restrict__ pa
 }
 
 // g[b][c] = mean_t a[b][t][c]; logits[b][j] = bo[j] + sum_c wo[j][c] g[b][c].
-// One workgroup per series; a wave takes every 16th time step.
+// One workgroup per series, its threads dealt out over channels and time steps.
 __global__ __launch_bounds__(1024) void k_pool_linear(const float *__restrict__ a, int C, int L,
                                                       const float *__restrict__ wo, const float *__restrict__ bo,
                                                       float *__restrict__ g, float *__restrict__ logits) {
-  __shared__ float red[16][kMaxC];
+  __shared__ float red[1024];
   __shared__ float gs[kMaxC];
   const int b = blockIdx.x, tid = threadIdx.x;
-  const int c = tid & 63, q = tid >> 6;
+  const int lgc = lg_lanes(C), c = tid & ((1 << lgc) - 1), rows = 1024 >> lgc;
   float s = 0.0f;
   if (c < C) {
     const float *row = a + static_cast<int64_t>(b) * L * C + c;
 #pragma unroll 8
-    for (int t = q; t < L; t += 16) s += row[static_cast<int64_t>(t) * C];
+    for (int t = tid >> lgc; t < L; t += rows) s += row[static_cast<int64_t>(t) * C];
   }
-  red[q][c] = s;
+  red[tid] = s;
   __syncthreads();
   if (tid < C) {
     float v = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) v += red[i][tid];
+#pragma unroll 16
+    for (int i = 0; i < rows; ++i) v += red[(i << lgc) + tid];
     gs[tid] = v / static_cast<float>(L);
     g[static_cast<int64_t>(b) * C + tid] = gs[tid];
   }
@@ -772,17 +804,16 @@ NetParams net_params(const float *theta, int C) {
 namespace {
 // Workspace of a training pass (floats).
 struct NetWs {
-  int64_t act, frags, slices, slices1, units;
+  int64_t act, slices, slices1, units;
   int64_t a1, a2, a3, d2, g, dch, logits, dlog, loss_b, wf, part, part_b, part1, total;
   NetWs(int C, int64_t B, int64_t L) {
-    const int64_t CP = pad32(C);
     act = B * C * L;
-    frags = KW * CP * CP;
+    const int64_t weights = static_cast<int64_t>(KW) * C * C;
     units = B * ((L + WT - 1) / WT);
     // the partial gradients take the room that a stored gradient of the pooled
     // layer would: more slices than that do not pay for their sums
-    const int64_t most = CP > 32 ? kSlices64 : 4 * kSlices64;
-    const int64_t room = (act + kNetSlices * static_cast<int64_t>(C) * (C * KW + 1)) / (frags + CP);
+    const int64_t most = C > 32 ? kSlices64 : 4 * kSlices64;
+    const int64_t room = (act + kNetSlices * static_cast<int64_t>(C) * (C * KW + 1)) / (weights + C);
     slices = units < most ? units : most;
     slices = slices < room ? slices : room;
     slices = slices > 1 ? slices : 1;
@@ -796,8 +827,8 @@ struct NetWs {
     a1 = take(act); a2 = take(act); a3 = take(act); d2 = take(act);
     g = take(B * C); dch = take(B * C);
     logits = take(B * NCLS); dlog = take(B * NCLS); loss_b = take(B);
-    wf = take(4 * frags);
-    part = take(slices * frags); part_b = take(slices * CP); part1 = take(slices1 * C * (KW + 1));
+    wf = take(4 * frag_floats(C));
+    part = take(slices * weights); part_b = take(slices * C); part1 = take(slices1 * C * (KW + 1));
     total = at;
   }
 };
@@ -834,15 +865,31 @@ hipError_t launch_wgrad(const NetWs &W, const float *x, const float *dz, const f
                        per, ws + W.part, ws + W.part_b);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const unsigned gx = static_cast<unsigned>(W.frags / 64 + (pad32(C) + 63) / 64);
+  static_assert(kMaxC <= 64, "one workgroup sums the bias");
+  const unsigned gx = static_cast<unsigned>((KW * C * C + 63) / 64 + 1);
   hipLaunchKernelGGL(k_sum_wgrad, dim3(gx), dim3(256), 0, st, ws + W.part, ws + W.part_b, C, static_cast<int>(used),
                      dw, db);
   return hipGetLastError();
 }
 
-hipError_t launch_frags(const float *w, int C, int flip, float *wf, hipStream_t st) {
-  const unsigned n = static_cast<unsigned>(KW * pad32(C) * pad32(C) / 256);
-  hipLaunchKernelGGL(k_weight_frags, dim3(n), dim3(256), 0, st, w, C, flip, wf);
+// Forward pass (net_forward), with the flipped weights too for a training pass.
+hipError_t forward(const float *theta, int C, const float *X, int64_t B, int64_t L, int64_t ldx, float *ws,
+                   float *logits, bool train, hipStream_t st) {
+  const NetParams P = net_params(theta, C);
+  const NetWs W(C, B, L);
+  const int frags = frag_floats(C);
+  static_assert(frag_floats(1) % 256 == 0 && frag_floats(kMaxC) % 256 == 0, "whole workgroups of weights");
+  float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *wf = ws + W.wf;
+  const int64_t wgs = B * ((L + T1 - 1) / T1) + (train ? 4 : 2) * (frags / 256);
+  if (wgs > 0x7fffffff) return hipErrorInvalidValue;  // (far above what the workspace limit lets in)
+  hipLaunchKernelGGL(k_conv1, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, st, X, ldx, static_cast<int>(B), C,
+                     static_cast<int>(L), P.w1, P.b1, a1, P.w2, P.w3, wf);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = launch_conv<false, false>(a1, nullptr, C, B, L, wf, P.b2, nullptr, a2, st);
+  if (e == hipSuccess) e = launch_conv<false, false>(a2, nullptr, C, B, L, wf + frags, P.b3, nullptr, a3, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_pool_linear, dim3(static_cast<unsigned>(B)), dim3(1024), 0, st, a3, C, static_cast<int>(L), P.wo,
+                     P.bo, ws + W.g, logits);
   return hipGetLastError();
 }
 }  // namespace
@@ -855,21 +902,7 @@ int64_t net_workspace_floats(int C, int64_t B, int64_t L) { return NetWs(C, B, L
 
 hipError_t net_forward(const float *theta, int C, const float *X, int64_t B, int64_t L,
                        int64_t ldx, float *ws, float *logits, hipStream_t st) {
-  const NetParams P = net_params(theta, C);
-  const NetWs W(C, B, L);
-  float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *wf = ws + W.wf;
-  hipError_t e = launch_frags(P.w2, C, 0, wf, st);
-  if (e == hipSuccess) e = launch_frags(P.w3, C, 0, wf + W.frags, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_conv1, dim3(static_cast<unsigned>((L + T1 - 1) / T1), static_cast<unsigned>(B)), dim3(256), 0, st,
-                     X, ldx, C, static_cast<int>(L), P.w1, P.b1, a1);
-  e = hipGetLastError();
-  if (e == hipSuccess) e = launch_conv<false, false>(a1, nullptr, C, B, L, wf, P.b2, nullptr, a2, st);
-  if (e == hipSuccess) e = launch_conv<false, false>(a2, nullptr, C, B, L, wf + W.frags, P.b3, nullptr, a3, st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_pool_linear, dim3(static_cast<unsigned>(B)), dim3(1024), 0, st, a3, C, static_cast<int>(L), P.wo,
-                     P.bo, ws + W.g, logits);
-  return hipGetLastError();
+  return forward(theta, C, X, B, L, ldx, ws, logits, false, st);
 }
 
 namespace {
@@ -929,10 +962,8 @@ hipError_t net_loss_grad(const float *theta, int C, const float *X, const int32_
   auto mut = [](const float *p) { return const_cast<float *>(p); };
   float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *d2 = ws + W.d2;
   float *g = ws + W.g, *dch = ws + W.dch, *logits = ws + W.logits, *dlog = ws + W.dlog, *loss_b = ws + W.loss_b;
-  float *wf3 = ws + W.wf + 2 * W.frags, *wf2 = ws + W.wf + 3 * W.frags;
-  hipError_t e = net_forward(theta, C, X, B, L, ldx, ws, logits, st);
-  if (e == hipSuccess) e = launch_frags(P.w3, C, 1, wf3, st);
-  if (e == hipSuccess) e = launch_frags(P.w2, C, 1, wf2, st);
+  const float *wf3 = ws + W.wf + 2 * frag_floats(C), *wf2 = ws + W.wf + 3 * frag_floats(C);
+  hipError_t e = forward(theta, C, X, B, L, ldx, ws, logits, true, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_softmax_ce, dim3(blocks_for(B, 128)), dim3(128), 0, st, logits, labels, static_cast<int>(B), loss_b, dlog);
   hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, loss_b, static_cast<int>(B), loss);
