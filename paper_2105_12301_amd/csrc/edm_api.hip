@@ -966,12 +966,15 @@ int check_net(edm_ctx *ctx, const void *params, int32_t C, const void *X, int64_
   return EDM_OK;
 }
 
-// The limit is the same for training and inference; inference needs (and
-// reserves) far less than training.
-int net_ws(edm_ctx *ctx, int32_t C, int64_t B, int64_t L, bool infer = false) {
-  if (sizeof(float) * static_cast<size_t>(edm::net_limit_floats(C, B, L)) > workspace_limit())
+// Reserves a pass's workspace under the limit, and returns the limit (floats)
+// that the pass lays it out by.  The calls that are refused are the same for
+// training and inference; inference reserves far less.
+int net_ws(edm_ctx *ctx, int32_t C, int64_t B, int64_t L, int64_t *limit, bool infer = false) {
+  *limit = static_cast<int64_t>(workspace_limit() / sizeof(float));
+  if (edm::net_limit_floats(C, B, L) > *limit)
     return set_err(ctx, EDM_E_NOMEM, "network workspace exceeds EDM_WORKSPACE_LIMIT: use smaller batches");
-  const int64_t floats = infer ? edm::net_infer_workspace_floats(C, B, L) : edm::net_workspace_floats(C, B, L);
+  const int64_t floats =
+      infer ? edm::net_infer_workspace_floats(C, B, L) : edm::net_workspace_floats(C, B, L, *limit);
   return ws_reserve(ctx, sizeof(float) * static_cast<size_t>(floats));
 }
 }  // namespace
@@ -983,8 +986,10 @@ int edm_net_forward(edm_ctx *ctx, const float *params, int32_t C, const float *X
   if (B > 0 && !logits) return set_err(ctx, EDM_E_ARG, "NULL logits");
   EDM_RC(check_ctx(ctx));
   if (B == 0) return EDM_OK;
-  EDM_RC(net_ws(ctx, C, B, L));
-  EDM_HIP(ctx, edm::net_forward(params, C, X, B, L, ldx, reinterpret_cast<float *>(ctx->ws), logits, ctx->stream));
+  int64_t limit = 0;
+  EDM_RC(net_ws(ctx, C, B, L, &limit));
+  EDM_HIP(ctx, edm::net_forward(params, C, X, B, L, ldx, reinterpret_cast<float *>(ctx->ws), limit, logits,
+                                ctx->stream));
   return EDM_OK;
 }
 
@@ -996,7 +1001,8 @@ int edm_net_forward_bf16(edm_ctx *ctx, const float *params, int32_t C, const flo
   if (B > 0 && !logits) return set_err(ctx, EDM_E_ARG, "NULL logits");
   EDM_RC(check_ctx(ctx));
   if (B == 0) return EDM_OK;
-  EDM_RC(net_ws(ctx, C, B, L, true));
+  int64_t limit = 0;
+  EDM_RC(net_ws(ctx, C, B, L, &limit, true));
   EDM_HIP(ctx, edm::net_forward_bf16(params, C, X, B, L, ldx, reinterpret_cast<float *>(ctx->ws), logits, ctx->stream));
   return EDM_OK;
 }
@@ -1008,8 +1014,10 @@ int edm_net_loss_grad(edm_ctx *ctx, const float *params, int32_t C, const float 
   EDM_RC(check_net(ctx, params, C, X, B, L, ldx));
   if (B < 1 || !labels || !loss || !grad) return set_err(ctx, EDM_E_ARG, "need B >= 1 and labels, loss, grad");
   EDM_RC(check_ctx(ctx));
-  EDM_RC(net_ws(ctx, C, B, L));
-  EDM_HIP(ctx, edm::net_loss_grad(params, C, X, labels, B, L, ldx, reinterpret_cast<float *>(ctx->ws), loss, grad, ctx->stream));
+  int64_t limit = 0;
+  EDM_RC(net_ws(ctx, C, B, L, &limit));
+  EDM_HIP(ctx, edm::net_loss_grad(params, C, X, labels, B, L, ldx, reinterpret_cast<float *>(ctx->ws), limit, loss, grad,
+                                  ctx->stream));
   return EDM_OK;
 }
 

@@ -806,7 +806,7 @@ namespace {
 struct NetWs {
   int64_t act, slices, slices1, units;
   int64_t a1, a2, a3, d2, g, dch, logits, dlog, loss_b, wf, part, part_b, part1, total;
-  NetWs(int C, int64_t B, int64_t L) {
+  NetWs(int C, int64_t B, int64_t L, int64_t limit) {
     act = B * C * L;
     const int64_t weights = static_cast<int64_t>(KW) * C * C;
     units = B * ((L + WT - 1) / WT);
@@ -818,6 +818,21 @@ struct NetWs {
     slices = slices < room ? slices : room;
     slices = slices > 1 ? slices : 1;
     slices1 = units < kSlices1 ? units : kSlices1;
+    lay_out(C, B);
+    if (total <= limit) return;
+    // the room beside one slice each: a quarter for layer 1, the rest for the other layers
+    const int64_t all = slices, all1 = slices1;
+    slices = slices1 = 1;
+    lay_out(C, B);
+    const int64_t spare = limit > total ? limit - total : 0;  // (sizes are rounded up to 64)
+    slices1 = 1 + spare / 4 / (C * (KW + 1) + 64);
+    slices1 = slices1 < all1 ? slices1 : all1;
+    slices = 1 + (spare - (slices1 - 1) * (C * (KW + 1) + 64)) / (weights + C + 128);
+    slices = slices < all ? slices : all;
+    lay_out(C, B);
+  }
+  void lay_out(int C, int64_t B) {
+    const int64_t weights = static_cast<int64_t>(KW) * C * C;
     int64_t at = 0;
     auto take = [&](int64_t n) {
       const int64_t o = at;
@@ -874,9 +889,9 @@ hipError_t launch_wgrad(const NetWs &W, const float *x, const float *dz, const f
 
 // Forward pass (net_forward), with the flipped weights too for a training pass.
 hipError_t forward(const float *theta, int C, const float *X, int64_t B, int64_t L, int64_t ldx, float *ws,
-                   float *logits, bool train, hipStream_t st) {
+                   int64_t limit, float *logits, bool train, hipStream_t st) {
   const NetParams P = net_params(theta, C);
-  const NetWs W(C, B, L);
+  const NetWs W(C, B, L, limit);
   const int frags = frag_floats(C);
   static_assert(frag_floats(1) % 256 == 0 && frag_floats(kMaxC) % 256 == 0, "whole workgroups of weights");
   float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *wf = ws + W.wf;
@@ -898,11 +913,11 @@ int64_t net_limit_floats(int C, int64_t B, int64_t L) {
   return 5 * B * C * L + B * C + 3 * B * NCLS + B + kNetSlices * (static_cast<int64_t>(C) * C * KW + C) + 64;
 }
 
-int64_t net_workspace_floats(int C, int64_t B, int64_t L) { return NetWs(C, B, L).total; }
+int64_t net_workspace_floats(int C, int64_t B, int64_t L, int64_t limit) { return NetWs(C, B, L, limit).total; }
 
 hipError_t net_forward(const float *theta, int C, const float *X, int64_t B, int64_t L,
-                       int64_t ldx, float *ws, float *logits, hipStream_t st) {
-  return forward(theta, C, X, B, L, ldx, ws, logits, false, st);
+                       int64_t ldx, float *ws, int64_t limit, float *logits, hipStream_t st) {
+  return forward(theta, C, X, B, L, ldx, ws, limit, logits, false, st);
 }
 
 namespace {
@@ -955,15 +970,15 @@ hipError_t net_forward_bf16(const float *theta, int C, const float *X, int64_t B
 }
 
 hipError_t net_loss_grad(const float *theta, int C, const float *X, const int32_t *labels,
-                         int64_t B, int64_t L, int64_t ldx, float *ws, float *loss,
+                         int64_t B, int64_t L, int64_t ldx, float *ws, int64_t limit, float *loss,
                          float *grad, hipStream_t st) {
   const NetParams P = net_params(theta, C), G = net_params(grad, C);
-  const NetWs W(C, B, L);
+  const NetWs W(C, B, L, limit);
   auto mut = [](const float *p) { return const_cast<float *>(p); };
   float *a1 = ws + W.a1, *a2 = ws + W.a2, *a3 = ws + W.a3, *d2 = ws + W.d2;
   float *g = ws + W.g, *dch = ws + W.dch, *logits = ws + W.logits, *dlog = ws + W.dlog, *loss_b = ws + W.loss_b;
   const float *wf3 = ws + W.wf + 2 * frag_floats(C), *wf2 = ws + W.wf + 3 * frag_floats(C);
-  hipError_t e = forward(theta, C, X, B, L, ldx, ws, logits, true, st);
+  hipError_t e = forward(theta, C, X, B, L, ldx, ws, limit, logits, true, st);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_softmax_ce, dim3(blocks_for(B, 128)), dim3(128), 0, st, logits, labels, static_cast<int>(B), loss_b, dlog);
   hipLaunchKernelGGL(k_mean, dim3(1), dim3(256), 0, st, loss_b, static_cast<int>(B), loss);

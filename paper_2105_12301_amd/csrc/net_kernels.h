@@ -13,26 +13,30 @@ struct NetParams {
   const float *w1, *b1, *w2, *b2, *w3, *b3, *wo, *bo;
 };
 
-constexpr int kNetSlices = 64;  // (series, time) slices of a weight gradient the limit counts with
+constexpr int kNetSlices = 64;  // (series, time) slices of a weight gradient that net_limit_floats counts with
 
 int64_t net_param_count(int C);
 NetParams net_params(const float *theta, int C);
-// Workspace (floats) of one forward/backward pass over B series of length L,
-// and the size that is held against the workspace limit (a stored gradient of
-// the pooled layer included, without the padding of the weights' fragments).
+// A call is refused where net_limit_floats, a bound of one pass over B series of
+// length L with a stored gradient of the pooled layer, passes the workspace
+// limit.  net_workspace_floats is what a forward/backward pass under that limit
+// (floats) reserves: its slices of partial gradients are as many as the limit
+// has room for.  (Up to four channels the weights' layout may pass a limit of
+// less than 30 KB; a workspace is a whole number of MiB.)
 int64_t net_limit_floats(int C, int64_t B, int64_t L);
-int64_t net_workspace_floats(int C, int64_t B, int64_t L);
+int64_t net_workspace_floats(int C, int64_t B, int64_t L, int64_t limit);
 // Workspace of net_forward_bf16.
 int64_t net_infer_workspace_floats(int C, int64_t B, int64_t L);
 
+// (limit: as given to net_workspace_floats)
 hipError_t net_forward(const float *theta, int C, const float *X, int64_t B, int64_t L,
-                       int64_t ldx, float *ws, float *logits, hipStream_t st);
+                       int64_t ldx, float *ws, int64_t limit, float *logits, hipStream_t st);
 // Inference with the C -> C convolutions on BF16 matrix cores (C = 32 or 64);
 // ws: net_infer_workspace_floats, 256-byte aligned.
 hipError_t net_forward_bf16(const float *theta, int C, const float *X, int64_t B, int64_t L,
                             int64_t ldx, float *ws, float *logits, hipStream_t st);
 hipError_t net_loss_grad(const float *theta, int C, const float *X, const int32_t *labels,
-                         int64_t B, int64_t L, int64_t ldx, float *ws, float *loss,
+                         int64_t B, int64_t L, int64_t ldx, float *ws, int64_t limit, float *loss,
                          float *grad, hipStream_t st);
 hipError_t net_adam(float *p, const float *g, float *m, float *v, int64_t n, int step, float lr,
                     float b1, float b2, float eps, hipStream_t st);
