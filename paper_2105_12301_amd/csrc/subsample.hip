@@ -35,11 +35,17 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kChunk = 2048;  // member indices staged per LDS chunk
 
+// Improving members are queued from this E on, inserted as they come below: the
+// queue's pushes and LDS cost more than insertions into two or three entries
+// save (20 sets of up to 20000 members, E = 1: 8.0 ms queued, 7.4 before).
+constexpr int kSubQueueE = 3;
+
 // a.X / a.L_uni: the library series; a.idx / a.w: tables [set][m][K]
 // (stride a.tbl_stride); members of set s: sets[off[s] .. off[s+1]).
 template <int E_T, int K>
 __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_t *__restrict__ sets,
                                                          const int64_t *__restrict__ off) {
+  constexpr bool kQueue = E_T >= kSubQueueE;
   extern __shared__ __attribute__((aligned(16))) float sub_smem[];
   const int E = E_T;
   const int tau = a.tau;
@@ -87,20 +93,27 @@ __global__ __launch_bounds__(kThreads) void k_knn_subset(KnnArgs a, const int32_
         const float d = vp[j] - xs[q + j * tau];
         acc = acc + d * d;
       }
-      pend.push(entry(acc, q), abs(q - p) > excl && acc < entry_key(l[K - 1]));
+      const bool want = abs(q - p) > excl && acc < entry_key(l[K - 1]);
+      if constexpr (kQueue) {
+        pend.push(entry(acc, q), want);
+      } else {
+        if (__builtin_amdgcn_ballot_w64(want)) list_insert<0, K, K>(l, entry(want ? acc : __builtin_inff(), q));
+      }
     };
     int i = 0;
     for (; i + kPendStep <= n; i += kPendStep) {
 #pragma unroll
       for (int u = 0; u < kPendStep; ++u) member(i + u);
-      if (pend.full()) flush();
+      if constexpr (kQueue)
+        if (pend.full()) flush();
     }
     for (; i < n; ++i) {
       member(i);
-      if (pend.full()) flush();
+      if constexpr (kQueue)
+        if (pend.full()) flush();
     }
   }
-  flush();
+  if constexpr (kQueue) flush();
   if (!active) return;
 
   int qi[K];
@@ -167,7 +180,7 @@ hipError_t launch_knn_subsets(const KnnArgs &a, const int32_t *sets, const int64
   const int64_t m = a.L_uni - static_cast<int64_t>(a.E - 1) * a.tau - a.Tp;
   if (m < 1) return hipSuccess;
   const size_t shm = static_cast<size_t>((a.L_uni + 1) / 2 * 2) * sizeof(float) + kChunk * sizeof(int32_t) +
-                     static_cast<size_t>(kThreads / kWave) * kPendBytes;
+                     (a.E >= kSubQueueE ? static_cast<size_t>(kThreads / kWave) * kPendBytes : 0);
   const void *fn = reinterpret_cast<const void *>(fns[a.E - 1]);
   if (shm > 65536) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
