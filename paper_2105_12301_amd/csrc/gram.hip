@@ -935,7 +935,7 @@ __global__ __launch_bounds__(kGramThreads) void k_sweep_small(KnnArgs a, int z0)
     case 1: gram_scan<19, 20, false>(a, row, bx, gram_smem); break;
     case 2: gram_scan<5, 8, false>(a, row, bx, gram_smem); break;
     case 3: gram_scan<17, 18, false>(a, row, bx, gram_smem); break;
-    case kSmallExactZ: group_scan<1, 4, 4, 2>(a, row, bx, gram_smem); break;
+    case kSmallExactZ: group_scan<1, 4, 4, 2, true>(a, row, bx, gram_smem); break;
     case 5: gram_scan<9, 11, false>(a, row, bx, gram_smem); break;
     default: gram_scan<12, 13, false>(a, row, bx, gram_smem); break;
   }
@@ -1040,7 +1040,7 @@ size_t gram_shm(int64_t ld, bool xg) {
 }
 
 size_t small_lds(int64_t L_max) {
-  const size_t exact = static_cast<size_t>(scan_floats(L_max)) * sizeof(float) + group_extra_lds<1, 4, 4, 2>();
+  const size_t exact = static_cast<size_t>(scan_floats(L_max)) * sizeof(float) + group_extra_lds<1, 4, 4, 2, true>();
   const size_t filter = gram_shm(gram_ld(L_max), false);
   return exact > filter ? exact : filter;
 }

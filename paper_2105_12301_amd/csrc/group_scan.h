@@ -15,17 +15,19 @@ namespace {
 constexpr int kPendQ = 16;  // queue positions per lane of a group's scan
 
 // LDS of a group's queues and merges, beyond the staged series.
-template <int ELO, int EHI, int Q, int S>
+template <int ELO, int EHI, int Q, int S, bool kQueue>
 constexpr size_t group_extra_lds() {
-  const size_t queue = (ELO == EHI ? kPendBytes : sizeof(int32_t) * kPendQ * kWave) * static_cast<size_t>(Q * S);
+  const size_t queue =
+      kQueue ? (ELO == EHI ? kPendBytes : sizeof(int32_t) * kPendQ * kWave) * static_cast<size_t>(Q * S) : 0;
   const size_t merge = merge_bytes<Q, S>(EHI + 1);
   return queue > merge ? queue : merge;
 }
 
 // One workgroup's share of a batched scan: query block `bx` of row `row`,
 // every E in [ELO, EHI].  Called by the grid kernel and by the persistent
-// kernel; every early return is uniform across the workgroup.
-template <int ELO, int EHI, int Q, int S>
+// kernel; every early return is uniform across the workgroup.  kQueue: improving
+// candidates are queued, otherwise inserted as they come.
+template <int ELO, int EHI, int Q, int S, bool kQueue>
 __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, const int bx,
                                            float *__restrict__ smem) {
   constexpr int kT = kWave * Q * S;
@@ -62,7 +64,7 @@ __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, cons
   static_for<ELO, EHI>([&](auto EC) {
     constexpr int E = decltype(EC)::value;
     constexpr int OFF = list_off<ELO>(E);
-    // table mode: lists of E that are not needed stay idle (kth = -1)
+    // lists of E that are not wanted stay idle (kth = -1)
     const bool act = p < L - (E - 1) - Tp && E <= a.E_max && (a.mom != nullptr || ((need >> (E - 1)) & 1u));
 #pragma unroll
     for (int i = 0; i < E + 1; ++i) l[OFF + i] = act ? entry_empty() : entry_idle();
@@ -75,7 +77,34 @@ __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, cons
   // every lane's q < m_hi: valid for all E
   const int s_full = m_hi - (kWave - 1) < s_end ? m_hi - (kWave - 1) : s_end;
   double *const extra = reinterpret_cast<double *>(smem + a.lds_x);
-  if constexpr (NG == 1) {
+  if constexpr (!kQueue) {
+    if (p0 < m_lo)
+      scan_steps<ELO, EHI, true, kScanUnroll>(
+          vp, xs, lane, 1, s0, s_end, s_full,
+          [&](int s, int q, const float(&key)[NG], auto edge) {
+            if (s == p0) return;  // (wave-uniform)
+            constexpr bool kEdge = decltype(edge)::value;
+            float d[NG];  // negative: the key improves E's list (see below)
+            static_for<ELO, EHI>([&](auto EC) {
+              constexpr int E = decltype(EC)::value;
+              d[E - ELO] = key[E - ELO] - entry_key(l[list_off<ELO>(E) + E]);
+              if constexpr (kEdge)
+                if (s >= s_end || q < 0 || q >= L - (E - 1) - Tp) d[E - ELO] = 0.0f;
+            });
+            float any = d[0];
+#pragma unroll
+            for (int g = 1; g < NG; ++g) any = fminf(any, d[g]);
+            if (__builtin_amdgcn_ballot_w64(any < 0.0f) == 0) return;
+            static_for<ELO, EHI>([&](auto EC) {
+              constexpr int E = decltype(EC)::value;
+              const bool want = d[E - ELO] < 0.0f;
+              if (NG == 1 || __builtin_amdgcn_ballot_w64(want))
+                list_insert<list_off<ELO>(E), E + 1, TOT>(
+                    l, entry(want ? key[E - ELO] : __builtin_inff(), q < 0 ? 0 : q));
+            });
+          },
+          []() {});
+  } else if constexpr (NG == 1) {
     // one E: its improving entries are queued with their keys
     Pending pend(extra);
     auto flush = [&]() { pend.drain([&](double e) { list_insert<0, ELO + 1, TOT>(l, e); }); };
@@ -96,6 +125,9 @@ __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, cons
     // alone) and inserted in batches, with every E's key recomputed.
     int32_t *pend = reinterpret_cast<int32_t *>(extra) + wave * (kPendQ * kWave) + lane;
     int n_pend = 0;
+    // (Every list of the group, wanted or not: their insertions are independent
+    // instructions of one block.  Skipping unwanted ones by a branch each costs
+    // 5-24 % where all are wanted, and both loops in one kernel spill.)
     auto flush = [&]() {
 #pragma unroll 1
       for (int i = 0; i < kPendQ; ++i) {

@@ -158,6 +158,8 @@ hipError_t launch_tables_from_sweep_all(const KnnArgs &a, int E_max, int nslots,
 // Launch the kNN kernel for `nslots` libraries whose longest series has
 // `L_max` samples.  Returns a hipError_t.
 hipError_t launch_knn(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st);
+// ... its launches alone, for a caller that times them as a family of its own.
+hipError_t launch_knn_scan(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st);
 
 // Whether the exact scan of one library of L samples splits its candidates over
 // 16 waves (too few workgroups to fill the chip): it then beats the filter.

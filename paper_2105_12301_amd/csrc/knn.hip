@@ -17,17 +17,22 @@ constexpr auto make_fast(std::index_sequence<I...>) {
 
 }  // namespace
 
-bool knn_splits(int64_t L) { return scan_layout(1, L, EDM_E_MAX + 1, false) == ScanLayout::kTable16; }
+bool knn_splits(int64_t L) { return scan_layout(1, L, EDM_E_MAX, EDM_E_MAX + 1, false) == ScanLayout::kTableSplit; }
 
-hipError_t launch_knn(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+hipError_t launch_knn_scan(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
   static const auto fast = make_fast(std::make_index_sequence<EDM_E_MAX>{});
   if (nslots <= 0) return hipSuccess;
   KnnArgs b = a;
   b.lds_x = scan_floats(L_max);
-  TimedLaunch timed(EDM_KF_EXACT_SCAN, st);
   // (E = 1 has no lag, and every lag is allowed with it: never a lagged scan)
   if ((a.tau == 1 || a.E == 1) && a.k == a.E + 1 && a.E >= 1 && a.E <= EDM_E_MAX) return fast[a.E - 1](b, nslots, L_max, st);
   return launch_knn_lagged(b, nslots, L_max, st);
+}
+
+hipError_t launch_knn(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
+  if (nslots <= 0) return hipSuccess;
+  TimedLaunch timed(EDM_KF_EXACT_SCAN, st);
+  return launch_knn_scan(a, nslots, L_max, st);
 }
 
 }  // namespace edm

@@ -51,14 +51,13 @@
 namespace edm {
 namespace {
 
-// Waves per SIMD the registers are kept to: four, or three where the list, the
-// window and the query's samples do not fit 128 registers (16-wave workgroups
-// have no choice).
-constexpr int knn_waves(int E, int threads) { return threads > 512 ? 4 : (E == 0 || E >= 15 ? 3 : 4); }
+// Waves per SIMD the registers are kept to: four, or three (two) where the list
+// and the epilogue's arrays of a scan without splits do not fit 128 (168).
+constexpr int knn_waves(int K, int S) { return S > 1 || K <= 17 ? 4 : (K <= 24 ? 3 : 2); }
 
-// Q, S: layout of the workgroup (topk_list.h).
-template <int E_T, int K, bool T1, int Q, int S>
-__global__ __launch_bounds__(kWave * Q * S, knn_waves(E_T, kWave * Q * S)) void k_knn(KnnArgs a, int slot0) {
+// Q, S: layout of the workgroup; kQueue: improving candidates are queued (topk_list.h).
+template <int E_T, int K, bool T1, int Q, int S, bool kQueue>
+__global__ __launch_bounds__(kWave * Q * S, knn_waves(K, S)) void k_knn(KnnArgs a, int slot0) {
   constexpr int EM = E_T ? E_T : EDM_E_MAX;
   constexpr int kT = kWave * Q * S;
   extern __shared__ __attribute__((aligned(16))) float knn_smem[];
@@ -106,12 +105,19 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(E_T, kWave * Q * S)) void 
     auto offer = [&](int s, float acc, int q, bool valid) {
       // T1: a lane's candidates come in ascending q; otherwise the residues
       // are walked one by one and equal keys are ordered by the entry
-      const bool lt = T1 ? acc < entry_key(l[K - 1]) : entry(acc, q) < l[K - 1];
-      pend.push(entry(acc, q), valid && abs(s - p0) > excl && lt);
+      if constexpr (kQueue) {
+        const bool lt = T1 ? acc < entry_key(l[K - 1]) : entry(acc, q) < l[K - 1];
+        pend.push(entry(acc, q), valid && abs(s - p0) > excl && lt);
+      } else {
+        if (abs(s - p0) <= excl) return;  // (wave-uniform)
+        const bool want = valid && (T1 ? acc < entry_key(l[K - 1]) : entry(acc, q) < l[K - 1]);
+        if (__builtin_amdgcn_ballot_w64(want)) list_insert<0, K, K>(l, entry(want ? acc : __builtin_inff(), q));
+      }
     };
     auto in_range = [&](int s, int q) { return s < s_end && static_cast<unsigned>(q) < static_cast<unsigned>(m); };
     auto check = [&]() {
-      if (pend.full()) flush();
+      if constexpr (kQueue)
+        if (pend.full()) flush();
     };
     if constexpr (E_T > 0) {
       const int s_full = m - (kWave - 1) < s_end ? m - (kWave - 1) : s_end;  // below: every lane's q < m
@@ -130,77 +136,111 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(E_T, kWave * Q * S)) void 
         float acc = 0.0f;
 #pragma unroll
         for (int j = 0; j < EM; ++j) {
-          if (j < E) {
-            const float d = vp[j] - xs[qc + j * tau];
-            acc = acc + d * d;
-          }
+          if (j >= E) break;  // (uniform: E branches, not 20)
+          const float d = vp[j] - xs[qc + j * tau];
+          acc = acc + d * d;
         }
         offer(s, acc, q, valid);
         check();
       }
     }
-    flush();
+    if constexpr (kQueue) flush();
   }
-  if constexpr (S > 1) {  // (the queues are drained: their LDS serves the merge)
-    merge_splits<Q, S, 0, K, K>(l, extra);
-  }
-  int qi[K];
-#pragma unroll
-  for (int i = 0; i < K; ++i) qi[i] = entry_idx(l[i]);
-
-  // Epilogue: float64 distances of the k winners, weights, outputs.  The
-  // loops over the winners stay rolled and rotate the register lists by one
-  // slot per trip, so only one neighbour's coordinates are live at a time.
+  // Epilogue: float64 distances of the k winners, weights (Section 2.1 step 3),
+  // outputs.  A slot stays unfilled (index 0) only if keys are NaN or overflow to
+  // +inf; the status word reports non-finite input.
   Mom mine = mom_zero();
-  if (active && sp == 0) {
+  const int64_t base = static_cast<int64_t>(slot) * a.tbl_stride + static_cast<int64_t>(p) * K;
+  auto distance = [&](int q) {
+    double s2 = 0.0;
+#pragma unroll
+    for (int j = 0; j < EM; ++j) {
+      if (E_T || j < E) {
+        const double d = static_cast<double>(vp[j]) - static_cast<double>(xs[q + j * tau]);
+        s2 += d * d;
+      }
+    }
+    return sqrt(s2);
+  };
+  auto weight = [](double d, double dmin) { return dmin > 0.0 ? exp(-d / dmin) : (d == 0.0 ? 1.0 : 0.0); };
+  if constexpr (S > 1) {
+    // The S waves of a query share its winners, whose indices, distances and
+    // weights pass through LDS (the queues and merges are over): register
+    // arrays of them beside the list spill in the 128 registers of a 16-wave
+    // workgroup.  Every sum keeps its order.
+    merge_splits<Q, S, 0, K, K>(l, extra);
+    int32_t *const nbr = reinterpret_cast<int32_t *>(extra + Q * K * kWave) + qg * K * kWave + lane;
+    double *const D = extra + qg * K * kWave + lane;
+    __syncthreads();
+    if (sp == 0) {
+#pragma unroll
+      for (int i = 0; i < K; ++i) nbr[i * kWave] = entry_idx(l[i]) < 0 ? 0 : entry_idx(l[i]);
+    }
+    __syncthreads();
+    if (active) {
+      for (int r = sp; r < K; r += S) {
+        const int q = nbr[r * kWave];
+        const double dq = distance(q);
+        D[r * kWave] = dq;
+        if (a.idx) a.idx[base + r] = q;
+        if (a.dist) a.dist[base + r] = static_cast<float>(dq);
+      }
+    }
+    __syncthreads();
+    double dmin = __builtin_inf();
+    for (int r = 0; r < K; ++r) dmin = fmin(dmin, D[r * kWave]);
+    __syncthreads();
+    if (active)
+      for (int r = sp; r < K; r += S) D[r * kWave] = weight(D[r * kWave], dmin);
+    __syncthreads();
+    if (active && (a.w || (a.mom && sp == 0))) {
+      double wsum = 0.0;
+      for (int r = 0; r < K; ++r) wsum += D[r * kWave];
+      const double inv = 1.0 / wsum;
+      if (a.w)
+        for (int r = sp; r < K; r += S) a.w[base + r] = static_cast<float>(D[r * kWave] * inv);
+      if (a.mom && sp == 0) {
+        const int o_off = off + a.Tp;
+        double yh = 0.0;
+        for (int r = 0; r < K; ++r) yh += (D[r * kWave] * inv) * static_cast<double>(xs[nbr[r * kWave] + o_off]);
+        mine.n = 1.0;
+        mine.mo = static_cast<double>(xs[p + o_off]);
+        mine.mp = yh;
+      }
+    }
+  } else if (active) {
+    // The loops over the winners stay rolled and rotate the register lists by
+    // one slot per trip, so only one neighbour's coordinates are live at a time.
+    int qi[K];
+#pragma unroll
+    for (int i = 0; i < K; ++i) qi[i] = entry_idx(l[i]);
     double D[K];  // distance, then weight, of neighbour qi[i]
-    float Df[K];  // distance rounded for output
     double dmin = __builtin_inf();
 #pragma unroll 1
     for (int r = 0; r < K; ++r) {
-      // A slot stays unfilled (-1) only if non-finite input made keys NaN;
-      // the status word reports that case, and index 0 keeps tables in range.
       const int q = qi[0] < 0 ? 0 : qi[0];
-      double s2 = 0.0;
-#pragma unroll
-      for (int j = 0; j < EM; ++j) {
-        if (E_T || j < E) {
-          const double d = static_cast<double>(vp[j]) - static_cast<double>(xs[q + j * tau]);
-          s2 += d * d;
-        }
-      }
-      const double dq = sqrt(s2);
+      const double dq = distance(q);
       dmin = fmin(dmin, dq);
 #pragma unroll
       for (int i = 0; i < K - 1; ++i) {
         qi[i] = qi[i + 1];
         D[i] = D[i + 1];
-        Df[i] = Df[i + 1];
       }
       qi[K - 1] = q;
       D[K - 1] = dq;
-      Df[K - 1] = static_cast<float>(dq);
+      if (a.idx) a.idx[base + r] = q;
+      if (a.dist) a.dist[base + r] = static_cast<float>(dq);
     }
     double wsum = 0.0;
 #pragma unroll 1
     for (int r = 0; r < K; ++r) {
-      const double d = D[0];
-      const double wq = dmin > 0.0 ? exp(-d / dmin) : (d == 0.0 ? 1.0 : 0.0);
+      const double wq = weight(D[0], dmin);
       wsum += wq;
 #pragma unroll
       for (int i = 0; i < K - 1; ++i) D[i] = D[i + 1];
       D[K - 1] = wq;
     }
     const double inv = 1.0 / wsum;
-    const int64_t base = static_cast<int64_t>(slot) * a.tbl_stride + static_cast<int64_t>(p) * K;
-    if (a.idx) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) a.idx[base + i] = qi[i];
-    }
-    if (a.dist) {
-#pragma unroll
-      for (int i = 0; i < K; ++i) a.dist[base + i] = Df[i];
-    }
     if (a.w) {
 #pragma unroll
       for (int i = 0; i < K; ++i) a.w[base + i] = static_cast<float>(D[i] * inv);
@@ -233,10 +273,10 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(E_T, kWave * Q * S)) void 
   }
 }
 
-template <int E_T, int K, bool T1, int Q, int S>
+template <int E_T, int K, bool T1, int Q, int S, bool kQueue>
 hipError_t launch_one(KnnArgs a, int nslots, int64_t L_max, hipStream_t st) {
-  const void *fn = reinterpret_cast<const void *>(&k_knn<E_T, K, T1, Q, S>);
-  const size_t shm = static_cast<size_t>(scan_lds<Q, S>(L_max, K, a.lds_x));
+  const void *fn = reinterpret_cast<const void *>(&k_knn<E_T, K, T1, Q, S, kQueue>);
+  const size_t shm = static_cast<size_t>(scan_lds<Q, S>(K, a.lds_x, kQueue));
   if (shm > 65536) {
     hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        static_cast<int>(shm));
@@ -246,7 +286,7 @@ hipError_t launch_one(KnnArgs a, int nslots, int64_t L_max, hipStream_t st) {
   const unsigned gx = static_cast<unsigned>((L_max + kWave * Q - 1) / (kWave * Q));
   for (int s0 = 0; s0 < nslots; s0 += kMaxY) {
     const int ny = nslots - s0 < kMaxY ? nslots - s0 : kMaxY;
-    hipLaunchKernelGGL((k_knn<E_T, K, T1, Q, S>), dim3(gx, static_cast<unsigned>(ny)), dim3(kWave * Q * S), shm,
+    hipLaunchKernelGGL((k_knn<E_T, K, T1, Q, S, kQueue>), dim3(gx, static_cast<unsigned>(ny)), dim3(kWave * Q * S), shm,
                        st, a, s0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -256,12 +296,18 @@ hipError_t launch_one(KnnArgs a, int nslots, int64_t L_max, hipStream_t st) {
 
 template <int E_T, int K, bool T1>
 hipError_t launch_layout(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
-  switch (scan_layout(nslots, L_max, K, a.mom != nullptr)) {
-    case ScanLayout::kTable16: return launch_one<E_T, K, T1, 1, 16>(a, nslots, L_max, st);
-    case ScanLayout::kSplit4: return launch_one<E_T, K, T1, 4, 4>(a, nslots, L_max, st);
-    case ScanLayout::kLong16: return launch_one<E_T, K, T1, 16, 1>(a, nslots, L_max, st);
-    case ScanLayout::kLong8: return launch_one<E_T, K, T1, 8, 1>(a, nslots, L_max, st);
-    default: return launch_one<E_T, K, T1, 4, 1>(a, nslots, L_max, st);
+  constexpr bool kQ = E_T >= kQueueE;
+  switch (scan_layout(nslots, L_max, E_T, K, a.mom != nullptr)) {
+    case ScanLayout::kTableSplit: return launch_one<E_T, K, T1, 1, 16, kQ>(a, nslots, L_max, st);
+    case ScanLayout::kSplit: return launch_one<E_T, K, T1, 4, 4, kQ>(a, nslots, L_max, st);
+    case ScanLayout::kLong16:
+      if constexpr (E_T <= 4) return launch_one<E_T, K, T1, 16, 1, false>(a, nslots, L_max, st);
+      return hipErrorInvalidValue;  // (not chosen)
+    case ScanLayout::kLong8: return launch_one<E_T, K, T1, 8, 1, false>(a, nslots, L_max, st);
+    case ScanLayout::kPlainQueue:
+      if constexpr (kQ) return launch_one<E_T, K, T1, 4, 1, true>(a, nslots, L_max, st);
+      return hipErrorInvalidValue;  // (not chosen)
+    default: return launch_one<E_T, K, T1, 4, 1, false>(a, nslots, L_max, st);
   }
 }
 

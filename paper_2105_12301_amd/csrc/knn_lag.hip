@@ -12,9 +12,10 @@ using LaunchFn = hipError_t (*)(const KnnArgs &, int, int64_t, hipStream_t);
 
 template <int K>
 hipError_t launch_generic(const KnnArgs &a, int nslots, int64_t L_max, hipStream_t st) {
-  if (scan_layout(nslots, L_max, K, a.mom != nullptr) == ScanLayout::kTable16)
-    return launch_one<0, K, false, 1, 16>(a, nslots, L_max, st);
-  return launch_one<0, K, false, 4, 1>(a, nslots, L_max, st);
+  if (a.mom == nullptr && (L_max + 63) / 64 * nslots <= kTableSplitGroups &&
+      scan_lds<1, 16>(K, a.lds_x, true) <= kScanLdsMax)
+    return launch_one<0, K, false, 1, 16, true>(a, nslots, L_max, st);
+  return launch_one<0, K, false, 4, 1, false>(a, nslots, L_max, st);
 }
 
 template <size_t... I>

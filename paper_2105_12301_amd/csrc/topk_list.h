@@ -123,16 +123,12 @@ struct Pending {
 };
 
 // Layouts of an exact scan's workgroup: Q waves of 64 queries, each query's
-// candidates split over S waves (workgroup = 64 Q S threads).
-// (4, 1): the plain layout.
-// (16, 1), then (8, 1): long series, whose staged samples leave room in LDS for
-//   one workgroup: as many waves share them as their queues leave room for.
-// (4, 4) and (1, 16): few workgroups.  A scan of m candidates is a chain of m
-//   steps however many compute units are idle; splitting it over S waves and
-//   merging their lists (list_merge, log2 S rounds through LDS) shortens it.
-//   (1, 16) writes tables only: a sweep's co-moments are merged per 256 queries.
+// candidates split over S waves (workgroup = 64 Q S threads), improving
+// candidates inserted from a queue or as they come (scan_layout).
 // Merge of the S lists of every query into the lists of split 0: in each
 // round the upper half of the splits left writes its lists to LDS.
+// (k_knn's epilogue takes the area over: 12 bytes an entry and query, which
+// S / 2 lists of 8 bytes hold from S = 4 on.)
 // area: merge_bytes<Q, S>(K) bytes; l: the lane's slice [OFF, OFF + K).
 template <int Q, int S>
 constexpr int merge_bytes(int K) {
@@ -157,31 +153,93 @@ __device__ __forceinline__ void merge_splits(double (&l)[TOT], double *area) {
 
 // LDS bytes of a scan: the staged series (lds_x floats), then the queues,
 // whose space the merge takes over.
-constexpr int64_t kScanLdsMax = 160 * 1024 - 4608;  // less the kernels' static LDS
+constexpr int64_t kLdsBytes = 160 * 1024, kLdsGrain = 1280;  // of a compute unit, and the steps it is given out in
+constexpr int64_t kScanLdsMax = kLdsBytes - 4608;            // less the kernels' static LDS
 template <int Q, int S>
-constexpr int64_t scan_lds(int64_t /*L_max*/, int K, int64_t lds_x) {
-  const int64_t queue = static_cast<int64_t>(Q) * S * kPendBytes;
+constexpr int64_t scan_lds(int K, int64_t lds_x, bool queue) {
+  const int64_t pend = queue ? static_cast<int64_t>(Q) * S * kPendBytes : 0;
   const int64_t merge = merge_bytes<Q, S>(K);
-  return lds_x * 4 + (queue > merge ? queue : merge);
+  return lds_x * 4 + (pend > merge ? pend : merge);
 }
 
-enum class ScanLayout { kPlain, kLong8, kLong16, kSplit4, kTable16 };
 constexpr int kCus = 256;  // compute units of the chip
-constexpr int64_t kTable16Groups = kCus;
-constexpr int64_t kSplit4Blocks = 2 * kCus;
-constexpr int64_t kLongSeries = 8192;  // above, 160 KB of LDS hold fewer than three workgroups of four waves
 
-// Layout of a launch over nslots series of up to L_max samples and lists of K
-// entries (wants_mom: the launch writes a sweep's co-moments).
-inline ScanLayout scan_layout(int64_t nslots, int64_t L_max, int K, bool wants_mom) {
+// Waves of a scan without splits that a compute unit holds: workgroups of Q
+// waves with `lds` bytes each, where the registers leave room for `cap` waves
+// and the launch has `blocks` blocks of 256 queries.
+constexpr int64_t resident_waves(int Q, int64_t lds, int cap, int64_t blocks) {
+  const int64_t fit = kLdsBytes / ((lds + kLdsGrain - 1) / kLdsGrain * kLdsGrain);
+  const int64_t by_lds = fit * Q, by_regs = cap / Q * Q, by_work = (blocks * 4 + kCus - 1) / kCus;
+  const int64_t w = by_lds < by_regs ? by_lds : by_regs;
+  return w < by_work ? w : by_work;
+}
+// The staged series is shared by a workgroup, so a long one leaves the more
+// waves in flight the larger the workgroup is: of 4, 8 and 16 waves (`most`)
+// the smallest with the most resident waves; 0 where nothing fits.  lds(Q):
+// all of a workgroup's LDS.  (One scan, E = 8, without queues: 100 series of
+// 20000 25.6 ms by 4 waves, 17.8 by 8; 300 of 12000 at E = 16, whose registers
+// hold 12 waves, 37.0 by 4, 45.5 by 8.)
+template <class F>
+constexpr int most_resident(int most, int cap, int64_t blocks, F &&lds) {
+  int best = 0;
+  int64_t waves = 0;
+  for (int q = 4; q <= most; q *= 2) {
+    const int64_t w = lds(q) <= kLdsBytes ? resident_waves(q, lds(q), cap, blocks) : 0;
+    if (w > waves) {
+      waves = w;
+      best = q;
+    }
+  }
+  return best;
+}
+
+// Queue or insertion as candidates come, in a scan of one E: an insertion
+// costs 2 (E + 1) float64 instructions on nearly every step of a wave, a queue
+// its pushes and 4 KB of LDS a wave, which long series need for waves in
+// flight.  Measured, queue against none: E = 6 490 / 500 us (1000 x 1000), 3411
+// / 3323 (2000 x 2000); E = 8 4405 / 4438 (2000 x 2000), 6299 / 5889 (512 x 5000);
+// E = 12 8610 / 8784 (512 x 5000), 11669 / 10766 (256 x 8000); E = 20 17758 / 17907
+// (256 x 8000), 54475 / 45873 (300 x 12000); E = 1 330 / 252 (1000 x 1000).
+constexpr int kQueueE = 5;  // from here on
+constexpr bool queue_wins(int E, int64_t L_max) { return E >= kQueueE && L_max <= 640 * (E - 4); }
+
+// Registers of a scan of one E, in waves a compute unit holds (k_knn: 64 up to
+// E = 6, 80 up to 9, 96 up to 11, 128 up to 16, 155 at 20).
+constexpr int scan_wave_cap(int E) { return E <= 6 ? 32 : E <= 9 ? 24 : E <= 11 ? 20 : E <= 16 ? 16 : 12; }
+
+enum class ScanLayout { kPlainQueue, kPlain, kLong8, kLong16, kSplit, kTableSplit };
+constexpr int64_t kTableSplitGroups = kCus;
+
+// Blocks of 256 queries up to which four waves share a query's candidates:
+// two workgroups of 16 waves a CU while the lists are short; with long ones
+// the merges cost more than the second round wins (384 blocks: E = 8 1000 samples
+// 121 against 129 us unsplit, E = 12 173 / 168, 4000 samples 474 / 502; E = 16
+// 225 / 206, 300 samples 114 / 103; E = 20 174 / 124; 256 blocks: faster at every E
+// and length, E = 20 163 / 223).
+constexpr int64_t split_blocks(int E, int64_t L_max) {
+  return E <= 10 || (E <= 14 && L_max >= 2000) ? 2 * kCus : kCus;
+}
+
+// Layout of a launch over nslots series of up to L_max samples at dimension E
+// with lists of K entries (wants_mom: the launch writes a sweep's co-moments).
+// kTableSplit, kSplit: few workgroups.  A scan of m candidates is a chain of m
+//   steps however many compute units are idle; splitting it over waves and
+//   merging their lists (list_merge, log2 S rounds through LDS) shortens it.
+//   kTableSplit writes tables only: a sweep's co-moments are merged per 256
+//   queries.  One table of 10000 samples, E = 1, 12: 64, 173 us by 16 waves, 210,
+//   525 by 4; more than 256 groups of 64 queries are a second round of the
+//   chip, which the other form does without.
+inline ScanLayout scan_layout(int64_t nslots, int64_t L_max, int E, int K, bool wants_mom) {
   const int64_t lds_x = L_max + 138;  // (scan_floats)
   const int64_t groups = (L_max + 63) / 64 * nslots, blocks = (L_max + 255) / 256 * nslots;
-  if (!wants_mom && groups <= kTable16Groups && scan_lds<1, 16>(L_max, K, lds_x) <= kScanLdsMax)
-    return ScanLayout::kTable16;
-  if (blocks <= kSplit4Blocks && scan_lds<4, 4>(L_max, K, lds_x) <= kScanLdsMax) return ScanLayout::kSplit4;
-  if (L_max > kLongSeries && scan_lds<16, 1>(L_max, K, lds_x) <= kScanLdsMax) return ScanLayout::kLong16;
-  if (L_max > kLongSeries && scan_lds<8, 1>(L_max, K, lds_x) <= kScanLdsMax) return ScanLayout::kLong8;
-  return ScanLayout::kPlain;
+  const bool queue = E >= kQueueE;
+  if (!wants_mom && groups <= kTableSplitGroups && scan_lds<1, 16>(K, lds_x, queue) <= kScanLdsMax)
+    return ScanLayout::kTableSplit;
+  if (blocks <= split_blocks(E, L_max) && scan_lds<4, 4>(K, lds_x, queue) <= kScanLdsMax) return ScanLayout::kSplit;
+  if (queue_wins(E, L_max)) return ScanLayout::kPlainQueue;
+  const int q = most_resident(E <= 4 ? 16 : 8, scan_wave_cap(E), blocks,
+                              [&](int w) { return lds_x * 4 + 48 * w; });  // (48: a wave's co-moments)
+  return q == 16 ? ScanLayout::kLong16 : q == 8 ? ScanLayout::kLong8 : ScanLayout::kPlain;
 }
 
 }  // namespace edm
