@@ -26,8 +26,9 @@ constexpr size_t group_extra_lds() {
 // One workgroup's share of a batched scan: query block `bx` of row `row`,
 // every E in [ELO, EHI].  Called by the grid kernel and by the persistent
 // kernel; every early return is uniform across the workgroup.  kQueue: improving
-// candidates are queued, otherwise inserted as they come.
-template <int ELO, int EHI, int Q, int S, bool kQueue>
+// candidates are queued, otherwise inserted as they come.  kGate: queued insertions
+// skip the lists that the row does not need.
+template <int ELO, int EHI, int Q, int S, bool kQueue, bool kGate = false>
 __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, const int bx,
                                            float *__restrict__ smem) {
   constexpr int kT = kWave * Q * S;
@@ -125,9 +126,10 @@ __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, cons
     // alone) and inserted in batches, with every E's key recomputed.
     int32_t *pend = reinterpret_cast<int32_t *>(extra) + wave * (kPendQ * kWave) + lane;
     int n_pend = 0;
+    [[maybe_unused]] const uint32_t needed = __builtin_amdgcn_readfirstlane(static_cast<int>(need));
     // (Every list of the group, wanted or not: their insertions are independent
-    // instructions of one block.  Skipping unwanted ones by a branch each costs
-    // 5-24 % where all are wanted, and both loops in one kernel spill.)
+    // instructions of one block.  Skipping unwanted ones by a branch each (kGate)
+    // costs 5-24 % where all are wanted, and both loops in one kernel spill.)
     auto flush = [&]() {
 #pragma unroll 1
       for (int i = 0; i < kPendQ; ++i) {
@@ -141,6 +143,8 @@ __device__ __forceinline__ void group_scan(const KnnArgs &a, const int row, cons
           acc = acc + d * d;
           if constexpr (j + 1 >= ELO) {
             constexpr int E = j + 1;
+            if constexpr (kGate)
+              if (!((needed >> (E - 1)) & 1u)) return;
             const float key = has && q < L - (E - 1) - Tp ? acc : __builtin_inff();
             list_insert<list_off<ELO>(E), E + 1, TOT>(l, entry(key, q));
           }

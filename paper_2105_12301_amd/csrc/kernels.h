@@ -109,8 +109,9 @@ struct LookupItem {
 // 3: 16-18, 4: 19-20) over its work list (counter: a device int that starts
 // at 0).
 // group: 0-4 the exact E groups {1-8, 9-12, 13-15, 16-18, 19-20}; 5: E 1-4.
+// few_needed: the rows need at most half of the group's E (the time alone).
 hipError_t launch_tables_persistent(const KnnArgs &a, int group, const TableItem *items,
-                                    int n_items, int *counter, int64_t L_max, int wg_per_cu,
+                                    int n_items, int *counter, int64_t L_max, bool few_needed, int wg_per_cu,
                                     int n_cu, hipStream_t st);
 
 // Blocks of 256 queries that one table item of `group` covers in a launch whose

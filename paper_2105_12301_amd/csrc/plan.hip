@@ -42,6 +42,7 @@ constexpr int kNLists = kNGroups + 1 + 2 * kNGram;
 struct Batch {
   int64_t L_max = 0, Lg_max = 0, Ls_max = 0;  // longest library; longest filtered; longest short filtered
   std::array<int64_t, kNLists> t_begin{}, t_count{};
+  std::array<bool, kNLists> t_few{};  // no library needs more than half of the list's E
   std::array<int64_t, EDM_E_MAX + 1> l_begin{}, l_count{}, lds_floats{};
 };
 
@@ -233,6 +234,7 @@ int edm_ccm_plan_create(edm_ctx *ctx, const int64_t *Lx, int64_t Nl, int64_t ldx
     // covers kKnnThreads queries)
     for (int c = 0; c < kNLists; ++c) {
       B.t_begin[c] = static_cast<int64_t>(titems.size());
+      B.t_few[c] = true;
       for (int64_t q = k0; q < k; ++q) {
         const int32_t i = order[static_cast<size_t>(q)];
         int lo = 0, hi = 0;
@@ -240,6 +242,7 @@ int edm_ccm_plan_create(edm_ctx *ctx, const int64_t *Lx, int64_t Nl, int64_t ldx
         uint32_t gm = 0;
         for (int E = lo; E <= hi; ++E) gm |= need[static_cast<size_t>(i)] & (1u << (E - 1));
         if (!gm) continue;
+        if (2 * __builtin_popcount(gm) > hi - lo + 1) B.t_few[c] = false;
         const int64_t m_lo = Lx[i] - (lo - 1) - Tp;
         const int64_t nb = (m_lo + edm::kKnnThreads - 1) / edm::kKnnThreads;
         const int step = c <= kNGroups ? edm::tables_item_blocks(c, B.L_max) : 1;
@@ -384,7 +387,7 @@ int enqueue_plan(edm_ctx *ctx, edm_plan *P, const float *X, const float *Y, floa
   for (const Batch &B : P->batches) {
     for (int g = 0; g <= kNGroups; ++g, ++c)
       EDM_HIP(ctx, edm::launch_tables_persistent(a, g, P->titems + B.t_begin[g], static_cast<int>(B.t_count[g]),
-                                                 P->counters + c, B.L_max, P->tune.tables_wg_per_cu,
+                                                 P->counters + c, B.L_max, B.t_few[g], P->tune.tables_wg_per_cu,
                                                  P->n_cu, st));
     for (int h = 0; h < 2; ++h) {  // short libraries (LDS stride of the short ones), then long ones
       edm::KnnArgs ah = a;

@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kWave * Q * S) void k_sweep_multi(KnnArgs a, int sl
 // ordered by the host longest first, from a device counter until the list is
 // exhausted (every workgroup reaches the exit).  The item index travels
 // through LDS and is made wave-uniform.
-template <int ELO, int EHI, int Q, bool kQueue>
+template <int ELO, int EHI, int Q, bool kQueue, bool kGate>
 __global__ __launch_bounds__(kWave * Q) void k_tables_persistent(KnnArgs a, const TableItem *__restrict__ items,
                                                                  int n_items, int *counter) {
   extern __shared__ __attribute__((aligned(16))) float scan_smem[];
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kWave * Q) void k_tables_persistent(KnnArgs a, cons
     }
     const int row = __builtin_amdgcn_readfirstlane(items[it].row);
     const int blk = __builtin_amdgcn_readfirstlane(static_cast<int>(items[it].blk));
-    group_scan<ELO, EHI, Q, 1, kQueue>(a, row, blk / (Q / 4), scan_smem);  // (blk: a multiple of Q / 4)
+    group_scan<ELO, EHI, Q, 1, kQueue, kGate>(a, row, blk / (Q / 4), scan_smem);  // (blk: a multiple of Q / 4)
   }
 }
 
@@ -274,41 +274,44 @@ struct Tables {
 };
 
 template <int ELO, int EHI>
-Tables tables_of(int64_t L_max) {
+Tables tables_of(int64_t L_max, bool gate) {
   constexpr int64_t kMany = int64_t(1) << 40;  // (a work list keeps every CU busy)
   return with_shape<ELO, EHI>(group_shape<ELO, EHI>(L_max, kMany), [&](auto QC, auto queue) {
     constexpr int Q = decltype(QC)::value;
     constexpr bool kQueue = decltype(queue)::value;
     const size_t lds = static_cast<size_t>(scan_floats(L_max)) * sizeof(float) + group_extra_lds<ELO, EHI, Q, 1, kQueue>();
-    return Tables{&k_tables_persistent<ELO, EHI, Q, kQueue>, Q, lds};
+    if constexpr (kQueue && ELO < EHI) {
+      if (gate) return Tables{&k_tables_persistent<ELO, EHI, Q, true, true>, Q, lds};
+    }
+    return Tables{&k_tables_persistent<ELO, EHI, Q, kQueue, false>, Q, lds};
   });
 }
 
-Tables tables_for(int group, int64_t L_max) {
+Tables tables_for(int group, int64_t L_max, bool gate) {
   switch (group) {
-    case 0: return tables_of<1, 8>(L_max);
-    case 1: return tables_of<9, 12>(L_max);
-    case 2: return tables_of<13, 15>(L_max);
-    case 3: return tables_of<16, 18>(L_max);
-    case 4: return tables_of<19, 20>(L_max);
-    default: return tables_of<1, 4>(L_max);
+    case 0: return tables_of<1, 8>(L_max, gate);
+    case 1: return tables_of<9, 12>(L_max, gate);
+    case 2: return tables_of<13, 15>(L_max, gate);
+    case 3: return tables_of<16, 18>(L_max, gate);
+    case 4: return tables_of<19, 20>(L_max, gate);
+    default: return tables_of<1, 4>(L_max, gate);
   }
 }
 
 }  // namespace
 
 int tables_item_blocks(int group, int64_t L_max) {
-  return group < 0 || group >= kTables ? 1 : tables_for(group, L_max).waves / 4;
+  return group < 0 || group >= kTables ? 1 : tables_for(group, L_max, false).waves / 4;
 }
 
 hipError_t launch_tables_persistent(const KnnArgs &a, int group, const TableItem *items,
-                                    int n_items, int *counter, int64_t L_max, int wg_per_cu,
+                                    int n_items, int *counter, int64_t L_max, bool few_needed, int wg_per_cu,
                                     int n_cu, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
   if (group < 0 || group >= kTables) return hipErrorInvalidValue;
   KnnArgs b = a;
   b.lds_x = scan_floats(L_max);
-  const Tables t = tables_for(group, L_max);
+  const Tables t = tables_for(group, L_max, few_needed);
   TimedLaunch timed(EDM_KF_BATCHED_SCAN, st);
   hipError_t e = allow_lds(t.fn, t.lds);
   if (e != hipSuccess) return e;
