@@ -151,12 +151,12 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(K, S)) void k_knn(KnnArgs 
   // +inf; the status word reports non-finite input.
   Mom mine = mom_zero();
   const int64_t base = static_cast<int64_t>(slot) * a.tbl_stride + static_cast<int64_t>(p) * K;
-  auto distance = [&](int q) {
+  auto distance = [&](const float (&v)[EM], int q) {
     double s2 = 0.0;
 #pragma unroll
     for (int j = 0; j < EM; ++j) {
       if (E_T || j < E) {
-        const double d = static_cast<double>(vp[j]) - static_cast<double>(xs[q + j * tau]);
+        const double d = static_cast<double>(v[j]) - static_cast<double>(xs[q + j * tau]);
         s2 += d * d;
       }
     }
@@ -178,9 +178,12 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(K, S)) void k_knn(KnnArgs 
     }
     __syncthreads();
     if (active) {
+      float vq[EM];  // (read again: the merges have no registers for them)
+#pragma unroll
+      for (int j = 0; j < EM; ++j) vq[j] = E_T || j < E ? xs[p + j * tau] : 0.0f;
       for (int r = sp; r < K; r += S) {
         const int q = nbr[r * kWave];
-        const double dq = distance(q);
+        const double dq = distance(vq, q);
         D[r * kWave] = dq;
         if (a.idx) a.idx[base + r] = q;
         if (a.dist) a.dist[base + r] = static_cast<float>(dq);
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(kWave * Q * S, knn_waves(K, S)) void k_knn(KnnArgs 
 #pragma unroll 1
     for (int r = 0; r < K; ++r) {
       const int q = qi[0] < 0 ? 0 : qi[0];
-      const double dq = distance(q);
+      const double dq = distance(vp, q);
       dmin = fmin(dmin, dq);
 #pragma unroll
       for (int i = 0; i < K - 1; ++i) {

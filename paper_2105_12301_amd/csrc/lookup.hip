@@ -68,6 +68,14 @@ constexpr int64_t kLdsFloats = (160 * 1024 - 512) / 4;
 static_assert(kGroups * kSubs == kWave, "lane layout");
 static_assert(kLookupItemMaxTargets == 16, "tile layout assumes at most 16 targets");
 
+// The lane, computed anew: what depends on it is not kept in registers across the
+// tiles (items) of a workgroup, whose walk has none to spare.
+__device__ __forceinline__ int own_lane() {
+  int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+  asm volatile("" : "+v"(lane));
+  return lane;
+}
+
 struct Sums {
   double so, sp, soo, spp, sop;
 };
@@ -157,7 +165,7 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
                                            float *const (&pred)[TPL], const float (&c)[TPL],
                                            Sums (&s)[TPL], const Split &split) {
   static_assert(!kSplit || TPL == 1, "exchange area: one target a lane");
-  const int lane = threadIdx.x & (kWave - 1);
+  const int lane = own_lane();
   const int g = lane >> 2;
   const int sub = lane & (kSubs - 1);
   // idle sub-lanes (T < 4) read sub-lane 0's targets; their sums are unused
@@ -204,7 +212,7 @@ __device__ __forceinline__ void tile_pairs(const int32_t *__restrict__ tidx,
       float ov[TPL];
       lds_read<TPL>(row_of(p), ov);
       // gathers in chunks of kChunk neighbours (bounds the registers in flight)
-      constexpr int kChunk = TPL == 4 ? 6 : (TPL == 2 ? 8 : 16);
+      constexpr int kChunk = TPL == 4 ? (K <= 12 ? 6 : K <= 20 ? 4 : K <= 24 ? 3 : 2) : (TPL == 2 ? 8 : 16);
       each<0, (K + kChunk - 1) / kChunk>([&](auto CC) {
         constexpr int i0 = decltype(CC)::value * kChunk;
         constexpr int i1 = i0 + kChunk < K ? i0 + kChunk : K;
@@ -321,7 +329,7 @@ struct TileLoad {
     return __builtin_amdgcn_readfirstlane(tile.ids ? tile.ids[tile.t0 + t] : tile.t0 + t);
   }
   __device__ __forceinline__ void load(const LookupArgs &a, const Tile &tile, int off, int n) {
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = own_lane();
     const float *row[4];
     int last[4];  // the target's last sample: no address past it
 #pragma unroll
@@ -344,7 +352,7 @@ struct TileLoad {
     }
   }
   __device__ __forceinline__ void store(const LookupArgs &a, const Tile &tile, int off, int n, float *vs, int T) {
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = own_lane();
     const int tq = first_target();
     float c[4];
     int end[4];  // samples of the window that the target has
@@ -413,33 +421,44 @@ __device__ __forceinline__ void wave_library(const LookupArgs &a, const int32_t 
                                              const float *tw, int lib, int64_t Lx, int m,
                                              const float *vs, const float *cs, const int *tgt,
                                              int Tn, int T, const Split &split = Split{}) {
-  const int lane = threadIdx.x & (kWave - 1);
+  const int lane = own_lane();
   const int sub = lane & (kSubs - 1);
-  bool ok[TPL];
-  int id[TPL];
+  // target u of the lane, or -1 where there is none or the pair is undefined
+  auto target = [&](int u) {
+    const int t = sub * TPL + u;
+    const bool in = sub * TPL < T && t < Tn;
+    const int id = in ? tgt[t] : 0;
+    return in && !(a.Ly_dev && a.Ly_dev[id] < Lx) ? id : -1;
+  };
   float c[TPL];
   float *pred[TPL];
 #pragma unroll
   for (int u = 0; u < TPL; ++u) {
-    const int t = sub * TPL + u;
-    const bool in = sub * TPL < T && t < Tn;
-    id[u] = in ? tgt[t] : 0;
-    ok[u] = in && !(a.Ly_dev && a.Ly_dev[id[u]] < Lx);
-    c[u] = in ? cs[t] : 0.0f;
-    pred[u] = (TPL == 1 && ok[u] && a.pred) ? a.pred + static_cast<int64_t>(id[u]) * a.ldpred : nullptr;
+    c[u] = 0.0f;
+    pred[u] = nullptr;
   }
   Sums s[TPL];
   // predictions are written only with one target per lane (tiles of at most
   // 4 targets), which keeps the wider instantiations free of their registers
-  if (TPL == 1 && a.pred)
+  if (TPL == 1 && a.pred) {
+    const int id = target(0);
+    if (id >= 0) {
+      c[0] = cs[sub];
+      pred[0] = a.pred + static_cast<int64_t>(id) * a.ldpred;
+    }
     tile_pairs<K, TPL, TPL == 1, kSplit>(tidx, tw, m, vs, T, pred, c, s, split);
-  else
+  } else {
     tile_pairs<K, TPL, false, kSplit>(tidx, tw, m, vs, T, pred, c, s, split);
+  }
   if (kSplit && (split.part != 0 || m <= 0)) return;
+  // (the targets are read again rather than kept over the walk, whose registers
+  // they would not fit beside)
   if (a.rho && lane < kSubs) {
 #pragma unroll
-    for (int u = 0; u < TPL; ++u)
-      if (ok[u]) a.rho[static_cast<int64_t>(lib) * a.ldrho + id[u]] = pair_rho(m, s[u]);
+    for (int u = 0; u < TPL; ++u) {
+      const int id = target(u);
+      if (id >= 0) a.rho[static_cast<int64_t>(lib) * a.ldrho + id] = pair_rho(m, s[u]);
+    }
   }
 }
 
