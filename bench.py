@@ -19,7 +19,8 @@ Prints one JSON line.  Besides the driver's fields it carries:
 * cpu_baseline: the CPU oracle timed on the host cores on 16/10000 of the
   step (16 series' E sweeps and 16 libraries' full cross-map rows);
 * parity: rho of those rows and sweeps against the oracle, E* with the
-  near-tie rule, and the libraries' kNN tables bit for bit.
+  near-tie rule, the libraries' kNN tables bit for bit, and their cross map
+  through the filter's tables bit for bit against the plain form's.
 
 Other workloads (--workload): network (1024 x 5000 logistic network), uneven
 (batched plan on 4096 series of uneven length), learned (network-selected E on
@@ -432,12 +433,18 @@ def bench_main(args, torch, edm, synth, wl, name):
                 gh = hashlib.sha1(idx.cpu().numpy().astype(np.int32).tobytes()).hexdigest()
                 tbl_ok &= gh == h
                 n_tbl += 1
-        ctx.set_form(edm.EDM_FORM_CHOSEN)
-        tbl_ok_c = True
-        for i, (_, hashes) in list(rows.items())[:4]:
-            for E, h in hashes.items():
-                idx, _, _ = edm.edm_knn(Xd[i].contiguous(), E, 1, 0, want_dist=False, want_w=False, ctx=ctx)
-                tbl_ok_c &= hashlib.sha1(idx.cpu().numpy().astype(np.int32).tobytes()).hexdigest() == h
+        # tables through the filter (a series' own table takes the exact scan in
+        # every form): the libraries' cross map in the chosen form, bit for bit
+        # against the plain form's and the timed step's
+        ids = sorted(rows)
+        Xl = Xd[torch.as_tensor(ids, device=Xd.device)].contiguous()
+        Ed = torch.from_numpy(np.ascontiguousarray(r["Es"], dtype=np.int32)).to(Xd.device)
+        got_f = []
+        for f in (edm.EDM_FORM_PLAIN, edm.EDM_FORM_CHOSEN):
+            ctx.set_form(f)
+            got_f.append(edm.edm_ccm(Xl, Ed, Y=Xd, ctx=ctx).cpu().numpy().view(np.int32))
+        step_rows = np.ascontiguousarray(np.stack([r["rho"][i] for i in ids]), dtype=np.float32).view(np.int32)
+        tbl_ok_c = bool(np.array_equal(got_f[0], got_f[1]) and np.array_equal(got_f[1], step_rows))
         ctx.sync()
         frac = len(libs) / N
         out["cpu_baseline"] = {
