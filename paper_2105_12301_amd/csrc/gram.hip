@@ -1046,7 +1046,10 @@ size_t small_lds(int64_t L_max) {
 }
 
 // Blocks of 256 queries up to which a sweep takes the one-launch form: its 7
-// groups then make up to two rounds of workgroups on 256 compute units.
+// groups then make up to two rounds of workgroups on 256 compute units.  With
+// few groups the times cross soon after (E 1-5 of 1000-sample series, one launch
+// against one a group: 64 blocks 114 / 138 us, 80 115 / 138, 96 168 / 139), with all
+// of them at about 256 (E 1-20: 64 blocks 218 / 657, 128 402 / 748, 256 742 / 762).
 constexpr int64_t kSmallBlocks = 64;
 
 }  // namespace

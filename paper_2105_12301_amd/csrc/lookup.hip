@@ -736,7 +736,9 @@ Shape shape_for(int T, int nslots, int64_t m_max, int64_t ntgt) {
 }
 
 // Workgroups of one E up to which the E go into one launch: a round of the
-// chip, so that a launch of its own would not fill it.
+// chip, so that a launch of its own would not fill it.  (Sweep and cross map of E
+// 1-20, one launch against one an E: 8 x 1000 219 / 345 us, 64 x 1000 912 / 976, 96 x
+// 1000 1559 / 1595, 96 x 300 784 / 809; past the line 128 x 300 825 / 779.)
 constexpr int64_t kAllBlocks = kCus;
 
 }  // namespace

@@ -5,7 +5,7 @@
 // selection of Section 2.1 step 1 / Section 3.4 of the kEDM paper):
 //   x[L] -> conv(1->C, KW) -> ReLU -> conv(C->C, KW) -> ReLU -> conv(C->C, KW)
 //        -> ReLU -> mean over time -> linear(C->20) -> logits over E = 1..20
-// with zero "same" padding.  Activations are [B][C][L] row-major.
+// with zero "same" padding.
 //
 // Training (float32): activations and their gradients are [B][L][C] in the
 // workspace, channels fastest.  The C -> C convolutions, their data gradients
@@ -306,7 +306,10 @@ __global__ void k_w_to_bf16(const float *__restrict__ w2, const float *__restric
 }
 
 // Sums over time of layer 3: part[b][split][C], split = blockIdx.x of gridDim.x.
-template <int C>
+// kShort: the series ends well before its only tile, and waves without a row of
+// it skip their products (4000 series of 8, C = 32: 147 -> 76 us with two
+// workgroups a CU; beside whole tiles the branches cost 0.5 %).
+template <int C, bool kShort>
 __global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *__restrict__ X, int64_t ldx, int L,
                                                    const float *__restrict__ w1, const float *__restrict__ b1,
                                                    const float *__restrict__ b2, const float *__restrict__ b3,
@@ -375,10 +378,7 @@ __global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *
 #pragma unroll 1
   for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
     const int t0 = tile * TO;
-    // Rows of layer 3 that lie in the series: waves whose rows none of these
-    // need skip their products (their rows of LDS are never used), as in the
-    // tile of a short series, whose other seven waves would only be in the way.
-    const int rows = L - t0 < TO ? L - t0 : TO;
+    const int rows = L - t0 < TO ? L - t0 : TO;  // of layer 3 that lie in the series
     // xin[i] = x[t0 - 3 HALO + i], zero outside the series
     for (int i = tid; i < R1 + 2 * HALO; i += IT) {
       const int t = t0 - 3 * HALO + i;
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *
     store_w();
     load_w(1);
     // layer 1: row r is time t0 - 2 HALO + r
-    for (int r = tid / CG; r < rows + 4 * HALO; r += IT / CG) {
+    for (int r = tid / CG; r < (kShort ? rows + 4 * HALO : R1); r += IT / CG) {
       const int t = t0 - 2 * HALO + r;
       float xv[KW];
 #pragma unroll
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *
       else *reinterpret_cast<uint2 *>(a1 + r * I::XS + c0) = uint2{o[0], o[1]};
     }
     __syncthreads();
-    if (32 * wave < rows + 2 * HALO) {
+    if (!kShort || 32 * wave < rows + 2 * HALO) {
       conv(a1);  // layer 2: row r is time t0 - HALO + r
       const int t = t0 - HALO + row;
       const bool in = t >= 0 && t < L;
@@ -429,7 +429,7 @@ __global__ __launch_bounds__(IT, C == 32 ? 4 : 2) void k_net_infer(const float *
     store_w();
     load_w(0);
     __syncthreads();
-    if (32 * wave >= rows) continue;  // (the next tile's barriers are the same for every wave)
+    if (kShort && 32 * wave >= rows) continue;  // (this was the only tile)
     conv(a2);  // layer 3: row r is time t0 + r
     const bool in = row < rows;
 #pragma unroll
@@ -934,13 +934,14 @@ template <int C>
 hipError_t launch_infer(const NetParams &P, const float *X, int64_t B, int64_t L, int64_t ldx, const uint16_t *wb,
                         float *part, hipStream_t st) {
   constexpr size_t shm = Infer<C>::lds;
+  const auto fn = L <= TO - 32 ? &k_net_infer<C, true> : &k_net_infer<C, false>;
   if (shm > 65536) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_net_infer<C>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(shm));
     if (e != hipSuccess) return e;
   }
   const dim3 grid(static_cast<unsigned>(infer_splits(B, L)), static_cast<unsigned>(B));
-  hipLaunchKernelGGL(k_net_infer<C>, grid, dim3(IT), shm, st, X, ldx, static_cast<int>(L), P.w1, P.b1, P.b2, P.b3,
+  hipLaunchKernelGGL(fn, grid, dim3(IT), shm, st, X, ldx, static_cast<int>(L), P.w1, P.b1, P.b2, P.b3,
                      reinterpret_cast<const u32x4_t *>(wb), infer_tiles(L), part);
   return hipGetLastError();
 }

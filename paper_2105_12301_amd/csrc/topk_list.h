@@ -226,9 +226,10 @@ constexpr int64_t split_blocks(int E, int64_t L_max) {
 //   steps however many compute units are idle; splitting it over waves and
 //   merging their lists (list_merge, log2 S rounds through LDS) shortens it.
 //   kTableSplit writes tables only: a sweep's co-moments are merged per 256
-//   queries.  One table of 10000 samples, E = 1, 12: 64, 173 us by 16 waves, 210,
-//   525 by 4; more than 256 groups of 64 queries are a second round of the
-//   chip, which the other form does without.
+//   queries.  Up to one group of 64 queries a CU, where it wins at every E and
+//   length (one table of 10000 samples, E = 1, 12: 64, 173 us by 16 waves, 210, 525
+//   by 4; 256 groups of 1000-sample series, E = 12: 42, 91); a second round
+//   still wins (512 groups 76 / 94), a fourth loses (1024 140 / 96).
 inline ScanLayout scan_layout(int64_t nslots, int64_t L_max, int E, int K, bool wants_mom) {
   const int64_t lds_x = L_max + 138;  // (scan_floats)
   const int64_t groups = (L_max + 63) / 64 * nslots, blocks = (L_max + 255) / 256 * nslots;

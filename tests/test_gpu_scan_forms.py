@@ -63,7 +63,7 @@ def test_sweeps_match_two_kernel_form(edm, kind, N, L, E_max, tau):
 
 
 # long series at every E: plain (one scan per E), grouped and filtered scans
-@pytest.mark.parametrize("N,L", [(4, 16000), (36, 8300), (5, 32000), (30, 9000)])
+@pytest.mark.parametrize("N,L", [(4, 16000), (36, 8300), (5, 32000), (30, 9000), (2, 32768)])
 def test_long_sweeps_agree_between_forms(edm, N, L):
     X = torch.from_numpy(_series("maps", N, L)).cuda()
     lens = np.full(N, L)
