@@ -263,7 +263,8 @@ def family_work(fam, form, N, L, E_max, E_star):
     used = sorted(set(int(e) for e in E_star if e >= 1))
     if fam == "lookup":
         return lookup_bytes(N, L, E_star), "hbm", \
-            "k_lookup<K>: 4 L B of target + 4 B rho per pair, 8 m k B of table per (library, E)"
+            "k_lookup<K>: 4 L B of target + 4 B rho per pair, 8 m k B of table per (library, E); algorithmic " \
+            "bytes, of which HBM moves a fraction (the targets stay in the last-level cache): issue and LDS bound it"
     if fam == "filter_scan":
         return gram_flops(N, L, 1), "mfma", \
             "k_gram<E_lo,E_hi>: BF16 Gram product, 2 E_hi flops per ordered pair per E group"

@@ -27,11 +27,11 @@ struct TimedLaunch {
 // The calling thread is inside a TimingScope of a context with timing on.
 bool timing_on();
 
-constexpr int kKnnThreads = 256;  // 4 waves of 64 query points per workgroup
+constexpr int kKnnThreads = 256;  // query points per block of co-moments (and per plain workgroup)
 
-// Arguments of the fused embedding + distance + top-k + weights kernel.
-// One workgroup handles 256 consecutive query points of one library; the
-// grid's y index is the library slot.
+// Arguments of the fused embedding + distance + top-k + weights kernels.  A
+// workgroup handles 64 to 1024 consecutive query points of one library (the
+// layouts in topk_list.h); the grid's y index is the library slot.
 struct KnnArgs {
   const float *X;            // libraries, row `row` at X + row*ldx
   int64_t ldx;

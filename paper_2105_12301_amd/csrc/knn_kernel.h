@@ -25,14 +25,15 @@
 // * The ranking key is the float32 sum of Algorithm 1 in lag order with a
 //   rounding after every operation: this file is compiled with contraction off
 //   (and says so with a pragma), and fp32 denormals are kept (gfx950 default).
-// * Improving candidates are queued in LDS and inserted in batches
-//   (topk_list.h).  What bounds the scan is VALU issue: 3 E + ~20 instructions a
-//   step (10000 x 2000, E = 20: 54 ms against 31 ms for its 61 operations a
-//   pair at one a lane and clock; the sweep over
-//   E = 1..20, epilogues included, 668 -> 595 ms against insertion as they come).
+// * Improving candidates are inserted into the packed lists as they come, or
+//   queued in LDS and inserted in batches where that pays (queue_wins in
+//   topk_list.h).  What bounds the scan is VALU issue: 3 E + ~20 instructions a
+//   step (2000 x 2000, E = 20: 10.9 ms against 6.2 ms for its 61 operations a
+//   pair at one a lane and clock; before packed entries 12.5 ms).
 // * Few workgroups (one series): the candidates of a query are split over 4 or
-//   16 waves whose lists are merged (one series of 1000, E = 3: 86 -> 15 us;
-//   10000 samples, E = 20: 560 us through the filter -> 277 us).
+//   16 waves whose lists are merged and whose epilogue they share (one series
+//   of 1000, E = 3: 86 -> 12 us; 10000 samples, E = 20: 560 us through the filter
+//   -> 255 us).
 // * Weights need only the k winners: their distances are recomputed in
 //   float64 from the staged samples, w_i = exp(-d_i / d_min) normalised
 //   (Section 2.1 step 3, "Normalize D_k" in Algorithm 2).

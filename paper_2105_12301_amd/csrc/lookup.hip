@@ -37,7 +37,7 @@
 // Grid kernel: blockIdx.x = tile of targets, blockIdx.y = group of 16
 // library slots (one wave each); consecutive workgroups share their
 // libraries' tables in L2; a wave that is done with its library loads its part
-// of the next tile meanwhile.  10000 series of 2000 samples: 199 -> 177 ms for
+// of the next tile meanwhile.  10000 series of 2000 samples: 199 -> 166 ms for
 // all E (rows loaded in quarters, tiles staged in lines: 97 -> 13 of 313 -> 240
 // thousand cycles a tile at K = 8); of the rest, 75 % is the walk itself
 // (issue: gathers, broadcasts and 4 fused adds a neighbour) and 19 % waiting for
@@ -710,7 +710,7 @@ struct Shape {
 // rounds of one per CU, a round taking (in walks) 1/W for the walk by W waves,
 // three quarters of that at 4 targets, and 0.15 for staging and exchange.  One
 // library of 1000 queries against 2000 targets: 48 -> 18 us with the
-// predictions; eight libraries: 374 -> 334 us for sweep and cross map.
+// predictions; eight libraries: 374 -> 331 us for sweep and cross map.
 constexpr int64_t kCus = 256;
 Shape shape_for(int T, int nslots, int64_t m_max, int64_t ntgt) {
   while (T > 1 && T / 2 >= ntgt) T >>= 1;  // no wider than the target count needs

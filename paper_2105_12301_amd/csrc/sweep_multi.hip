@@ -13,8 +13,8 @@
 // Everything else follows the per-E kernel in knn_kernel.h: library staged in
 // LDS, one query per lane, diagonal candidate order (lane l sees q = s + l), a
 // sliding window of samples in registers, improving candidates queued in LDS
-// and inserted in batches (10000 x 2000, Tp = 1: E 1-4 27.2 -> 22.1 ms, all
-// five groups 453 -> 388 ms against insertion as they come), float64 weights of
+// and inserted in batches where that pays (10000 x 2000, Tp = 1: E 1-4 27.2 -> 21
+// ms, all five groups 453 -> 388 ms against insertion as they come), float64 weights of
 // the winners, the self-prediction and its Pearson
 // co-moments reduced per block.  tau = 1 only (the sweep's lag); other lags
 // use the per-E kernel.

@@ -87,6 +87,7 @@ __device__ __forceinline__ void list_merge(double (&l)[TOT], F &&other) {
 // as the fullest lane holds, not as many as the union of steps.  The k-th key
 // a lane tests against is the one of the last flush, so entries that no longer
 // enter are queued too; the insertion leaves the list as it is for them.
+// (Where this pays: queue_wins below.)
 constexpr int kPend = 8;          // queue positions per lane
 constexpr int kPendStep = 4;      // candidates between two looks at the fill
 constexpr int kPendBytes = kPend * 8 * 64;  // LDS per wave
