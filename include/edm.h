@@ -62,7 +62,8 @@ typedef struct edm_ctx edm_ctx;
  * EDM_FORM_CHOSEN : EDM_FORM_BATCHED, and for E >= 5 (series up to 32000
  *                   samples) a BF16 matrix-core estimate of every key filters
  *                   the candidates; the ones that may enter a top-k list are
- *                   re-ranked with the exact float32 key.
+ *                   re-ranked with the exact float32 key; calls of few
+ *                   queries take the exact scan where it is faster.
  * EDM_FORM_TWO_KERNEL: the paper's own form of the kNN step (Section 3.3):
  *                   Algorithm 1 writes each library's whole distance matrix
  *                   (float32 keys, m x m) to device memory, then Algorithm 2
@@ -138,7 +139,8 @@ void edm_ctx_destroy(edm_ctx *ctx);
 enum {
   EDM_KF_EXACT_SCAN = 0,        /* k_knn: one candidate scan per (library, E)        */
   EDM_KF_BATCHED_SCAN = 1,      /* k_sweep_multi, k_tables_persistent: exact scans
-                                   of groups of E values; k_sweep_small's, which
+                                   of groups of E values (k_knn where a group's
+                                   tables are of one E); k_sweep_small's, which
                                    timing runs as launches of their own             */
   EDM_KF_FILTER_PREP = 2,       /* k_gram_mean, k_gram_norms                         */
   EDM_KF_FILTER_SCAN = 3,       /* k_gram, k_gram_items: matrix-core filtered scans;
@@ -190,8 +192,10 @@ int edm_embed(edm_ctx *ctx, const float *x, int64_t L, int32_t E, int32_t tau,
  *        step 3; when min d = 0 the weights are 1 at zero distance and 0
  *        elsewhere before normalising                               (or NULL)
  * nq = L - (E-1)*tau - Tp.
- * In EDM_FORM_CHOSEN with tau = 1, k = E+1, E >= 5, L <= 32000 and dist ==
- * NULL, the table comes from the matrix-core filtered scan (same result). */
+ * The exact scan, its candidates split over waves up to 16384 samples.  In
+ * EDM_FORM_CHOSEN longer series (up to 32000 samples) with tau = 1, k = E+1,
+ * E >= 5, no exclusion radius and dist == NULL take the matrix-core filtered
+ * scan (same result). */
 int edm_knn(edm_ctx *ctx, const float *x, int64_t L, int32_t E, int32_t tau,
             int32_t Tp, int32_t k, int32_t *idx, float *dist, float *w);
 
